@@ -29,6 +29,7 @@
 namespace {
 
 typedef __bf16 bf16;
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -139,92 +140,246 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
     }
 }
 
-// Larger wave tiles for large layers: v_mfma_f32_32x32x16_bf16 (lane l
-// holds A[l % 32][8 (l / 32) + v], B[8 (l / 32) + v][l % 32] for v < 8 and
-// D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] for v < 16; verified on the
-// device).  A wave owns 64 pixels x (32 CT) output channels: per step of 16
-// input channels it loads two pixel operands and CT weight operands and
-// issues 2 CT MFMAs, twice the work per loaded byte of the 16x16x32 tiling.
+// Tiled convolution: a block owns a TX x TY pixel tile (P = 32 MP WP pixels)
+// and 32 NC WC output channels.  The input tile with its one-pixel ring is
+// staged once in LDS with all input channels (zeros outside the image, so
+// the taps need no masks), the weights stream through two LDS buffers of KS
+// reduction elements each (the next stage's global loads are in flight while
+// the current one is multiplied), and every MFMA operand is one 16-byte LDS
+// read.  Rows are padded by 16 bytes: 16 lanes that read 16 bytes at that
+// stride (an odd multiple of 16 bytes) touch every bank once.
+// v_mfma_f32_32x32x16_bf16: lane l holds A[l % 32][8 (l / 32) + v],
+// B[8 (l / 32) + v][l % 32] for v < 8 and D[8 (v / 4) + 4 (l / 32) + v % 4]
+// [l % 32] for v < 16.  Weights are the A operand and pixels the B operand,
+// so a lane ends with groups of four consecutive channels of one pixel; the
+// block writes them to LDS and from there out in 16-byte pieces.  The
+// reduction runs tap by tap and channel by channel in one accumulator, the
+// order of conv_fwd_kernel (a 32x32x16 chain gives the same bits as a
+// 16x16x32 one, checked on the device), so the path taken never shows in
+// the result.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int kConv32MinPix = 65536;  // layers with at least this many pixels
-                                      // use the 64-pixel wave tiles
 
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int CT>
-__global__ __launch_bounds__(256) void conv_fwd32_kernel(ConvArgs a) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int px0 = blockIdx.x * 256 + 64 * wv;
-  const int co0 = blockIdx.y * (32 * CT);
+constexpr int kLdsBytes = 160 * 1024;
+
+template <int MP, int NC, int WP, int WC, int TX, int KS>
+struct ConvTile {
+  static constexpr int P = 32 * MP * WP, CB = 32 * NC * WC, TY = P / TX;
+  static constexpr int WS = 2 * KS + 16;   // LDS bytes per weight row
+  static constexpr int OS = 2 * CB + 16;   // LDS bytes per output pixel
+  static_assert(WP * WC == 4 && TY * TX == P && KS % 32 == 0 && 288 % KS == 0, "tile");
+  static size_t lds(int cin) {
+    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + 2 * (size_t)CB * WS;
+    return in > (size_t)P * OS ? in : (size_t)P * OS;
+  }
+};
+
+template <int MP, int NC, int WP, int WC, int TX, int KS>
+__global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
+  using L = ConvTile<MP, NC, WP, WC, TX, KS>;
+  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2);
+  extern __shared__ __align__(16) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = wv % WP, wc = wv / WP;
   const int r = lane & 31, g = lane >> 5;
-  int pidx[2], py[2], pxx[2];
-  bool pv[2];
+  int tile = blockIdx.x;
+  const int tx = tile % tiles_x;
+  tile /= tiles_x;
+  const int ty = tile % tiles_y, img = tile / tiles_y;
+  const int x0 = tx * TX, y0 = ty * TY, co0 = blockIdx.y * L::CB;
+  const int S = 2 * a.cin + 16;
+  char* sx = smem;
+  char* sw = smem + HP * S;
+  const int nst = 9 * a.cin / KS;
+
+  // weights of one stage: CB rows of KS consecutive reduction elements
+  constexpr int kRowVec = KS / 8, kWVec = L::CB * kRowVec, kWPer = (kWVec + 255) / 256;
+  bf16x8 wreg[kWPer];
+  auto load_w = [&](int st) {
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    const int p = px0 + 32 * s + r;
-    pv[s] = p < a.npix;
-    const int q = pv[s] ? p : 0;
-    pidx[s] = q;
-    pxx[s] = q % a.wd;
-    py[s] = (q / a.wd) % a.h;
-  }
-  f32x16 acc[2][CT];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int b = 0; b < CT; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[s][b][v] = 0.f;
-  for (int t = 0; t < 9; ++t) {
-    const int dy = t / 3 - 1, dx = t % 3 - 1;
-    const bf16* xa[2];
-    bool ok[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int yy = py[s] + dy, xx = pxx[s] + dx;
-      ok[s] = pv[s] && yy >= 0 && yy < a.h && xx >= 0 && xx < a.wd;
-      xa[s] = a.x + (long long)(ok[s] ? pidx[s] + dy * a.wd + dx : 0) * a.ldx + 8 * g;
+    for (int i = 0; i < kWPer; ++i) {
+      const int v = tid + 256 * i;
+      if (kWVec % 256 == 0 || v < kWVec)
+        wreg[i] = *reinterpret_cast<const bf16x8*>(
+            a.w + (long long)(co0 + v / kRowVec) * 9 * a.cin + st * KS + 8 * (v % kRowVec));
     }
-    const bf16* wb[CT];
+  };
+  auto store_w = [&](int buf) {
 #pragma unroll
-    for (int b = 0; b < CT; ++b)
-      wb[b] = a.w + ((long long)(co0 + 32 * b + r) * 9 + t) * a.cin + 8 * g;
-    for (int c0 = 0; c0 < a.cin; c0 += 16) {
-      bf16x8 A[2], B[CT];
+    for (int i = 0; i < kWPer; ++i) {
+      const int v = tid + 256 * i;
+      if (kWVec % 256 == 0 || v < kWVec)
+        *reinterpret_cast<bf16x8*>(sw + buf * (L::CB * L::WS) + (v / kRowVec) * L::WS +
+                                   16 * (v % kRowVec)) = wreg[i];
+    }
+  };
+  load_w(0);
+  {
+    // input tile: HP pixels x cin channels, eight 16-byte loads in flight
+    const int cv = a.cin >> 3, nvec = HP * cv;
+    const bf16* xi = a.x + (long long)img * a.h * a.wd * a.ldx;
+    int px = tid / cv, c = tid % cv;
+    const int qs = 256 / cv, rs = 256 % cv;
+    for (int base = 0; base < nvec; base += 8 * 256) {
+      bf16x8 v[8];
+      int at[8];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        A[s] = *reinterpret_cast<const bf16x8*>(xa[s] + c0);
-        if (!ok[s]) A[s] = bf16x8{};
+      for (int u = 0; u < 8; ++u) {
+        const bool in = base + 256 * u + tid < nvec;
+        const int yy = px / HX, xx = px - yy * HX;
+        const int y = y0 + yy - 1, x = x0 + xx - 1;
+        at[u] = in ? px * S + 16 * c : -1;
+        v[u] = bf16x8{};
+        if (in && y >= 0 && y < a.h && x >= 0 && x < a.wd)
+          v[u] = *reinterpret_cast<const bf16x8*>(xi + (long long)(y * a.wd + x) * a.ldx + 8 * c);
+        px += qs;
+        c += rs;
+        if (c >= cv) {
+          c -= cv;
+          ++px;
+        }
       }
 #pragma unroll
-      for (int b = 0; b < CT; ++b) B[b] = *reinterpret_cast<const bf16x8*>(wb[b] + c0);
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int b = 0; b < CT; ++b) acc[s][b] = mfma32(A[s], B[b], acc[s][b]);
+      for (int u = 0; u < 8; ++u)
+        if (at[u] >= 0) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
     }
   }
+  store_w(0);
+  __syncthreads();
+
+  f32x16 acc[NC][MP];
 #pragma unroll
-  for (int s = 0; s < 2; ++s)
+  for (int b = 0; b < NC; ++b)
 #pragma unroll
-    for (int b = 0; b < CT; ++b) {
-      const int co = co0 + 32 * b + r;
-      const float bias = a.bias ? a.bias[co] : 0.f;
+    for (int s = 0; s < MP; ++s)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int p = px0 + 32 * s + 8 * (v / 4) + 4 * g + (v % 4);
-        if (p >= a.npix) continue;
-        float val = acc[s][b][v] + bias;
-        if (a.relu) val = fmaxf(val, 0.f);
-        if (a.out_f32)
-          static_cast<float*>(a.y)[(long long)p * a.ldy + co] = val;
-        else
-          static_cast<bf16*>(a.y)[(long long)p * a.ldy + co] = (bf16)val;
+      for (int v = 0; v < 16; ++v) acc[b][s][v] = 0.f;
+  const char* xb[MP];
+#pragma unroll
+  for (int s = 0; s < MP; ++s) {
+    const int q = 32 * (wp * MP + s) + r;
+    xb[s] = sx + ((q / TX) * HX + q % TX) * S + 16 * g;
+  }
+  const int wrow = (32 * NC * wc + r) * L::WS + 16 * g;
+  int c2 = 0, tapoff = 0, tcol = 0;   // 2 x channel, byte offset and column of the tap
+  for (int st = 0; st < nst; ++st) {
+    if (st + 1 < nst) load_w(st + 1);
+    const char* wb = sw + (st & 1) * (L::CB * L::WS) + wrow;
+#pragma unroll
+    for (int j = 0; j < KS / 32; ++j) {
+      const int off = tapoff + c2;
+      bf16x8 A[2][NC], B[2][MP];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int s = 0; s < MP; ++s)
+          B[h][s] = *reinterpret_cast<const bf16x8*>(xb[s] + off + 32 * h);
+#pragma unroll
+        for (int b = 0; b < NC; ++b)
+          A[h][b] = *reinterpret_cast<const bf16x8*>(wb + b * (32 * L::WS) + 64 * j + 32 * h);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int b = 0; b < NC; ++b)
+#pragma unroll
+          for (int s = 0; s < MP; ++s) acc[b][s] = mfma32(A[h][b], B[h][s], acc[b][s]);
+      c2 += 64;
+      const bool next = c2 == 2 * a.cin;   // uniform: the next tap
+      tapoff += next ? (tcol == 2 ? TX * S : S) : 0;
+      tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
+      c2 = next ? 0 : c2;
+    }
+    if (st + 1 < nst) store_w((st + 1) & 1);
+    __syncthreads();
+  }
+
+  if (a.out_f32) {
+#pragma unroll
+    for (int b = 0; b < NC; ++b)
+#pragma unroll
+      for (int s = 0; s < MP; ++s) {
+        const int q = 32 * (wp * MP + s) + r;
+        const int y = y0 + q / TX, x = x0 + q % TX;
+        if (y >= a.h || x >= a.wd) continue;
+        float* o = static_cast<float*>(a.y) +
+                   ((long long)(img * a.h + y) * a.wd + x) * a.ldy + co0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int co = 32 * (NC * wc + b) + 8 * v + 4 * g;
+          f32x4 val;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            val[i] = acc[b][s][4 * v + i] + (a.bias ? a.bias[co0 + co + i] : 0.f);
+            if (a.relu) val[i] = fmaxf(val[i], 0.f);
+          }
+          *reinterpret_cast<f32x4*>(o + co) = val;
+        }
+      }
+    return;
+  }
+  // bf16: through LDS (the staging areas are free after the last barrier)
+#pragma unroll
+  for (int b = 0; b < NC; ++b)
+#pragma unroll
+    for (int s = 0; s < MP; ++s) {
+      const int q = 32 * (wp * MP + s) + r;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int co = 32 * (NC * wc + b) + 8 * v + 4 * g;
+        bf16x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float val = acc[b][s][4 * v + i] + (a.bias ? a.bias[co0 + co + i] : 0.f);
+          if (a.relu) val = fmaxf(val, 0.f);
+          o[i] = (bf16)val;
+        }
+        *reinterpret_cast<bf16x4*>(smem + q * L::OS + 2 * co) = o;
       }
     }
+  __syncthreads();
+  constexpr int kOVec = L::CB / 8;
+#pragma unroll
+  for (int i = 0; i < L::P * kOVec / 256; ++i) {
+    const int v = tid + 256 * i, q = v / kOVec, c = v % kOVec;
+    const int y = y0 + q / TX, x = x0 + q % TX;
+    if (y < a.h && x < a.wd)
+      *reinterpret_cast<bf16x8*>(static_cast<bf16*>(a.y) +
+                                 ((long long)(img * a.h + y) * a.wd + x) * a.ldy + co0 + 8 * c) =
+          *reinterpret_cast<const bf16x8*>(smem + q * L::OS + 16 * c);
+  }
+}
+
+template <int MP, int NC, int WP, int WC, int TX, int KS>
+int launch_conv_tile(const ConvArgs& a, hipStream_t st) {
+  using L = ConvTile<MP, NC, WP, WC, TX, KS>;
+  const int tx = (a.wd + TX - 1) / TX, ty = (a.h + L::TY - 1) / L::TY;
+  const size_t lds = L::lds(a.cin);
+  auto* fn = conv_tile_kernel<MP, NC, WP, WC, TX, KS>;
+  if (lds > 64 * 1024)
+    UCHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  dim3 grid(tx * ty * (a.npix / (a.h * a.wd)), a.cout / L::CB);
+  hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, a, tx, ty);
+  UCHECK(hipGetLastError());
+  return UNET_OK;
+}
+
+// Runs the tiling if its LDS fits and its grid is in range.
+template <int MP, int NC, int WP, int WC, int KS>
+bool conv_tile_fits(const ConvArgs& a, bool narrow) {
+  const size_t b = narrow ? ConvTile<MP, NC, WP, WC, 16, KS>::lds(a.cin)
+                          : ConvTile<MP, NC, WP, WC, 32, KS>::lds(a.cin);
+  return b <= (size_t)kLdsBytes;
+}
+template <int MP, int NC, int WP, int WC, int KS>
+int conv_tile_go(const ConvArgs& a, bool narrow, hipStream_t st) {
+  return narrow ? launch_conv_tile<MP, NC, WP, WC, 16, KS>(a, st)
+                : launch_conv_tile<MP, NC, WP, WC, 32, KS>(a, st);
 }
 
 int launch_conv(const ConvArgs& a, hipStream_t st) {
@@ -235,16 +390,22 @@ int launch_conv(const ConvArgs& a, hipStream_t st) {
   if (a.npix <= 0 || a.h <= 0 || a.wd <= 0 || a.npix % (a.h * a.wd))
     return fail(UNET_EINVAL, "conv: bad image size");
   if (!a.x || !a.w || !a.y) return fail(UNET_EINVAL, "conv: null pointer");
-  if (a.npix >= kConv32MinPix) {
-    // large layers: 64-pixel wave tiles on the 32x32x16 MFMA
-    if (a.cout % 64 == 0) {
-      dim3 grid((a.npix + 255) / 256, a.cout / 64);
-      hipLaunchKernelGGL(conv_fwd32_kernel<2>, grid, dim3(256), 0, st, a);
-    } else {
-      dim3 grid((a.npix + 255) / 256, a.cout / 32);
-      hipLaunchKernelGGL(conv_fwd32_kernel<1>, grid, dim3(256), 0, st, a);
-    }
-  } else if (a.cout % 64 == 0) {
+  // 16-pixel-wide tiles where 32 would pad the rows more
+  const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32;
+  // the largest wave tile that still gives about one wave per SIMD (1024)
+  const long long px32 = (a.npix + 31) / 32;
+  if (a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048 && conv_tile_fits<2, 2, 4, 1, 96>(a, narrow))
+    return conv_tile_go<2, 2, 4, 1, 96>(a, narrow, st);
+  if (a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024 &&
+      conv_tile_fits<1, 2, 2, 2, 96>(a, narrow))
+    return conv_tile_go<1, 2, 2, 2, 96>(a, narrow, st);
+  if (a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 288>(a, narrow))
+    return conv_tile_go<1, 1, 2, 2, 288>(a, narrow, st);
+  if (px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 288>(a, narrow))
+    return conv_tile_go<2, 1, 4, 1, 288>(a, narrow, st);
+  if (conv_tile_fits<1, 1, 4, 1, 288>(a, narrow)) return conv_tile_go<1, 1, 4, 1, 288>(a, narrow, st);
+  // more input channels than LDS holds: operands straight from memory
+  if (a.cout % 64 == 0) {
     dim3 grid((a.npix + 63) / 64, a.cout / 64);
     hipLaunchKernelGGL(conv_fwd_kernel<2>, grid, dim3(256), 0, st, a);
   } else {

@@ -1,0 +1,56 @@
+"""Tile variants of the convolution kernels, at the sizes where each takes
+over and where tiles are ragged.  Bounds as in test_gpu_unet: FP32
+accumulation within 1e-5 of the sum of absolute products, bf16 outputs within
+one bf16 ulp (2^-8 relative) on top."""
+import numpy as np
+import pytest
+
+from oracle import unet_ref as R
+from test_gpu_unet import U, bf, dev, host  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (16, 261, 16, 32, 64),    # 64 x 64 wave tiles, 16 columns, last tile row partial
+    (1, 130, 129, 64, 128),   # 32 x 64 wave tiles, last tile row and column partial
+    (3, 37, 53, 64, 192),     # 32 x 32 wave tiles, all weights of a tap row per stage
+    (1, 5, 33, 384, 64),      # the same with the shorter weight stages (LDS)
+    (2, 9, 7, 96, 32),        # 32 output channels, image smaller than a tile
+    (1, 259, 257, 96, 32),    # 32 output channels, 64-pixel wave tiles
+    (1, 3, 5, 1216, 64),      # more input channels than LDS holds
+    (1, 1, 1, 1216, 32),      # one pixel
+])
+def test_conv_tiles(U, n, h, w, cin, cout):
+    import torch
+    print("[gpu-case] conv tiles", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(20)
+    x, wt = bf(rng, n, h, w, cin), bf(rng, cout, 9, cin, scale=0.1)
+    b = rng.standard_normal(cout).astype(np.float32).astype(np.float64)
+    ref, bound = R.conv3x3(x, wt, b), R.conv3x3(np.abs(x), np.abs(wt)) + np.abs(b)
+    xd, wd, bd = dev(x, torch.bfloat16), dev(wt, torch.bfloat16), dev(b, torch.float32)
+    # output rows wider than the layer: the neighbours' channels stay as they are
+    y = torch.full((n, h, w, cout + 8), 7.0, device="cuda", dtype=torch.float32)
+    U.conv3x3_fwd(xd, wd, bd, cout, out_f32=True, y=y)
+    assert (np.abs(host(y)[..., :cout] - ref) <= 1e-5 * bound + 1e-6).all()
+    assert (host(y)[..., cout:] == 7.0).all()
+    yr = torch.full((n, h, w, cout + 8), 7.0, device="cuda", dtype=torch.bfloat16)
+    U.conv3x3_fwd(xd, wd, bd, cout, relu=True, y=yr)
+    refr = np.maximum(ref, 0)
+    assert (np.abs(host(yr)[..., :cout] - refr) <= 2 ** -8 * refr + 1e-5 * bound + 1e-6).all()
+    assert (host(yr)[..., cout:] == 7.0).all()
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [(33, 64, 64, 64, 64), (9, 64, 128, 96, 32),
+                                            (40, 16, 16, 128, 128)])
+def test_conv_variants_agree_bit_for_bit(U, n, h, w, cin, cout):
+    """One image alone takes another wave tile than the batch it is part of;
+    the sums run in the same order."""
+    import torch
+    print("[gpu-case] conv variants", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(21)
+    x, wt = dev(bf(rng, n, h, w, cin), torch.bfloat16), dev(bf(rng, cout, 9, cin), torch.bfloat16)
+    y = U.conv3x3_fwd(x, wt, None, cout, out_f32=True)
+    for k in (0, n - 1):
+        one = U.conv3x3_fwd(x[k:k + 1].contiguous(), wt, None, cout, out_f32=True)
+        assert torch.equal(one[0], y[k])
