@@ -172,7 +172,8 @@ struct ConvTile {
   static constexpr int OS = 2 * CB + 16;   // LDS bytes per output pixel
   static_assert(WP * WC == 4 && TY * TX == P && KS % 32 == 0 && 288 % KS == 0, "tile");
   static size_t lds(int cin) {
-    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + 2 * (size_t)CB * WS;
+    const size_t bufs = 9 * cin > KS ? 2 : 1;
+    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + bufs * CB * WS;
     return in > (size_t)P * OS ? in : (size_t)P * OS;
   }
 };
@@ -401,6 +402,8 @@ int launch_conv(const ConvArgs& a, hipStream_t st) {
     return conv_tile_go<1, 2, 2, 2, 96>(a, narrow, st);
   if (a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 288>(a, narrow))
     return conv_tile_go<1, 1, 2, 2, 288>(a, narrow, st);
+  if (a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 96>(a, narrow))
+    return conv_tile_go<1, 1, 2, 2, 96>(a, narrow, st);
   if (px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 288>(a, narrow))
     return conv_tile_go<2, 1, 4, 1, 288>(a, narrow, st);
   if (conv_tile_fits<1, 1, 4, 1, 288>(a, narrow)) return conv_tile_go<1, 1, 4, 1, 288>(a, narrow, st);
@@ -416,21 +419,71 @@ int launch_conv(const ConvArgs& a, hipStream_t st) {
   return UNET_OK;
 }
 
-// wt[ci][t][co] = w[co][8 - t][ci]
-__global__ void flip_transpose_kernel(const bf16* w, bf16* wt, int cin, int cout) {
-  const long long total = 9LL * cin * cout;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int co = int(e % cout);
-    const long long rest = e / cout;
-    const int t = int(rest % 9), ci = int(rest / 9);
-    wt[e] = w[((long long)co * 9 + (8 - t)) * cin + ci];
-  }
+// Flipped, transposed weights of one or more layers: wt[ci][t][co] =
+// w[co][8 - t][ci], both at offset `off` of their arrays.  A block moves one
+// 32 x 32 channel tile of one tap through LDS, so reads and writes are rows
+// of 64 bytes (element by element, one thread per output, the strided reads
+// took 4.8 us per layer).
+constexpr int kMaxFlip = 16;
+struct FlipArgs {
+  const bf16* w;
+  bf16* wt;
+  int layers;
+  struct {
+    long long off;
+    int cin, cout, first;   // first: index of the layer's first tile
+  } l[kMaxFlip];
+};
+
+__global__ __launch_bounds__(256) void flip_tiles_kernel(FlipArgs a) {
+  __shared__ bf16 s[32][34];
+  int k = 0;
+  while (k + 1 < a.layers && int(blockIdx.x) >= a.l[k + 1].first) ++k;
+  const int cin = a.l[k].cin, cout = a.l[k].cout;
+  int tile = blockIdx.x - a.l[k].first;
+  const int t = tile % 9;
+  tile /= 9;
+  const int ci0 = (tile % (cin / 32)) * 32, co0 = (tile / (cin / 32)) * 32;
+  const bf16* w = a.w + a.l[k].off;
+  bf16* wt = a.wt + a.l[k].off;
+  const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    s[q + 8 * i][c] = w[((long long)(co0 + q + 8 * i) * 9 + (8 - t)) * cin + ci0 + c];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    wt[((long long)(ci0 + q + 8 * i) * 9 + t) * cout + co0 + c] = s[c][q + 8 * i];
 }
+
+int flip_tiles(int cin, int cout) { return 9 * (cin / 32) * (cout / 32); }
 
 // ---------------------------------------------------------------------------
 // Convolution, weight and bias gradients
 // ---------------------------------------------------------------------------
+// Tiled weight gradient: a block owns 32 WCO output x 32 WCI input channels
+// of all nine taps and runs over pixel tiles of TX x TY (one share of them,
+// `split`).  dy and x (with its one-pixel ring, zeros outside the image) are
+// staged in LDS as they lie in memory, [pixel][channel]; the MFMA reduces
+// over pixels, so both operands are read with the transposing LDS load
+// (ds_read_b64_tr_b16: of 16 lanes, lane i receives element i of four rows
+// of 16), two loads per operand of 16 pixels x 32 channels.  One dy operand
+// serves the nine taps, whose x operands are the same rows shifted by the
+// tap.  LDS rows are an odd multiple of 32 bytes, so that the 32-byte pieces
+// of eight rows fall on different banks.  The next tile's global loads are
+// in flight while the current one is multiplied.  The 4 / (WCO WCI) waves of
+// one channel tile split the pixels and add their sums in LDS at the end.
+// The bias partial sums are one more MFMA against a matrix of ones.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ bf16x8 lds_tr8(const char* p0, const char* p1) {
+  using P = __attribute__((address_space(3))) s16x4*;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)p0);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((P)p1);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 struct WgradArgs {
   const bf16* dy;
   int lddy;
@@ -438,281 +491,208 @@ struct WgradArgs {
   int ldx;
   float* part;        // [splits][cout][9][cin]
   float* bpart;       // [splits][cout] or null
-  int npix, h, wd, cin, cout, chunk;
+  int n, h, wd, cin, cout;
+  int tiles_x, tiles_y, units, splits;
 };
 
-constexpr int kPadPx = 40;   // LDS row length (32 pixels + 8) in bf16
-constexpr int kWgrad2Blocks = 1024;   // blocks the channel-major path aims for
+template <int WCO, int WCI, int TX, int TY>
+__global__ __launch_bounds__(256, 2) void wgrad_tile_kernel(WgradArgs a) {
+  constexpr int CO = 32 * WCO, CI = 32 * WCI, WK = 4 / (WCO * WCI);
+  constexpr int SD = 2 * CO + 32, SX = 2 * CI + 32, HX = TX + 2, HP = HX * (TY + 2), P = TX * TY;
+  constexpr int kDyVec = P * CO / 8, kXVec = HP * CI / 8;
+  constexpr int kDyPer = (kDyVec + 255) / 256, kXPer = (kXVec + 255) / 256;
+  constexpr int kSum = 4 * 32 * 33 * 4;   // bytes of the final sums over waves
+  constexpr int kStage = P * SD + HP * SX;
+  __shared__ __align__(16) char smem[kStage > kSum ? kStage : kSum];
+  char* sd = smem;
+  char* sx = smem + P * SD;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wv % WK, wci = (wv / WK) % WCI, wco = wv / (WK * WCI);
+  const int nci = a.cin / CI;
+  const int ci0 = (blockIdx.x % nci) * CI, co0 = (blockIdx.x / nci) * CO;
+  const int u0 = int((long long)blockIdx.y * a.units / a.splits);
+  const int u1 = int((long long)(blockIdx.y + 1) * a.units / a.splits);
+  const bool bias = a.bpart != nullptr && ci0 == 0 && wci == 0;
 
-__global__ __launch_bounds__(256) void wgrad_kernel(WgradArgs a) {
-  __shared__ bf16 sA[4][32][kPadPx];   // per wave: dy tile [co][pixel]
-  __shared__ bf16 sB[4][32][kPadPx];   // per wave: x tile [ci][pixel]
-  __shared__ float sR[4][32][33];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int bid = blockIdx.x;
-  const int t = bid % 9;
-  bid /= 9;
-  const int nci = a.cin / 32;
-  const int ci0 = (bid % nci) * 32, co0 = (bid / nci) * 32;
-  const int dy = t / 3 - 1, dx = t % 3 - 1;
-  const int pbeg = blockIdx.y * a.chunk;
-  const int pend = min(a.npix, pbeg + a.chunk);
-  const int r = lane & 15, g = lane >> 4;
-  f32x4 acc[2][2];
+  bf16x8 rd[kDyPer], rx[kXPer];
+  auto load = [&](int u) {
+    const int tx = u % a.tiles_x;
+    const int rest = u / a.tiles_x;
+    const int ty = rest % a.tiles_y, img = rest / a.tiles_y;
+    const int x0 = tx * TX, y0 = ty * TY;
+    const long long base = (long long)img * a.h * a.wd;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // chunk is a multiple of 128: every wave runs the same number of steps
-  for (int k0 = pbeg + 32 * wv; k0 < pbeg + a.chunk; k0 += 128) {
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int q = lane + 64 * e;
-      const int pl = q >> 2, cv = q & 3;
-      const int p = k0 + pl;
-      bf16x8 vd = bf16x8{}, vx = bf16x8{};
-      if (p < pend) {
-        vd = *reinterpret_cast<const bf16x8*>(a.dy + (long long)p * a.lddy + co0 + 8 * cv);
-        const int xx = p % a.wd, yy = (p / a.wd) % a.h;
-        const int sy = yy + dy, sx = xx + dx;
-        if (sy >= 0 && sy < a.h && sx >= 0 && sx < a.wd)
-          vx = *reinterpret_cast<const bf16x8*>(a.x + (long long)(p + dy * a.wd + dx) * a.ldx +
-                                                ci0 + 8 * cv);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        sA[wv][8 * cv + u][pl] = vd[u];
-        sB[wv][8 * cv + u][pl] = vx[u];
-      }
+    for (int i = 0; i < kDyPer; ++i) {
+      const int v = tid + 256 * i, px = v / (CO / 8), c = v % (CO / 8);
+      const int y = y0 + px / TX, x = x0 + px % TX;
+      rd[i] = bf16x8{};
+      if ((kDyVec % 256 == 0 || v < kDyVec) && y < a.h && x < a.wd)
+        rd[i] = *reinterpret_cast<const bf16x8*>(a.dy + (base + (long long)y * a.wd + x) * a.lddy +
+                                                 co0 + 8 * c);
     }
+#pragma unroll
+    for (int i = 0; i < kXPer; ++i) {
+      const int v = tid + 256 * i, px = v / (CI / 8), c = v % (CI / 8);
+      const int yy = px / HX, y = y0 + yy - 1, x = x0 + px - yy * HX - 1;
+      rx[i] = bf16x8{};
+      if ((kXVec % 256 == 0 || v < kXVec) && y >= 0 && y < a.h && x >= 0 && x < a.wd)
+        rx[i] = *reinterpret_cast<const bf16x8*>(a.x + (base + (long long)y * a.wd + x) * a.ldx +
+                                                 ci0 + 8 * c);
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < kDyPer; ++i) {
+      const int v = tid + 256 * i;
+      if (kDyVec % 256 == 0 || v < kDyVec)
+        *reinterpret_cast<bf16x8*>(sd + (v / (CO / 8)) * SD + 16 * (v % (CO / 8))) = rd[i];
+    }
+#pragma unroll
+    for (int i = 0; i < kXPer; ++i) {
+      const int v = tid + 256 * i;
+      if (kXVec % 256 == 0 || v < kXVec)
+        *reinterpret_cast<bf16x8*>(sx + (v / (CI / 8)) * SX + 16 * (v % (CI / 8))) = rx[i];
+    }
+  };
+
+  f32x16 acc[9], accb;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    accb[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t][v] = 0.f;
+  }
+  bf16x8 ones;
+#pragma unroll
+  for (int v = 0; v < 8; ++v) ones[v] = (bf16)1.f;
+  // this lane's pixel row and channel within an operand (first of two loads)
+  const int lrow = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  const int lch = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const char* pd = sd + lrow * SD + 2 * (32 * wco + lch);
+  const char* px = sx + lrow * SX + 2 * (32 * wci + lch);
+  if (u0 < u1) load(u0);
+  for (int u = u0; u < u1; ++u) {
     __syncthreads();
-    bf16x8 A[2], B[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      A[b] = *reinterpret_cast<const bf16x8*>(&sA[wv][16 * b + r][8 * g]);
-      B[b] = *reinterpret_cast<const bf16x8*>(&sB[wv][16 * b + r][8 * g]);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(A[i], B[j], acc[i][j]);
+    store();
     __syncthreads();
-  }
+    if (u + 1 < u1) load(u + 1);
+    for (int k = wk; k < P / 16; k += WK) {
+      const int q = 16 * k;
+      const char* d = pd + q * SD;
+      const char* b = px + ((q / TX) * HX + q % TX) * SX;
+      const bf16x8 A = lds_tr8(d, d + 4 * SD);
+      bf16x8 B[9];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sR[wv][16 * i + 4 * g + v][16 * j + r] = acc[i][j][v];
-  __syncthreads();
-  for (int e = threadIdx.x; e < 1024; e += 256) {
-    const int co = e >> 5, ci = e & 31;
-    const float s = sR[0][co][ci] + sR[1][co][ci] + sR[2][co][ci] + sR[3][co][ci];
-    a.part[(((long long)blockIdx.y * a.cout + co0 + co) * 9 + t) * a.cin + ci0 + ci] = s;
-  }
-  // bias partials: the blocks of tap 0 and the first input-channel tile
-  if (a.bpart && t == 0 && ci0 == 0 && threadIdx.x < 32) {
-    const int co = co0 + threadIdx.x;
-    float s = 0.f;
-    for (int p = pbeg; p < pend; ++p) s += (float)a.dy[(long long)p * a.lddy + co];
-    a.bpart[(long long)blockIdx.y * a.cout + co] = s;
-  }
-}
-
-// ---- weight gradient on channel-major copies (width a multiple of 8) ------
-// The pixel sum is the MFMA reduction dimension, so both operands are first
-// copied channel-major ([c][p], pixels contiguous): then every A and B
-// operand is 8 consecutive pixels of one channel, one 16-byte load (two and
-// a lane-local shift for the taps with dx = +-1), with no LDS transposes.
-
-// dst[c * rowlen + p] = src[p][c] for c < ch, p < npix (bf16; rowlen a
-// multiple of 8); 64 pixels x 32 channels per block through LDS.
-__global__ __launch_bounds__(256) void to_channel_major_kernel(const bf16* __restrict__ src,
-                                                                int lds, bf16* __restrict__ dst,
-                                                                int npix, int rowlen) {
-  __shared__ bf16 t[64][32 + 2];
-  const int p0 = blockIdx.x * 64, c0 = blockIdx.y * 32;
-  // load: 64 pixels x 4 vectors of 8 channels = 256 vectors, one per thread
-  {
-    const int pl = threadIdx.x >> 2, cv = threadIdx.x & 3;
-    const int p = p0 + pl;
-    bf16x8 v = bf16x8{};
-    if (p < npix) v = *reinterpret_cast<const bf16x8*>(src + (long long)p * lds + c0 + 8 * cv);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[pl][8 * cv + u] = v[u];
-  }
-  __syncthreads();
-  // store: 32 channels x 8 vectors of 8 pixels = 256 vectors
-  {
-    const int c = threadIdx.x >> 3, pv = threadIdx.x & 7;
-    const int p = p0 + 8 * pv;
-    if (p < npix) {
-      bf16x8 o;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) o[u] = t[8 * pv + u][c];
-      if (p + 8 <= npix) {
-        *reinterpret_cast<bf16x8*>(dst + (long long)(c0 + c) * rowlen + p) = o;
-      } else {
-        for (int u = 0; u < 8 && p + u < npix; ++u) dst[(long long)(c0 + c) * rowlen + p + u] = o[u];
+      for (int t = 0; t < 9; ++t) {
+        const char* bt = b + ((t / 3) * HX + t % 3) * SX;
+        B[t] = lds_tr8(bt, bt + 4 * SX);
       }
+#pragma unroll
+      for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[t], acc[t]);
+      if (bias) accb = mfma32(A, ones, accb);
     }
   }
-}
-
-struct Wgrad2Args {
-  const bf16* dyT;    // [cout][npix]
-  const bf16* xT;     // [cin][npix]
-  float* part;        // [splits][cout][9][cin]
-  float* bpart;       // [splits][cout] (bias partial sums) or null
-  int npix, npad, h, wd, cin, cout, chunk;
-};
-
-// 8 consecutive pixels p .. p + 7 (one row: p % 8 == 0, width % 8 == 0) of
-// channel row `row` (npad elements, a multiple of 8), shifted by the tap
-// (dy, dx) with zero padding.
-__device__ __forceinline__ bf16x8 tap_row8(const bf16* __restrict__ row, int p, int npix,
-                                           int npad, int h, int wd, int dy, int dx) {
-  bf16x8 z = bf16x8{};
-  if (p >= npix) return z;
-  const int y = (p / wd) % h;
-  if (y + dy < 0 || y + dy >= h) return z;
-  const int q = p + dy * wd;   // aligned source of the unshifted columns
-  const bf16x8 v0 = *reinterpret_cast<const bf16x8*>(row + q);
-  if (dx == 0) return v0;
-  bf16x8 o;
-  if (dx < 0) {
-    // pixel p + u takes column u - 1: the element before the vector, zero
-    // at the start of a row
-    const bool first = p % wd == 0;
-    const bf16x8 vp = *reinterpret_cast<const bf16x8*>(row + (q >= 8 ? q - 8 : 0));
-    o[0] = first ? bf16(0.f) : vp[7];
+  const int r = lane & 31, g = lane >> 5;
+  float* part = a.part + (long long)blockIdx.y * 9 * a.cin * a.cout;
+  if constexpr (WK == 1) {
 #pragma unroll
-    for (int u = 1; u < 8; ++u) o[u] = v0[u - 1];
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int co = co0 + 32 * wco + 8 * (v / 4) + 4 * g + v % 4;
+        part[((long long)co * 9 + t) * a.cin + ci0 + 32 * wci + r] = acc[t][v];
+      }
+    if (bias && r == 0)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        a.bpart[(long long)blockIdx.y * a.cout + co0 + 32 * wco + 8 * (v / 4) + 4 * g + v % 4] =
+            accb[v];
   } else {
-    const bool last = (p + 8) % wd == 0;
-    const bf16x8 vn = *reinterpret_cast<const bf16x8*>(row + (q + 8 < npad ? q + 8 : q));
+    // sum over the WK waves of a channel tile, tap by tap
+    float (*s)[32][33] = reinterpret_cast<float (*)[32][33]>(smem);
+    const int grp = wv / WK, lt = tid % (64 * WK);   // channel tile, thread within it
 #pragma unroll
-    for (int u = 0; u < 7; ++u) o[u] = v0[u + 1];
-    o[7] = last ? bf16(0.f) : vn[0];
+    for (int t = 0; t < 10; ++t) {
+      if (t == 9 && a.bpart == nullptr) break;
+      __syncthreads();
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        s[wv][8 * (v / 4) + 4 * g + v % 4][r] = t < 9 ? acc[t < 9 ? t : 0][v] : accb[v];
+      __syncthreads();
+      for (int e = lt; e < 1024; e += 64 * WK) {
+        const int co = e >> 5, ci = e & 31;
+        float v = s[grp * WK][co][ci];
+#pragma unroll
+        for (int k = 1; k < WK; ++k) v += s[grp * WK + k][co][ci];
+        if (t < 9)
+          part[((long long)(co0 + 32 * wco + co) * 9 + t) * a.cin + ci0 + 32 * wci + ci] = v;
+        else if (bias && ci == 0)
+          a.bpart[(long long)blockIdx.y * a.cout + co0 + 32 * wco + co] = v;
+      }
+    }
   }
-  return o;
 }
 
-// One block: a 32 x 32 tile of one tap over one pixel chunk (split); its
-// partial sum goes to `part`.  The blocks of the centre tap and the first
-// input-channel tile also sum dy over their chunk for the bias gradient
-// (`bpart`), so the bias needs no launch of its own.
-__global__ __launch_bounds__(256) void wgrad2_kernel(Wgrad2Args a) {
-  __shared__ float sR[4][32][33];
-  __shared__ float sB[256];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int bid = blockIdx.x;
-  const int t = bid % 9;
-  bid /= 9;
-  const int nci = a.cin / 32;
-  const int ci0 = (bid % nci) * 32, co0 = (bid / nci) * 32;
-  const int dy = t / 3 - 1, dx = t % 3 - 1;
-  const int pbeg = blockIdx.y * a.chunk;
-  const int r = lane & 15, g = lane >> 4;
-  const bf16* arow[2];
-  const bf16* brow[2];
-#pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    arow[b] = a.dyT + (long long)(co0 + 16 * b + r) * a.npad;
-    brow[b] = a.xT + (long long)(ci0 + 16 * b + r) * a.npad;
-  }
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = pbeg + 32 * wv; k0 < pbeg + a.chunk; k0 += 128) {
-    const int p = k0 + 8 * g;
-    bf16x8 A[2], B[2];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      A[b] = p < a.npix ? *reinterpret_cast<const bf16x8*>(arow[b] + p) : bf16x8{};
-      B[b] = tap_row8(brow[b], p, a.npix, a.npad, a.h, a.wd, dy, dx);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(A[i], B[j], acc[i][j]);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sR[wv][16 * i + 4 * g + v][16 * j + r] = acc[i][j][v];
+// Both sums of the weight gradient: out[i] = sum_s part[s][i] for i < count
+// and bout[j] = sum_s bpart[s][j] for j < bcount (bpart may be null).  A block
+// owns 64 consecutive entries; its 16 groups of 16 threads each add every
+// 16th split (four entries per thread), then one group adds the 16 sums, all
+// in a fixed order.  count and bcount are multiples of 4.
+__global__ __launch_bounds__(256) void sum_splits_kernel(const float* part, long long count,
+                                                         const float* bpart, int bcount,
+                                                         int splits, float* out, float* bout) {
+  __shared__ f32x4 s[16][16];
+  const int e = threadIdx.x & 15, k0 = threadIdx.x >> 4;
+  const long long wblocks = (count + 63) / 64;
+  const bool bias = blockIdx.x >= wblocks;
+  const float* src = bias ? bpart : part;
+  float* dst = bias ? bout : out;
+  const long long n = bias ? bcount : count;
+  const long long i = ((long long)blockIdx.x - (bias ? wblocks : 0)) * 64 + 4 * e;
+  f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (i < n)
+    for (int k = k0; k < splits; k += 16)
+      v += *reinterpret_cast<const f32x4*>(src + (long long)k * n + i);
+  s[k0][e] = v;
   __syncthreads();
-  const long long wcount = 9LL * a.cin * a.cout;
-  for (int e = threadIdx.x; e < 1024; e += 256) {
-    const int co = e >> 5, ci = e & 31;
-    const float s = sR[0][co][ci] + sR[1][co][ci] + sR[2][co][ci] + sR[3][co][ci];
-    a.part[blockIdx.y * wcount + ((long long)(co0 + co) * 9 + t) * a.cin + ci0 + ci] = s;
-  }
-  const bool bias_tile = a.bpart != nullptr && t == 4 && ci0 == 0;
-  if (bias_tile) {
-    // eight threads per output channel, 8 pixels per load, fixed order
-    const int co = threadIdx.x >> 3, l8 = threadIdx.x & 7;
-    const bf16* row = a.dyT + (long long)(co0 + co) * a.npad;
-    const int pend = min(a.npix, pbeg + a.chunk);
-    float s = 0.f;
-    for (int p = pbeg + 8 * l8; p < pend; p += 64) {
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(row + p);
+  if (k0 == 0 && i < n) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (p + u < pend) s += (float)v[u];
-    }
-    sB[threadIdx.x] = s;
-    __syncthreads();
-    if (l8 == 0) {
-      float b = 0.f;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) b += sB[threadIdx.x + u];
-      a.bpart[(long long)blockIdx.y * a.cout + co0 + co] = b;
-    }
+    for (int k = 1; k < 16; ++k) v += s[k][e];
+    *reinterpret_cast<f32x4*>(dst + i) = v;
   }
 }
 
-// out[i] = sum_s part[s][i] (fixed order)
-__global__ void sum_splits_kernel(const float* part, long long count, int splits, float* out) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < count;
-       i += (long long)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += part[(long long)k * count + i];
-    out[i] = s;
-  }
-}
+// Split of the weight gradient: which channel tile a block owns and into how
+// many shares the pixel tiles go.  A share costs its tiles (clocks per tile
+// of one block, measured; more blocks than compute units share them) and its
+// partial sums are written and read once more (about 1.7 kB per clock).
+struct WgradPlan {
+  int wide, narrow, tiles_x, tiles_y, units, splits;
+};
 
-// Both sums of the weight gradient in one launch: out[i] = sum_s part[s][i]
-// for i < count and bout[j] = sum_s bpart[s][j] for j < bcount (bpart may be
-// null), each in split order.
-__global__ void sum_splits2_kernel(const float* part, long long count, const float* bpart,
-                                   int bcount, int splits, float* out, float* bout) {
-  const long long total = count + (bpart ? bcount : 0);
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    float s = 0.f;
-    if (i < count) {
-      for (int k = 0; k < splits; ++k) s += part[(long long)k * count + i];
-      out[i] = s;
-    } else {
-      const long long j = i - count;
-      for (int k = 0; k < splits; ++k) s += bpart[(long long)k * bcount + j];
-      bout[j] = s;
+WgradPlan wgrad_plan(int n, int h, int wd, int cin, int cout) {
+  WgradPlan best{};
+  double best_cost = 0.0;
+  const int narrow = wd <= 16;
+  const int tx = narrow ? 16 : 32, ty = narrow ? 8 : 4;
+  const int tiles_x = (wd + tx - 1) / tx, tiles_y = (h + ty - 1) / ty;
+  const int units = n * tiles_x * tiles_y;
+  for (int wide = 0; wide < 2; ++wide) {
+    if (wide && (cin % 64 || cout % 64)) continue;
+    const int base = (cin / (wide ? 64 : 32)) * (cout / (wide ? 64 : 32));
+    const double clk = wide ? 2800.0 : 1100.0;
+    for (int s = 1; s <= units && s <= 1024; s *= 2) {
+      const double share = std::max(1.0, (double)base * s / 256.0);
+      const double cost = share * ((units + s - 1) / s) * clk +
+                          (double)s * (9.0 * cin * cout + cout) * 8.0 / 1700.0;
+      if (best.splits == 0 || cost < best_cost) {
+        best = WgradPlan{wide, narrow, tiles_x, tiles_y, units, s};
+        best_cost = cost;
+      }
     }
   }
-}
-
-void wgrad_plan(int npix, int cin, int cout, int* splits, int* chunk, int target = 2048) {
-  const int base = (cout / 32) * (cin / 32) * 9;
-  const int want = std::max(1, (target + base - 1) / base);
-  int c = (npix + want - 1) / want;
-  c = std::max(128, (c + 127) / 128 * 128);
-  *chunk = c;
-  *splits = (npix + c - 1) / c;
+  return best;
 }
 
 // ---------------------------------------------------------------------------
@@ -1131,9 +1111,15 @@ int unet_conv3x3_bwd_data(const void* dy, int32_t lddy, const void* w, void* dx,
   if (!work || !w) return fail(UNET_EINVAL, "bwd_data: null pointer");
   if (n <= 0 || h <= 0 || wd <= 0) return fail(UNET_EINVAL, "bwd_data: bad size");
   hipStream_t st = as_stream(stream);
-  const long long cnt = 9LL * cin * cout;
-  hipLaunchKernelGGL(flip_transpose_kernel, dim3(grid_for(cnt)), dim3(256), 0, st,
-                     static_cast<const bf16*>(w), static_cast<bf16*>(work), cin, cout);
+  if (cin <= 0 || cout <= 0 || cin % 32 || cout % 32)
+    return fail(UNET_EINVAL, "bwd_data: cin and cout must be positive multiples of 32");
+  FlipArgs f{};
+  f.w = static_cast<const bf16*>(w);
+  f.wt = static_cast<bf16*>(work);
+  f.layers = 1;
+  f.l[0].cin = cin;
+  f.l[0].cout = cout;
+  hipLaunchKernelGGL(flip_tiles_kernel, dim3(flip_tiles(cin, cout)), dim3(256), 0, st, f);
   ConvArgs a{static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(work), nullptr, dx,
              lddx, n * h * wd, h, wd, cout, cin, 0, 0};
   return launch_conv(a, st);
@@ -1141,17 +1127,7 @@ int unet_conv3x3_bwd_data(const void* dy, int32_t lddy, const void* w, void* dx,
 
 int64_t unet_wgrad_work_floats(int32_t n, int32_t h, int32_t wd, int32_t cin, int32_t cout) {
   if (n <= 0 || h <= 0 || wd <= 0 || cin <= 0 || cout <= 0) return 0;
-  int splits, chunk;
-  wgrad_plan(n * h * wd, cin, cout, &splits, &chunk);
-  int64_t words = (int64_t)splits * (9LL * cin * cout + cout);
-  if (wd % 8 == 0) {
-    // channel-major path: fewer splits, plus the two bf16 copies
-    wgrad_plan(n * h * wd, cin, cout, &splits, &chunk, kWgrad2Blocks);
-    const int64_t npad = ((int64_t)n * h * wd + 7) / 8 * 8 + 8;
-    words = std::max<int64_t>(words, (int64_t)splits * (9LL * cin * cout + cout) +
-                                         (npad * (cin + cout) + 1) / 2 + 64);
-  }
-  return words;
+  return (int64_t)wgrad_plan(n, h, wd, cin, cout).splits * (9LL * cin * cout + cout);
 }
 
 int unet_conv3x3_bwd_weight(const void* dy, int32_t lddy, const void* x, int32_t ldx, float* dw,
@@ -1164,43 +1140,25 @@ int unet_conv3x3_bwd_weight(const void* dy, int32_t lddy, const void* x, int32_t
   if (lddy % 8 || ldx % 8 || lddy < cout || ldx < cin)
     return fail(UNET_EINVAL, "bwd_weight: bad ld");
   hipStream_t st = as_stream(stream);
-  const int npix = n * h * wd;
-  int splits, chunk;
+  const WgradPlan p = wgrad_plan(n, h, wd, cin, cout);
   const long long wcount = 9LL * cin * cout;
-  if (wd % 8 == 0) {
-    wgrad_plan(npix, cin, cout, &splits, &chunk, kWgrad2Blocks);
-    const int npad = (npix + 7) / 8 * 8 + 8;
-    float* part = work;
-    float* bpart = work + (long long)splits * wcount;
-    // bf16 copies after the partial sums (256-byte aligned)
-    const long long used = ((long long)splits * (wcount + cout) + 63) / 64 * 64;
-    bf16* dyT = reinterpret_cast<bf16*>(work + used);
-    bf16* xT = dyT + (long long)cout * npad;
-    const int tiles = (cout / 32) * (cin / 32) * 9;
-    hipLaunchKernelGGL(to_channel_major_kernel, dim3((npix + 63) / 64, cout / 32), dim3(256), 0,
-                       st, static_cast<const bf16*>(dy), lddy, dyT, npix, npad);
-    hipLaunchKernelGGL(to_channel_major_kernel, dim3((npix + 63) / 64, cin / 32), dim3(256), 0,
-                       st, static_cast<const bf16*>(x), ldx, xT, npix, npad);
-    UCHECK(hipGetLastError());
-    Wgrad2Args a2{dyT, xT, part, dbias ? bpart : nullptr, npix, npad, h, wd, cin, cout, chunk};
-    hipLaunchKernelGGL(wgrad2_kernel, dim3(tiles, splits), dim3(256), 0, st, a2);
-    UCHECK(hipGetLastError());
-    hipLaunchKernelGGL(sum_splits2_kernel, dim3(grid_for(wcount + cout)), dim3(256), 0, st, part,
-                       wcount, dbias ? bpart : nullptr, cout, splits, dw, dbias);
-    UCHECK(hipGetLastError());
-    return UNET_OK;
-  }
-  wgrad_plan(npix, cin, cout, &splits, &chunk);
-  WgradArgs a{static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(x), ldx, work,
-              work + (long long)splits * wcount, npix, h, wd, cin, cout, chunk};
-  dim3 grid((cout / 32) * (cin / 32) * 9, splits);
-  hipLaunchKernelGGL(wgrad_kernel, grid, dim3(256), 0, st, a);
+  float* bpart = dbias ? work + p.splits * wcount : nullptr;
+  WgradArgs a{static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(x), ldx, work, bpart,
+              n, h, wd, cin, cout, p.tiles_x, p.tiles_y, p.units, p.splits};
+  const int ct = p.wide ? 64 : 32;
+  dim3 grid((cin / ct) * (cout / ct), p.splits);
+  if (p.wide && p.narrow)
+    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 16, 8>), grid, dim3(256), 0, st, a);
+  else if (p.wide)
+    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 32, 4>), grid, dim3(256), 0, st, a);
+  else if (p.narrow)
+    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 16, 8>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 32, 4>), grid, dim3(256), 0, st, a);
   UCHECK(hipGetLastError());
-  hipLaunchKernelGGL(sum_splits_kernel, dim3(grid_for(wcount)), dim3(256), 0, st, work, wcount,
-                     splits, dw);
-  if (dbias)
-    hipLaunchKernelGGL(sum_splits_kernel, dim3(grid_for(cout)), dim3(256), 0, st,
-                       work + (long long)splits * wcount, (long long)cout, splits, dbias);
+  const long long blocks = (wcount + 63) / 64 + (dbias ? (cout + 63) / 64 : 0);
+  hipLaunchKernelGGL(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, st, work, wcount,
+                     bpart, cout, p.splits, dw, dbias);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
@@ -1379,7 +1337,7 @@ struct unet {
   bf16* gact[B_COUNT] = {};
   float* out = nullptr;  // FP32 network output (training)
   bf16* gout = nullptr;  // bf16 gradient of the output
-  void* wt = nullptr;    // flipped weights scratch
+  bf16* wt = nullptr;    // flipped, transposed weights (input gradients), kept with pb
   float* wwork = nullptr;
   double* lwork = nullptr;
 };
@@ -1451,8 +1409,31 @@ int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_d
                                    net->grad + c.w_off, net->grad + c.b_off, n, s, s, c.cin,
                                    c.cout, net->wwork, st);
   if (rc || !need_dx) return rc;
-  return unet_conv3x3_bwd_data(dy, lddy, net->pb + c.w_off, net->gact[c.in] + c.in_off,
-                               kBuf[c.in].ch, n, s, s, c.cin, c.cout, net->wt, st);
+  ConvArgs a{dy, lddy, net->wt + c.w_off, nullptr, net->gact[c.in] + c.in_off, kBuf[c.in].ch,
+             n * s * s, s, s, c.cout, c.cin, 0, 0};
+  return launch_conv(a, st);
+}
+
+// Flipped weights of every layer whose input gradient is needed (all but the
+// first), after each change of pb: one launch.
+int flip_weights(unet* net) {
+  static_assert(kNumConvs <= kMaxFlip, "flip table");
+  FlipArgs f{};
+  f.w = net->pb;
+  f.wt = net->wt;
+  int tiles = 0;
+  for (int k = 1; k < kNumConvs; ++k) {
+    const Conv& c = net->convs[k];
+    auto& l = f.l[f.layers++];
+    l.off = c.w_off;
+    l.cin = c.cin;
+    l.cout = c.cout;
+    l.first = tiles;
+    tiles += flip_tiles(c.cin, c.cout);
+  }
+  hipLaunchKernelGGL(flip_tiles_kernel, dim3(tiles), dim3(256), 0, net->stream, f);
+  UCHECK(hipGetLastError());
+  return UNET_OK;
 }
 
 // In place: gradient of buffer b (channels [off, off + ch)) times relu'.
@@ -1565,7 +1546,6 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
   net->max_batch = max_batch;
   net->res = res;
   long long off = 0;
-  size_t wt_max = 0;
   long long wwork_max = 0;
   for (int k = 0; k < kNumConvs; ++k) {
     Conv c = kConvs[k];
@@ -1574,7 +1554,6 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
     c.b_off = off;
     off += c.cout;
     net->convs.push_back(c);
-    wt_max = std::max(wt_max, (size_t)9 * c.cin * c.cout);
     const int s = res >> c.level;
     for (int nb = 1; nb <= max_batch; ++nb)
       wwork_max = std::max<long long>(wwork_max, unet_wgrad_work_floats(nb, s, s, c.cin, c.cout));
@@ -1589,7 +1568,7 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
             alloc((void**)&net->v, sizeof(float) * off) &&
             alloc((void**)&net->out, sizeof(float) * (size_t)max_batch * res * res * UNET_OUT_CHANNELS) &&
             alloc((void**)&net->gout, 2ULL * max_batch * res * res * UNET_OUT_CHANNELS) &&
-            alloc(&net->wt, 2 * wt_max) && alloc((void**)&net->wwork, sizeof(float) * wwork_max) &&
+            alloc((void**)&net->wt, 2 * off) && alloc((void**)&net->wwork, sizeof(float) * wwork_max) &&
             alloc((void**)&net->lwork, sizeof(double) * unet_loss_work_doubles(0));
   for (int b = 0; ok && b < B_COUNT; ++b) {
     const long long s = res >> kBuf[b].level;
@@ -1656,6 +1635,8 @@ int unet_set_params(unet* net, const float* host) {
   hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(net->nparams)), dim3(256), 0, net->stream,
                      net->p, net->pb, net->nparams);
   UCHECK(hipGetLastError());
+  const int rc = flip_weights(net);
+  if (rc) return rc;
   UCHECK(hipStreamSynchronize(net->stream));
   return UNET_OK;
 }
@@ -1690,8 +1671,9 @@ int unet_train_step(unet* net, const void* x0, const float* target, const uint8_
   int rc = unet_backward(net, x0, target, fluid, n, loss);
   if (rc) return rc;
   net->t += 1;
-  return unet_adam(net->p, net->m, net->v, net->grad, net->pb, net->nparams, lr, 0.9, 0.999, 1e-8,
-                   net->t, net->stream);
+  rc = unet_adam(net->p, net->m, net->v, net->grad, net->pb, net->nparams, lr, 0.9, 0.999, 1e-8,
+                 net->t, net->stream);
+  return rc ? rc : flip_weights(net);
 }
 
 }  // extern "C"

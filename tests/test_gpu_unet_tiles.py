@@ -54,3 +54,24 @@ def test_conv_variants_agree_bit_for_bit(U, n, h, w, cin, cout):
     for k in (0, n - 1):
         one = U.conv3x3_fwd(x[k:k + 1].contiguous(), wt, None, cout, out_f32=True)
         assert torch.equal(one[0], y[k])
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (1, 1, 1, 32, 32),        # one pixel
+    (2, 13, 35, 32, 96),      # 32-column tiles, ragged both ways, one share per tile
+    (3, 21, 11, 64, 64),      # 16-column tiles
+    (24, 64, 64, 64, 64),     # many pixel tiles: 64 x 64 channel tiles or shared partial sums
+    (64, 40, 12, 128, 64),    # the same with 16-column tiles
+    (5, 33, 65, 96, 128),     # 96 input channels
+])
+def test_weight_gradient_tiles(U, n, h, w, cin, cout):
+    import torch
+    print("[gpu-case] weight gradient tiles", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(22)
+    dyf, xf = bf(rng, n, h, w, cout + 8), bf(rng, n, h, w, cin + 32)
+    dy, x = dyf[..., :cout], xf[..., :cin]
+    dw_ref, db_ref = R.conv3x3_bwd_weight(dy, x)
+    bound, _ = R.conv3x3_bwd_weight(np.abs(dy), np.abs(x))
+    dw, db = U.conv3x3_bwd_weight(dev(dyf, torch.bfloat16), dev(xf, torch.bfloat16), cin, cout)
+    assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()
+    assert (np.abs(host(db) - db_ref) <= 1e-5 * np.abs(dy).reshape(-1, cout).sum(0) + 1e-6).all()
