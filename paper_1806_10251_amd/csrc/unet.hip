@@ -65,7 +65,20 @@ struct ConvArgs {
   int ldy;
   int npix, h, wd, cin, cout;
   int relu, out_f32;
+  // fused neighbours of the network's convolutions (bf16 output only):
+  const bf16* mask;    // ReLU backward: zero the output where mask <= 0, or null
+  int ldmask;
+  bf16* pool;          // 2x2 mean of the output (h, wd even), or null
+  int ldpool;
+  int up;              // write each pixel to its four fine pixels (2h x 2wd image)
 };
+
+__device__ __forceinline__ bf16x8 relu_mask(bf16x8 d, const bf16x8& y) {
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (!((float)y[u] > 0.f)) d[u] = (bf16)0.f;
+  return d;
+}
 
 // WC: waves along the output channels (1 or 2); 4 / WC waves along pixels.
 template <int WC>
@@ -174,7 +187,7 @@ struct ConvTile {
   static size_t lds(int cin) {
     const size_t bufs = 9 * cin > KS ? 2 : 1;
     const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + bufs * CB * WS;
-    return in > (size_t)P * OS ? in : (size_t)P * OS;
+    return 4 * CB + (in > (size_t)P * OS ? in : (size_t)P * OS);   // bias, then the tiles
   }
 };
 
@@ -182,7 +195,9 @@ template <int MP, int NC, int WP, int WC, int TX, int KS>
 __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
   using L = ConvTile<MP, NC, WP, WC, TX, KS>;
   constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2);
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(16) char smem_all[];
+  float* sbias = reinterpret_cast<float*>(smem_all);
+  char* smem = smem_all + 4 * L::CB;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wp = wv % WP, wc = wv / WP;
@@ -219,6 +234,7 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
     }
   };
   load_w(0);
+  if (tid < L::CB) sbias[tid] = a.bias ? a.bias[co0 + tid] : 0.f;
   {
     // input tile: HP pixels x cin channels, eight 16-byte loads in flight
     const int cv = a.cin >> 3, nvec = HP * cv;
@@ -315,7 +331,7 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
           f32x4 val;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            val[i] = acc[b][s][4 * v + i] + (a.bias ? a.bias[co0 + co + i] : 0.f);
+            val[i] = acc[b][s][4 * v + i] + sbias[co + i];
             if (a.relu) val[i] = fmaxf(val[i], 0.f);
           }
           *reinterpret_cast<f32x4*>(o + co) = val;
@@ -335,7 +351,7 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
         bf16x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          float val = acc[b][s][4 * v + i] + (a.bias ? a.bias[co0 + co + i] : 0.f);
+          float val = acc[b][s][4 * v + i] + sbias[co + i];
           if (a.relu) val = fmaxf(val, 0.f);
           o[i] = (bf16)val;
         }
@@ -348,10 +364,43 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   for (int i = 0; i < L::P * kOVec / 256; ++i) {
     const int v = tid + 256 * i, q = v / kOVec, c = v % kOVec;
     const int y = y0 + q / TX, x = x0 + q % TX;
-    if (y < a.h && x < a.wd)
-      *reinterpret_cast<bf16x8*>(static_cast<bf16*>(a.y) +
-                                 ((long long)(img * a.h + y) * a.wd + x) * a.ldy + co0 + 8 * c) =
-          *reinterpret_cast<const bf16x8*>(smem + q * L::OS + 16 * c);
+    if (y >= a.h || x >= a.wd) continue;
+    bf16x8 o = *reinterpret_cast<const bf16x8*>(smem + q * L::OS + 16 * c);
+    const long long p = (long long)(img * a.h + y) * a.wd + x;
+    if (a.mask)
+      o = relu_mask(o, *reinterpret_cast<const bf16x8*>(a.mask + p * a.ldmask + co0 + 8 * c));
+    bf16* out = static_cast<bf16*>(a.y) + co0 + 8 * c;
+    if (!a.up) {
+      *reinterpret_cast<bf16x8*>(out + p * a.ldy) = o;
+    } else {
+#pragma unroll
+      for (int f = 0; f < 4; ++f)
+        *reinterpret_cast<bf16x8*>(
+            out + ((long long)(img * 2 * a.h + 2 * y + f / 2) * 2 * a.wd + 2 * x + f % 2) * a.ldy) =
+            o;
+    }
+  }
+  if (a.pool) {
+    // tiles start at even coordinates and h, wd are even: whole 2 x 2 cells
+    for (int v = tid; v < L::P / 4 * kOVec; v += 256) {
+      const int q = v / kOVec, c = v % kOVec;
+      const int yy = 2 * (q / (TX / 2)), xx = 2 * (q % (TX / 2));
+      if (y0 + yy >= a.h || x0 + xx >= a.wd) continue;
+      float m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        const bf16x8 e = *reinterpret_cast<const bf16x8*>(
+            smem + ((yy + f / 2) * TX + xx + f % 2) * L::OS + 16 * c);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m[u] += (float)e[u];
+      }
+      bf16x8 o;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) o[u] = (bf16)(0.25f * m[u]);
+      const long long p =
+          ((long long)img * (a.h / 2) + (y0 + yy) / 2) * (a.wd / 2) + (x0 + xx) / 2;
+      *reinterpret_cast<bf16x8*>(a.pool + p * a.ldpool + co0 + 8 * c) = o;
+    }
   }
 }
 
@@ -407,7 +456,9 @@ int launch_conv(const ConvArgs& a, hipStream_t st) {
   if (px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 288>(a, narrow))
     return conv_tile_go<2, 1, 4, 1, 288>(a, narrow, st);
   if (conv_tile_fits<1, 1, 4, 1, 288>(a, narrow)) return conv_tile_go<1, 1, 4, 1, 288>(a, narrow, st);
-  // more input channels than LDS holds: operands straight from memory
+  // more input channels than LDS holds (none of the network's layers):
+  // operands straight from memory
+  if (a.mask || a.pool || a.up) return fail(UNET_EINVAL, "conv: no fused form of this size");
   if (a.cout % 64 == 0) {
     dim3 grid((a.npix + 63) / 64, a.cout / 64);
     hipLaunchKernelGGL(conv_fwd_kernel<2>, grid, dim3(256), 0, st, a);
@@ -634,31 +685,46 @@ __global__ __launch_bounds__(256, 2) void wgrad_tile_kernel(WgradArgs a) {
   }
 }
 
-// Both sums of the weight gradient: out[i] = sum_s part[s][i] for i < count
-// and bout[j] = sum_s bpart[s][j] for j < bcount (bpart may be null).  A block
-// owns 64 consecutive entries; its 16 groups of 16 threads each add every
-// 16th split (four entries per thread), then one group adds the 16 sums, all
-// in a fixed order.  count and bcount are multiples of 4.
-__global__ __launch_bounds__(256) void sum_splits_kernel(const float* part, long long count,
-                                                         const float* bpart, int bcount,
-                                                         int splits, float* out, float* bout) {
+// Sums over the splits of one or more weight gradients: dw[i] = sum_s
+// part[s][i] for i < count and db[j] = sum_s bpart[s][j] for j < bcount (bpart
+// may be null).  A block owns 64 consecutive entries; its 16 groups of 16
+// threads each add every 16th split (four entries per thread), then one
+// group adds the 16 sums, all in a fixed order.  Counts are multiples of 4.
+constexpr int kMaxLayers = 16;
+struct SumArgs {
+  int layers;
+  struct {
+    const float* part;
+    const float* bpart;
+    float* dw;
+    float* db;
+    long long count;
+    int bcount, splits, first, wblocks;   // first block, blocks of the weights
+  } l[kMaxLayers];
+};
+
+__global__ __launch_bounds__(256) void sum_splits_kernel(SumArgs a) {
   __shared__ f32x4 s[16][16];
   const int e = threadIdx.x & 15, k0 = threadIdx.x >> 4;
-  const long long wblocks = (count + 63) / 64;
-  const bool bias = blockIdx.x >= wblocks;
-  const float* src = bias ? bpart : part;
-  float* dst = bias ? bout : out;
-  const long long n = bias ? bcount : count;
-  const long long i = ((long long)blockIdx.x - (bias ? wblocks : 0)) * 64 + 4 * e;
+  int k = 0;
+  while (k + 1 < a.layers && int(blockIdx.x) >= a.l[k + 1].first) ++k;
+  const int block = blockIdx.x - a.l[k].first, splits = a.l[k].splits;
+  const bool bias = block >= a.l[k].wblocks;
+  const float* src = bias ? a.l[k].bpart : a.l[k].part;
+  float* dst = bias ? a.l[k].db : a.l[k].dw;
+  const long long n = bias ? a.l[k].bcount : a.l[k].count;
+  const long long i = (long long)(block - (bias ? a.l[k].wblocks : 0)) * 64 + 4 * e;
   f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (i < n)
-    for (int k = k0; k < splits; k += 16)
-      v += *reinterpret_cast<const f32x4*>(src + (long long)k * n + i);
+  if (i < n) {
+#pragma unroll 4
+    for (int j = k0; j < splits; j += 16)
+      v += *reinterpret_cast<const f32x4*>(src + (long long)j * n + i);
+  }
   s[k0][e] = v;
   __syncthreads();
   if (k0 == 0 && i < n) {
 #pragma unroll
-    for (int k = 1; k < 16; ++k) v += s[k][e];
+    for (int j = 1; j < 16; ++j) v += s[j][e];
     *reinterpret_cast<f32x4*>(dst + i) = v;
   }
 }
@@ -704,12 +770,9 @@ __global__ void relu_bwd_kernel(bf16* d, int ldd, const bf16* y, int ldy, long l
        e += (long long)gridDim.x * blockDim.x) {
     const long long p = e / cv;
     const int c = int(e % cv) * 8;
-    bf16x8 dv = *reinterpret_cast<const bf16x8*>(d + p * ldd + c);
-    const bf16x8 yv = *reinterpret_cast<const bf16x8*>(y + p * ldy + c);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (!((float)yv[u] > 0.f)) dv[u] = (bf16)0.f;
-    *reinterpret_cast<bf16x8*>(d + p * ldd + c) = dv;
+    const bf16x8 dv = *reinterpret_cast<const bf16x8*>(d + p * ldd + c);
+    *reinterpret_cast<bf16x8*>(d + p * ldd + c) =
+        relu_mask(dv, *reinterpret_cast<const bf16x8*>(y + p * ldy + c));
   }
 }
 
@@ -741,8 +804,10 @@ __global__ void pool2_fwd_kernel(const bf16* x, int ldx, bf16* y, int ldy, int n
   }
 }
 
+// mask (or null): the result is zeroed where mask <= 0 (ReLU backward)
 __global__ void pool2_bwd_kernel(const bf16* dy, int lddy, const bf16* add, int ldadd, bf16* dx,
-                                 int lddx, int n, int h, int wd, int cv) {
+                                 int lddx, int n, int h, int wd, int cv, const bf16* mask,
+                                 int ldmask) {
   const int ho = h / 2, wo = wd / 2;
   const long long total = (long long)n * h * wd * cv;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
@@ -758,6 +823,7 @@ __global__ void pool2_bwd_kernel(const bf16* dy, int lddy, const bf16* add, int 
     bf16x8 o;
 #pragma unroll
     for (int u = 0; u < 8; ++u) o[u] = (bf16)((float)a[u] + 0.25f * (float)g[u]);
+    if (mask) o = relu_mask(o, *reinterpret_cast<const bf16x8*>(mask + p * ldmask + c));
     *reinterpret_cast<bf16x8*>(dx + p * lddx + c) = o;
   }
 }
@@ -779,8 +845,10 @@ __global__ void up2_fwd_kernel(const bf16* x, int ldx, bf16* y, int ldy, int n, 
   }
 }
 
+// mask (or null): a fine image (2h x 2wd) that holds each coarse value four
+// times; the result is zeroed where it is <= 0 (ReLU backward)
 __global__ void up2_bwd_kernel(const bf16* dy, int lddy, bf16* dx, int lddx, int n, int h, int wd,
-                               int cv) {
+                               int cv, const bf16* mask, int ldmask) {
   const int wf = 2 * wd;
   const long long total = (long long)n * h * wd * cv;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
@@ -802,6 +870,9 @@ __global__ void up2_bwd_kernel(const bf16* dy, int lddy, bf16* dx, int lddx, int
     bf16x8 o;
 #pragma unroll
     for (int u = 0; u < 8; ++u) o[u] = (bf16)s[u];
+    if (mask)
+      o = relu_mask(o, *reinterpret_cast<const bf16x8*>(
+                           mask + ((nn * 2 * h + 2 * Y) * wf + 2 * X) * ldmask + c));
     *reinterpret_cast<bf16x8*>(dx + pc * lddx + c) = o;
   }
 }
@@ -847,16 +918,24 @@ __global__ __launch_bounds__(256) void loss_partial_kernel(const float* out, int
   }
 }
 
-// fixed-order tree over the per-block partials (one block of 256 threads)
-__global__ __launch_bounds__(256) void loss_final_kernel(double* work, int blocks) {
+// Gradient of the loss, 8 channels of one pixel per thread.  Every block
+// first adds the per-block partials in the same fixed-order tree (8 KB from
+// L2, cheaper than a launch of its own); block 0 writes the loss and the
+// fluid count behind the partials.  ldo is a multiple of 8.
+__global__ __launch_bounds__(256) void loss_grad_kernel(const float* __restrict__ out, int ldo,
+                                                        const float* __restrict__ t,
+                                                        const uint8_t* __restrict__ fluid,
+                                                        long long npix, bf16* __restrict__ dout,
+                                                        const double* __restrict__ work,
+                                                        double* __restrict__ fin, int blocks) {
   __shared__ double ssq[256], sn[256];
-  double sq = 0.0, n = 0.0;
+  double sq = 0.0, cnt = 0.0;
   for (int b = threadIdx.x; b < blocks; b += 256) {
     sq += work[2 * b];
-    n += work[2 * b + 1];
+    cnt += work[2 * b + 1];
   }
   ssq[threadIdx.x] = sq;
-  sn[threadIdx.x] = n;
+  sn[threadIdx.x] = cnt;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) {
@@ -865,24 +944,22 @@ __global__ __launch_bounds__(256) void loss_final_kernel(double* work, int block
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    work[2 * blocks] = sn[0] > 0 ? ssq[0] / (3.0 * sn[0]) : 0.0;
-    work[2 * blocks + 1] = sn[0];
+  const double n = sn[0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    fin[0] = n > 0 ? ssq[0] / (3.0 * n) : 0.0;
+    fin[1] = n;
   }
-}
-
-__global__ void loss_grad_kernel(const float* out, int ldo, const float* t, const uint8_t* fluid,
-                                 long long npix, bf16* dout, const double* fin) {
-  const double n = fin[1];
   const float scale = n > 0 ? float(2.0 / (3.0 * n)) : 0.f;
-  const long long total = npix * ldo;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const long long p = e / ldo;
-    const int c = int(e % ldo);
-    float g = 0.f;
-    if (c < 3 && fluid[p]) g = scale * (out[p * ldo + c] - t[p * 3 + c]);
-    dout[e] = (bf16)g;
+  const int cv = ldo / 8;
+  const long long total = npix * cv;
+  for (long long e = blockIdx.x * 256LL + threadIdx.x; e < total; e += gridDim.x * 256LL) {
+    const long long p = e / cv;
+    bf16x8 g = bf16x8{};
+    if (e == p * cv && fluid[p]) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) g[c] = (bf16)(scale * (out[p * ldo + c] - t[p * 3 + c]));
+    }
+    *reinterpret_cast<bf16x8*>(dout + 8 * e) = g;
   }
 }
 
@@ -1089,6 +1166,52 @@ static int launch_fields(const float* out, int ldo, int n, int res, const float*
   return UNET_OK;
 }
 
+// Partial sums of a weight gradient; the sums over its splits are appended
+// to `sums` (launch_sums).  Returns the floats of `work` it uses in *used.
+static int launch_wgrad(const bf16* dy, int lddy, const bf16* x, int ldx, float* dw, float* db,
+                        int n, int h, int wd, int cin, int cout, float* work, SumArgs& sums,
+                        hipStream_t st, long long* used = nullptr) {
+  const WgradPlan p = wgrad_plan(n, h, wd, cin, cout);
+  const long long wcount = 9LL * cin * cout;
+  float* bpart = db ? work + p.splits * wcount : nullptr;
+  WgradArgs a{dy, lddy, x, ldx, work, bpart, n, h, wd, cin, cout, p.tiles_x, p.tiles_y, p.units,
+              p.splits};
+  const int ct = p.wide ? 64 : 32;
+  dim3 grid((cin / ct) * (cout / ct), p.splits);
+  if (p.wide && p.narrow)
+    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 16, 8>), grid, dim3(256), 0, st, a);
+  else if (p.wide)
+    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 32, 4>), grid, dim3(256), 0, st, a);
+  else if (p.narrow)
+    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 16, 8>), grid, dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 32, 4>), grid, dim3(256), 0, st, a);
+  UCHECK(hipGetLastError());
+  auto& l = sums.l[sums.layers];
+  const int prev = sums.layers - 1;
+  l.part = work;
+  l.bpart = bpart;
+  l.dw = dw;
+  l.db = db;
+  l.count = wcount;
+  l.bcount = db ? cout : 0;
+  l.splits = p.splits;
+  l.wblocks = int((wcount + 63) / 64);
+  l.first = prev < 0 ? 0 : sums.l[prev].first + sums.l[prev].wblocks +
+                               (sums.l[prev].bcount + 63) / 64;
+  ++sums.layers;
+  if (used) *used = p.splits * (wcount + cout);
+  return UNET_OK;
+}
+
+static int launch_sums(const SumArgs& sums, hipStream_t st) {
+  const auto& l = sums.l[sums.layers - 1];
+  hipLaunchKernelGGL(sum_splits_kernel, dim3(l.first + l.wblocks + (l.bcount + 63) / 64),
+                     dim3(256), 0, st, sums);
+  UCHECK(hipGetLastError());
+  return UNET_OK;
+}
+
 // ===========================================================================
 // C ABI: layers
 // ===========================================================================
@@ -1139,28 +1262,10 @@ int unet_conv3x3_bwd_weight(const void* dy, int32_t lddy, const void* x, int32_t
     return fail(UNET_EINVAL, "bwd_weight: cin and cout must be positive multiples of 32");
   if (lddy % 8 || ldx % 8 || lddy < cout || ldx < cin)
     return fail(UNET_EINVAL, "bwd_weight: bad ld");
-  hipStream_t st = as_stream(stream);
-  const WgradPlan p = wgrad_plan(n, h, wd, cin, cout);
-  const long long wcount = 9LL * cin * cout;
-  float* bpart = dbias ? work + p.splits * wcount : nullptr;
-  WgradArgs a{static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(x), ldx, work, bpart,
-              n, h, wd, cin, cout, p.tiles_x, p.tiles_y, p.units, p.splits};
-  const int ct = p.wide ? 64 : 32;
-  dim3 grid((cin / ct) * (cout / ct), p.splits);
-  if (p.wide && p.narrow)
-    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 16, 8>), grid, dim3(256), 0, st, a);
-  else if (p.wide)
-    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 32, 4>), grid, dim3(256), 0, st, a);
-  else if (p.narrow)
-    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 16, 8>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 32, 4>), grid, dim3(256), 0, st, a);
-  UCHECK(hipGetLastError());
-  const long long blocks = (wcount + 63) / 64 + (dbias ? (cout + 63) / 64 : 0);
-  hipLaunchKernelGGL(sum_splits_kernel, dim3((unsigned)blocks), dim3(256), 0, st, work, wcount,
-                     bpart, cout, p.splits, dw, dbias);
-  UCHECK(hipGetLastError());
-  return UNET_OK;
+  SumArgs sums{};
+  const int rc = launch_wgrad(static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(x), ldx,
+                              dw, dbias, n, h, wd, cin, cout, work, sums, as_stream(stream));
+  return rc ? rc : launch_sums(sums, as_stream(stream));
 }
 
 int unet_relu_bwd(void* d, int32_t ldd, const void* y, int32_t ldy, int64_t npix, int32_t ch,
@@ -1194,7 +1299,7 @@ int unet_pool2_bwd(const void* dy, int32_t lddy, const void* add, int32_t ldadd,
   const long long total = (long long)n * h * wd * (ch / 8);
   hipLaunchKernelGGL(pool2_bwd_kernel, dim3(grid_for(total)), dim3(256), 0, as_stream(stream),
                      static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(add), ldadd,
-                     static_cast<bf16*>(dx), lddx, n, h, wd, ch / 8);
+                     static_cast<bf16*>(dx), lddx, n, h, wd, ch / 8, (const bf16*)nullptr, 0);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
@@ -1218,7 +1323,7 @@ int unet_up2_bwd(const void* dy, int32_t lddy, void* dx, int32_t lddx, int32_t n
   const long long total = (long long)n * h * wd * (ch / 8);
   hipLaunchKernelGGL(up2_bwd_kernel, dim3(grid_for(total)), dim3(256), 0, as_stream(stream),
                      static_cast<const bf16*>(dy), lddy, static_cast<bf16*>(dx), lddx, n, h, wd,
-                     ch / 8);
+                     ch / 8, (const bf16*)nullptr, 0);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
@@ -1235,10 +1340,11 @@ int unet_mse_loss(const float* out, int32_t ldo, const float* target, const uint
   hipStream_t st = as_stream(stream);
   hipLaunchKernelGGL(loss_partial_kernel, dim3(kLossBlocks), dim3(256), 0, st, out, ldo, target,
                      fluid, (long long)npix, work);
-  hipLaunchKernelGGL(loss_final_kernel, dim3(1), dim3(256), 0, st, work, kLossBlocks);
-  hipLaunchKernelGGL(loss_grad_kernel, dim3(grid_for(npix * ldo)), dim3(256), 0, st, out, ldo,
-                     target, fluid, (long long)npix, static_cast<bf16*>(dout),
-                     (const double*)(work + 2 * kLossBlocks));
+  const long long vecs = npix * (ldo / 8);
+  hipLaunchKernelGGL(loss_grad_kernel, dim3((unsigned)std::min<long long>((vecs + 255) / 256, 1024)),
+                     dim3(256), 0, st, out, ldo, target, fluid, (long long)npix,
+                     static_cast<bf16*>(dout), (const double*)work, work + 2 * kLossBlocks,
+                     kLossBlocks);
   UCHECK(hipGetLastError());
   if (loss) {
     UCHECK(hipMemcpyAsync(loss, work + 2 * kLossBlocks, sizeof(double), hipMemcpyDeviceToHost,
@@ -1354,7 +1460,9 @@ long long npix(const unet* net, int level, int n) {
 int forward_impl(unet* net, const bf16* x0, int n, float* out) {
   hipStream_t st = net->stream;
   net->act[B_X0] = const_cast<bf16*>(x0);
-  auto conv = [&](int k) -> int {
+  // pool: buffer that receives the 2x2 means of the output, or -1; up: the
+  // output goes upsampled into the finer level's buffer c.out names
+  auto conv = [&](int k, int pool = -1, int up = -1) -> int {
     const Conv& c = net->convs[k];
     const int s = side(net, c.level);
     ConvArgs a{};
@@ -1366,10 +1474,17 @@ int forward_impl(unet* net, const bf16* x0, int n, float* out) {
       a.y = out;
       a.ldy = UNET_OUT_CHANNELS;
       a.out_f32 = 1;
+    } else if (up >= 0) {
+      a.y = net->act[up];
+      a.ldy = kBuf[up].ch;
+      a.up = 1;
     } else {
       a.y = net->act[c.out] + c.out_off;
       a.ldy = kBuf[c.out].ch;
-      a.out_f32 = 0;
+    }
+    if (pool >= 0) {
+      a.pool = net->act[pool];
+      a.ldpool = kBuf[pool].ch;
     }
     a.npix = n * s * s;
     a.h = s;
@@ -1379,38 +1494,44 @@ int forward_impl(unet* net, const bf16* x0, int n, float* out) {
     a.relu = c.relu;
     return launch_conv(a, st);
   };
-  auto pool = [&](int src, int off, int dst, int level, int ch) -> int {
-    const int s = side(net, level);
-    return unet_pool2_fwd(net->act[src] + off, kBuf[src].ch, net->act[dst], kBuf[dst].ch, n, s, s,
-                          ch, st);
-  };
-  auto up = [&](int src, int dst, int coarse_level, int ch) -> int {
-    const int s = side(net, coarse_level);
-    return unet_up2_fwd(net->act[src], kBuf[src].ch, net->act[dst], kBuf[dst].ch, n, s, s, ch,
-                        st);
-  };
   int rc;
-  if ((rc = conv(0)) || (rc = conv(1)) || (rc = pool(B_CAT0, 64, B_P1, 0, 32)) ||
-      (rc = conv(2)) || (rc = conv(3)) || (rc = pool(B_CAT1, 128, B_P2, 1, 64)) ||
-      (rc = conv(4)) || (rc = conv(5)) || (rc = pool(B_CAT2, 256, B_P3, 2, 128)) ||
-      (rc = conv(6)) || (rc = conv(7)) || (rc = up(B_B3, B_CAT2, 3, 256)) || (rc = conv(8)) ||
-      (rc = conv(9)) || (rc = up(B_D2, B_CAT1, 2, 128)) || (rc = conv(10)) || (rc = conv(11)) ||
-      (rc = up(B_D1, B_CAT0, 1, 64)) || (rc = conv(12)) || (rc = conv(13)) || (rc = conv(14)))
+  if ((rc = conv(0)) || (rc = conv(1, B_P1)) || (rc = conv(2)) || (rc = conv(3, B_P2)) ||
+      (rc = conv(4)) || (rc = conv(5, B_P3)) || (rc = conv(6)) || (rc = conv(7, -1, B_CAT2)) ||
+      (rc = conv(8)) || (rc = conv(9, -1, B_CAT1)) || (rc = conv(10)) ||
+      (rc = conv(11, -1, B_CAT0)) || (rc = conv(12)) || (rc = conv(13)) || (rc = conv(14)))
     return rc;
   return UNET_OK;
 }
 
-// Gradients of conv k given the gradient of its (pre-activation) output.
-int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_dx) {
+// Gradients of conv k given the gradient of its (pre-activation) output; the
+// input gradient is masked by the ReLU of the input buffer (relu), or left
+// as it is where the buffer has none or receives further gradients.
+int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_dx, bool relu,
+                  SumArgs& sums, long long& used) {
   const Conv& c = net->convs[k];
   const int s = side(net, c.level);
   hipStream_t st = net->stream;
-  int rc = unet_conv3x3_bwd_weight(dy, lddy, net->act[c.in] + c.in_off, kBuf[c.in].ch,
-                                   net->grad + c.w_off, net->grad + c.b_off, n, s, s, c.cin,
-                                   c.cout, net->wwork, st);
+  long long u = 0;
+  int rc = launch_wgrad(dy, lddy, net->act[c.in] + c.in_off, kBuf[c.in].ch, net->grad + c.w_off,
+                        net->grad + c.b_off, n, s, s, c.cin, c.cout, net->wwork + used, sums, st,
+                        &u);
+  used += u;
   if (rc || !need_dx) return rc;
-  ConvArgs a{dy, lddy, net->wt + c.w_off, nullptr, net->gact[c.in] + c.in_off, kBuf[c.in].ch,
-             n * s * s, s, s, c.cout, c.cin, 0, 0};
+  ConvArgs a{};
+  a.x = dy;
+  a.ldx = lddy;
+  a.w = net->wt + c.w_off;
+  a.y = net->gact[c.in] + c.in_off;
+  a.ldy = kBuf[c.in].ch;
+  a.npix = n * s * s;
+  a.h = s;
+  a.wd = s;
+  a.cin = c.cout;
+  a.cout = c.cin;
+  if (relu) {
+    a.mask = net->act[c.in] + c.in_off;
+    a.ldmask = kBuf[c.in].ch;
+  }
   return launch_conv(a, st);
 }
 
@@ -1436,82 +1557,54 @@ int flip_weights(unet* net) {
   return UNET_OK;
 }
 
-// In place: gradient of buffer b (channels [off, off + ch)) times relu'.
-int relu_back(unet* net, int b, int off, int ch, int n) {
-  return unet_relu_bwd(net->gact[b] + off, kBuf[b].ch, net->act[b] + off, kBuf[b].ch,
-                       npix(net, kBuf[b].level, n), ch, net->stream);
-}
-
 int backward_impl(unet* net, int n) {
   hipStream_t st = net->stream;
-  int rc;
+  int rc = UNET_OK;
+  SumArgs sums{};
+  long long used = 0;   // partial sums of all layers stay until one launch adds them
+  auto conv = [&](int k, int buf, int off, bool need_dx, bool relu) {
+    const bf16* dy = buf < 0 ? net->gout : net->gact[buf] + off;
+    return conv_backward(net, k, n, dy, buf < 0 ? UNET_OUT_CHANNELS : kBuf[buf].ch, need_dx, relu,
+                         sums, used);
+  };
+  // gradient of an upsampled buffer (channels [0, ch) of the concatenation),
+  // masked by its ReLU: the concatenation holds its values
   auto upb = [&](int fine_buf, int coarse_buf, int coarse_level, int ch) -> int {
-    const int s = side(net, coarse_level);
-    return unet_up2_bwd(net->gact[fine_buf], kBuf[fine_buf].ch, net->gact[coarse_buf],
-                        kBuf[coarse_buf].ch, n, s, s, ch, st);
+    const int s = side(net, coarse_level), ldf = kBuf[fine_buf].ch;
+    hipLaunchKernelGGL(up2_bwd_kernel, dim3(grid_for((long long)n * s * s * (ch / 8))), dim3(256),
+                       0, st, net->gact[fine_buf], ldf, net->gact[coarse_buf],
+                       kBuf[coarse_buf].ch, n, s, s, ch / 8, net->act[fine_buf], ldf);
+    UCHECK(hipGetLastError());
+    return UNET_OK;
   };
+  // skip gradient (channels [off, ..) of the concatenation) plus the pooled
+  // path, masked by the ReLU
   auto poolb = [&](int coarse_buf, int fine_buf, int off, int fine_level, int ch) -> int {
-    const int s = side(net, fine_level);
+    const int s = side(net, fine_level), ldf = kBuf[fine_buf].ch;
     bf16* g = net->gact[fine_buf] + off;
-    return unet_pool2_bwd(net->gact[coarse_buf], kBuf[coarse_buf].ch, g, kBuf[fine_buf].ch, g,
-                          kBuf[fine_buf].ch, n, s, s, ch, st);
+    hipLaunchKernelGGL(pool2_bwd_kernel, dim3(grid_for((long long)n * s * s * (ch / 8))),
+                       dim3(256), 0, st, net->gact[coarse_buf], kBuf[coarse_buf].ch, g, ldf, g,
+                       ldf, n, s, s, ch / 8, net->act[fine_buf] + off, ldf);
+    UCHECK(hipGetLastError());
+    return UNET_OK;
   };
-  // output layer (linear)
-  if ((rc = conv_backward(net, 14, n, net->gout, UNET_OUT_CHANNELS, true))) return rc;
-  // level 0 decoder
-  if ((rc = relu_back(net, B_D0, 0, 32, n)) || (rc = conv_backward(net, 13, n, net->gact[B_D0], 32, true)))
+  // output layer (linear), then the decoder upwards: per level the two
+  // convolutions, then the upsampled half of the concatenation
+  if ((rc = conv(14, -1, 0, true, true)) || (rc = conv(13, B_D0, 0, true, true)) ||
+      (rc = conv(12, B_D0A, 0, true, false)) || (rc = upb(B_CAT0, B_D1, 1, 64)) ||
+      (rc = conv(11, B_D1, 0, true, true)) || (rc = conv(10, B_D1A, 0, true, false)) ||
+      (rc = upb(B_CAT1, B_D2, 2, 128)) || (rc = conv(9, B_D2, 0, true, true)) ||
+      (rc = conv(8, B_D2A, 0, true, false)) || (rc = upb(B_CAT2, B_B3, 3, 256)))
     return rc;
-  if ((rc = relu_back(net, B_D0A, 0, 32, n)) ||
-      (rc = conv_backward(net, 12, n, net->gact[B_D0A], 32, true)))
+  // bottom, then the encoder
+  if ((rc = conv(7, B_B3, 0, true, true)) || (rc = conv(6, B_B3A, 0, true, false)) ||
+      (rc = poolb(B_P3, B_CAT2, 256, 2, 128)) || (rc = conv(5, B_CAT2, 256, true, true)) ||
+      (rc = conv(4, B_E2A, 0, true, false)) || (rc = poolb(B_P2, B_CAT1, 128, 1, 64)) ||
+      (rc = conv(3, B_CAT1, 128, true, true)) || (rc = conv(2, B_E1A, 0, true, false)) ||
+      (rc = poolb(B_P1, B_CAT0, 64, 0, 32)) || (rc = conv(1, B_CAT0, 64, true, true)) ||
+      (rc = conv(0, B_E0A, 0, false, false)))
     return rc;
-  if ((rc = upb(B_CAT0, B_D1, 1, 64))) return rc;
-  // level 1 decoder
-  if ((rc = relu_back(net, B_D1, 0, 64, n)) || (rc = conv_backward(net, 11, n, net->gact[B_D1], 64, true)))
-    return rc;
-  if ((rc = relu_back(net, B_D1A, 0, 64, n)) ||
-      (rc = conv_backward(net, 10, n, net->gact[B_D1A], 64, true)))
-    return rc;
-  if ((rc = upb(B_CAT1, B_D2, 2, 128))) return rc;
-  // level 2 decoder
-  if ((rc = relu_back(net, B_D2, 0, 128, n)) ||
-      (rc = conv_backward(net, 9, n, net->gact[B_D2], 128, true)))
-    return rc;
-  if ((rc = relu_back(net, B_D2A, 0, 128, n)) ||
-      (rc = conv_backward(net, 8, n, net->gact[B_D2A], 128, true)))
-    return rc;
-  if ((rc = upb(B_CAT2, B_B3, 3, 256))) return rc;
-  // bottom
-  if ((rc = relu_back(net, B_B3, 0, 256, n)) ||
-      (rc = conv_backward(net, 7, n, net->gact[B_B3], 256, true)))
-    return rc;
-  if ((rc = relu_back(net, B_B3A, 0, 256, n)) ||
-      (rc = conv_backward(net, 6, n, net->gact[B_B3A], 256, true)))
-    return rc;
-  // level 2 encoder: skip gradient (cat2[256:]) plus the pooled path
-  if ((rc = poolb(B_P3, B_CAT2, 256, 2, 128))) return rc;
-  if ((rc = relu_back(net, B_CAT2, 256, 128, n)) ||
-      (rc = conv_backward(net, 5, n, net->gact[B_CAT2] + 256, 384, true)))
-    return rc;
-  if ((rc = relu_back(net, B_E2A, 0, 128, n)) ||
-      (rc = conv_backward(net, 4, n, net->gact[B_E2A], 128, true)))
-    return rc;
-  // level 1 encoder
-  if ((rc = poolb(B_P2, B_CAT1, 128, 1, 64))) return rc;
-  if ((rc = relu_back(net, B_CAT1, 128, 64, n)) ||
-      (rc = conv_backward(net, 3, n, net->gact[B_CAT1] + 128, 192, true)))
-    return rc;
-  if ((rc = relu_back(net, B_E1A, 0, 64, n)) ||
-      (rc = conv_backward(net, 2, n, net->gact[B_E1A], 64, true)))
-    return rc;
-  // level 0 encoder
-  if ((rc = poolb(B_P1, B_CAT0, 64, 0, 32))) return rc;
-  if ((rc = relu_back(net, B_CAT0, 64, 32, n)) ||
-      (rc = conv_backward(net, 1, n, net->gact[B_CAT0] + 64, 96, true)))
-    return rc;
-  if ((rc = relu_back(net, B_E0A, 0, 32, n)) ||
-      (rc = conv_backward(net, 0, n, net->gact[B_E0A], 32, false)))
-    return rc;
-  return UNET_OK;
+  return launch_sums(sums, st);
 }
 
 uint64_t splitmix_next(uint64_t& s) {
@@ -1554,11 +1647,17 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
     c.b_off = off;
     off += c.cout;
     net->convs.push_back(c);
-    const int s = res >> c.level;
-    for (int nb = 1; nb <= max_batch; ++nb)
-      wwork_max = std::max<long long>(wwork_max, unet_wgrad_work_floats(nb, s, s, c.cin, c.cout));
   }
   net->nparams = off;
+  // the partial sums of all layers of one backward pass
+  for (int nb = 1; nb <= max_batch; ++nb) {
+    long long words = 0;
+    for (const Conv& c : net->convs) {
+      const int s = res >> c.level;
+      words += unet_wgrad_work_floats(nb, s, s, c.cin, c.cout);
+    }
+    wwork_max = std::max(wwork_max, words);
+  }
   auto alloc = [&](void** p, size_t bytes) {
     return hipMalloc(p, bytes) == hipSuccess;
   };
@@ -1573,7 +1672,8 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
   for (int b = 0; ok && b < B_COUNT; ++b) {
     const long long s = res >> kBuf[b].level;
     const size_t bytes = 2ULL * max_batch * s * s * kBuf[b].ch;
-    if (b != B_X0) ok = alloc((void**)&net->act[b], bytes);
+    // (B_B3, B_D2 and B_D1 live upsampled in the concatenations only)
+    if (b != B_X0 && b != B_B3 && b != B_D2 && b != B_D1) ok = alloc((void**)&net->act[b], bytes);
     if (ok) ok = alloc((void**)&net->gact[b], bytes);
   }
   if (!ok) {
