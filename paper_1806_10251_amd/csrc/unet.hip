@@ -49,6 +49,23 @@ int fail(int code, const std::string& m) {
 
 inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
+// 16-byte loads through a buffer resource: a byte offset at or beyond `bytes`
+// reads zeros, so image borders cost one select and no branch.
+using Rsrc = __amdgpu_buffer_rsrc_t;
+constexpr unsigned kOutside = 0xFFFFFFF0u;   // an offset no image reaches
+constexpr long long kMaxRsrc = 0x7FFFFFF0LL;
+__device__ __forceinline__ Rsrc image_rsrc(const bf16* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(p), 0, int(bytes), 0x00020000);
+}
+__device__ __forceinline__ bf16x8 load8(Rsrc r, unsigned off) {
+  return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, int(off), 0, 0));
+}
+// Bytes from the first channel of an image (pixel stride ld) to the end of
+// the last pixel's ch channels.
+inline long long image_bytes(int h, int wd, int ld, int ch) {
+  return 2 * (((long long)h * wd - 1) * ld + ch);
+}
+
 __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, const f32x4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -71,6 +88,7 @@ struct ConvArgs {
   bf16* pool;          // 2x2 mean of the output (h, wd even), or null
   int ldpool;
   int up;              // write each pixel to its four fine pixels (2h x 2wd image)
+  unsigned xbytes;     // image_bytes of x (set by launch_conv)
 };
 
 __device__ __forceinline__ bf16x8 relu_mask(bf16x8 d, const bf16x8& y) {
@@ -238,31 +256,30 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   {
     // input tile: HP pixels x cin channels, eight 16-byte loads in flight
     const int cv = a.cin >> 3, nvec = HP * cv;
-    const bf16* xi = a.x + (long long)img * a.h * a.wd * a.ldx;
-    int px = tid / cv, c = tid % cv;
-    const int qs = 256 / cv, rs = 256 % cv;
+    const Rsrc xr = image_rsrc(a.x + (long long)img * a.h * a.wd * a.ldx, a.xbytes);
+    const int qs = 256 / cv, rs = 256 - qs * cv;
+    int px = tid / cv, c = tid - px * cv;
     for (int base = 0; base < nvec; base += 8 * 256) {
       bf16x8 v[8];
       int at[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const bool in = base + 256 * u + tid < nvec;
-        const int yy = px / HX, xx = px - yy * HX;
-        const int y = y0 + yy - 1, x = x0 + xx - 1;
-        at[u] = in ? px * S + 16 * c : -1;
-        v[u] = bf16x8{};
-        if (in && y >= 0 && y < a.h && x >= 0 && x < a.wd)
-          v[u] = *reinterpret_cast<const bf16x8*>(xi + (long long)(y * a.wd + x) * a.ldx + 8 * c);
-        px += qs;
-        c += rs;
-        if (c >= cv) {
-          c -= cv;
-          ++px;
+        if (base + 256 * u < nvec) {
+          const int yy = px / HX, xx = px - yy * HX;
+          const int y = y0 + yy - 1, x = x0 + xx - 1;
+          const bool in = unsigned(y) < unsigned(a.h) && unsigned(x) < unsigned(a.wd);
+          v[u] = load8(xr, in ? unsigned((y * a.wd + x) * a.ldx + 8 * c) * 2u : kOutside);
+          at[u] = px * S + 16 * c;
+          px += qs;
+          c += rs;
+          const bool wrap = c >= cv;
+          px += wrap ? 1 : 0;
+          c -= wrap ? cv : 0;
         }
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (at[u] >= 0) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
+        if (base + 256 * u + tid < nvec) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
     }
   }
   store_w(0);
@@ -432,7 +449,7 @@ int conv_tile_go(const ConvArgs& a, bool narrow, hipStream_t st) {
                 : launch_conv_tile<MP, NC, WP, WC, 32, KS>(a, st);
 }
 
-int launch_conv(const ConvArgs& a, hipStream_t st) {
+int launch_conv(ConvArgs a, hipStream_t st) {
   if (a.cin <= 0 || a.cout <= 0 || a.cin % 32 || a.cout % 32)
     return fail(UNET_EINVAL, "conv: cin and cout must be positive multiples of 32");
   if (a.ldx % 8 || a.ldy % 8 || a.ldx < a.cin || a.ldy < a.cout)
@@ -440,22 +457,27 @@ int launch_conv(const ConvArgs& a, hipStream_t st) {
   if (a.npix <= 0 || a.h <= 0 || a.wd <= 0 || a.npix % (a.h * a.wd))
     return fail(UNET_EINVAL, "conv: bad image size");
   if (!a.x || !a.w || !a.y) return fail(UNET_EINVAL, "conv: null pointer");
+  const long long xbytes = image_bytes(a.h, a.wd, a.ldx, a.cin);
+  a.xbytes = (unsigned)xbytes;
+  const bool tiles = xbytes <= kMaxRsrc;   // (an image of 2 GB takes the general path)
   // 16-pixel-wide tiles where 32 would pad the rows more
   const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32;
   // the largest wave tile that still gives about one wave per SIMD (1024)
   const long long px32 = (a.npix + 31) / 32;
-  if (a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048 && conv_tile_fits<2, 2, 4, 1, 96>(a, narrow))
+  if (tiles && a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048 &&
+      conv_tile_fits<2, 2, 4, 1, 96>(a, narrow))
     return conv_tile_go<2, 2, 4, 1, 96>(a, narrow, st);
-  if (a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024 &&
+  if (tiles && a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024 &&
       conv_tile_fits<1, 2, 2, 2, 96>(a, narrow))
     return conv_tile_go<1, 2, 2, 2, 96>(a, narrow, st);
-  if (a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 288>(a, narrow))
+  if (tiles && a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 288>(a, narrow))
     return conv_tile_go<1, 1, 2, 2, 288>(a, narrow, st);
-  if (a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 96>(a, narrow))
+  if (tiles && a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 96>(a, narrow))
     return conv_tile_go<1, 1, 2, 2, 96>(a, narrow, st);
-  if (px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 288>(a, narrow))
-    return conv_tile_go<2, 1, 4, 1, 288>(a, narrow, st);
-  if (conv_tile_fits<1, 1, 4, 1, 288>(a, narrow)) return conv_tile_go<1, 1, 4, 1, 288>(a, narrow, st);
+  if (tiles && px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 96>(a, narrow))
+    return conv_tile_go<2, 1, 4, 1, 96>(a, narrow, st);
+  if (tiles && conv_tile_fits<1, 1, 4, 1, 96>(a, narrow))
+    return conv_tile_go<1, 1, 4, 1, 96>(a, narrow, st);
   // more input channels than LDS holds (none of the network's layers):
   // operands straight from memory
   if (a.mask || a.pool || a.up) return fail(UNET_EINVAL, "conv: no fused form of this size");
@@ -512,19 +534,21 @@ int flip_tiles(int cin, int cout) { return 9 * (cin / 32) * (cout / 32); }
 // ---------------------------------------------------------------------------
 // Convolution, weight and bias gradients
 // ---------------------------------------------------------------------------
-// Tiled weight gradient: a block owns 32 WCO output x 32 WCI input channels
-// of all nine taps and runs over pixel tiles of TX x TY (one share of them,
-// `split`).  dy and x (with its one-pixel ring, zeros outside the image) are
-// staged in LDS as they lie in memory, [pixel][channel]; the MFMA reduces
-// over pixels, so both operands are read with the transposing LDS load
-// (ds_read_b64_tr_b16: of 16 lanes, lane i receives element i of four rows
-// of 16), two loads per operand of 16 pixels x 32 channels.  One dy operand
-// serves the nine taps, whose x operands are the same rows shifted by the
-// tap.  LDS rows are an odd multiple of 32 bytes, so that the 32-byte pieces
-// of eight rows fall on different banks.  The next tile's global loads are
-// in flight while the current one is multiplied.  The 4 / (WCO WCI) waves of
-// one channel tile split the pixels and add their sums in LDS at the end.
-// The bias partial sums are one more MFMA against a matrix of ones.
+// Tiled weight gradient of one or more layers in one launch: a block owns 32
+// output x 32 input channels of all nine taps of a layer and runs over a
+// share (split) of its pixel tiles of 16 x 16.  dy and x (with its one-pixel
+// ring, zeros outside the image) are staged in LDS as they lie in memory,
+// [pixel][channel]; the MFMA reduces over pixels, so both operands are read
+// with the transposing LDS load (ds_read_b64_tr_b16: of 16 lanes, lane i
+// receives element i of four rows of 16), two loads per operand of 16 pixels
+// x 32 channels.  Rows of 64 bytes without padding: the four rows that half
+// a wave reads cover every bank once (with 96 bytes 37 % of the LDS cycles
+// were conflicts).  A wave owns two image rows; one dy operand serves the
+// nine taps, and the x operands of the second row are two thirds those of
+// the first.  Tiles are double buffered: the next one goes to LDS after this
+// one is multiplied, the one after that is in flight meanwhile.  At the end
+// the eight waves add their sums in LDS.  The bias partial sums are one more
+// MFMA against a matrix of ones.
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
@@ -535,74 +559,134 @@ __device__ __forceinline__ bf16x8 lds_tr8(const char* p0, const char* p1) {
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-struct WgradArgs {
+constexpr int kMaxLayers = 16;
+struct WgradLayer {
   const bf16* dy;
-  int lddy;
   const bf16* x;
-  int ldx;
   float* part;        // [splits][cout][9][cin]
   float* bpart;       // [splits][cout] or null
-  int n, h, wd, cin, cout;
+  float* dw;          // sums over the splits
+  float* db;
+  int lddy, ldx, h, wd, cin, cout;
   int tiles_x, tiles_y, units, splits;
+  int first;                  // first block
+  unsigned dybytes, xbytes;   // image_bytes of a channel tile of dy and of x
+};
+struct WgradGroup {
+  int layers;
+  WgradLayer l[kMaxLayers];
 };
 
-template <int WCO, int WCI, int TX, int TY>
-__global__ __launch_bounds__(256, 2) void wgrad_tile_kernel(WgradArgs a) {
-  constexpr int CO = 32 * WCO, CI = 32 * WCI, WK = 4 / (WCO * WCI);
-  constexpr int SD = 2 * CO + 32, SX = 2 * CI + 32, HX = TX + 2, HP = HX * (TY + 2), P = TX * TY;
+// BIG: images of 2 GB or more, whose loads take 64-bit addresses.
+template <bool BIG>
+__global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
+  constexpr int TX = 16, TY = 16;
+  constexpr int CO = 32, CI = 32, NT = 512, WK = NT / 64;
+  constexpr int SD = 2 * CO, SX = 2 * CI, HX = TX + 2, HP = HX * (TY + 2), P = TX * TY;
   constexpr int kDyVec = P * CO / 8, kXVec = HP * CI / 8;
-  constexpr int kDyPer = (kDyVec + 255) / 256, kXPer = (kXVec + 255) / 256;
-  constexpr int kSum = 4 * 32 * 33 * 4;   // bytes of the final sums over waves
+  constexpr int kDyPer = kDyVec / NT, kXPer = (kXVec + NT - 1) / NT;
+  constexpr int kSum = WK * 32 * 33 * 4;   // bytes of the final sums over waves
   constexpr int kStage = P * SD + HP * SX;
-  __shared__ __align__(16) char smem[kStage > kSum ? kStage : kSum];
-  char* sd = smem;
-  char* sx = smem + P * SD;
+  constexpr int RW = TY / WK;              // rows per wave
+  static_assert(kDyVec % NT == 0 && kStage >= kSum, "tile");
+  __shared__ __align__(16) char smem[2 * kStage];   // two tiles: dy, then x
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wk = wv % WK, wci = (wv / WK) % WCI, wco = wv / (WK * WCI);
-  const int nci = a.cin / CI;
-  const int ci0 = (blockIdx.x % nci) * CI, co0 = (blockIdx.x / nci) * CO;
-  const int u0 = int((long long)blockIdx.y * a.units / a.splits);
-  const int u1 = int((long long)(blockIdx.y + 1) * a.units / a.splits);
-  const bool bias = a.bpart != nullptr && ci0 == 0 && wci == 0;
+  const int wk = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int layer = 0;
+  while (layer + 1 < G.layers && int(blockIdx.x) >= G.l[layer + 1].first) ++layer;
+  const WgradLayer a = G.l[layer];
+  const int nci = a.cin / CI, base = nci * (a.cout / CO);
+  // the channel tiles of one share run on one XCD (block b on XCD b % 8), so
+  // its pixels come into one L2 once
+  const int idx = blockIdx.x - a.first;
+  const bool by8 = a.splits % 8 == 0;
+  const int split = by8 ? (idx >> 3) / base * 8 + (idx & 7) : idx / base;
+  const int tile = (by8 ? idx >> 3 : idx) % base;
+  if (split >= a.splits) return;
+  const int ci0 = (tile % nci) * CI, co0 = (tile / nci) * CO;
+  const int u0 = int((long long)split * a.units / a.splits);
+  const int u1 = int((long long)(split + 1) * a.units / a.splits);
+  const bool bias = a.bpart != nullptr && ci0 == 0;
 
+  // this thread's pieces of a tile: pixel within the tile and byte offset
+  // from the tile's first pixel, the same for every tile
+  int pd_[kDyPer], px_[kXPer];
+  unsigned od[kDyPer], ox[kXPer];
+#pragma unroll
+  for (int i = 0; i < kDyPer; ++i) {
+    const int v = tid + NT * i, q = v / (CO / 8), c = v % (CO / 8);
+    pd_[i] = (q / TX) << 16 | (q % TX);
+    od[i] = unsigned(((q / TX) * a.wd + q % TX) * a.lddy + 8 * c) * 2u;
+  }
+#pragma unroll
+  for (int i = 0; i < kXPer; ++i) {
+    const int v = tid + NT * i, q = v / (CI / 8), c = v % (CI / 8);
+    px_[i] = v < kXVec ? (q / HX) << 16 | (q % HX) : 0x7FFF0000;   // (never inside)
+    ox[i] = unsigned((q / HX * a.wd + q % HX) * a.ldx + 8 * c) * 2u;
+  }
+  // next tile to load
+  int tx = u0 % a.tiles_x, ty = (u0 / a.tiles_x) % a.tiles_y, img = u0 / (a.tiles_x * a.tiles_y);
   bf16x8 rd[kDyPer], rx[kXPer];
-  auto load = [&](int u) {
-    const int tx = u % a.tiles_x;
-    const int rest = u / a.tiles_x;
-    const int ty = rest % a.tiles_y, img = rest / a.tiles_y;
+  auto load = [&]() {
     const int x0 = tx * TX, y0 = ty * TY;
-    const long long base = (long long)img * a.h * a.wd;
+    const long long org = (long long)img * a.h * a.wd;
+    const bf16* dy = a.dy + org * a.lddy + co0;
+    const bf16* xs = a.x + org * a.ldx + ci0;
+    if constexpr (BIG) {
 #pragma unroll
-    for (int i = 0; i < kDyPer; ++i) {
-      const int v = tid + 256 * i, px = v / (CO / 8), c = v % (CO / 8);
-      const int y = y0 + px / TX, x = x0 + px % TX;
-      rd[i] = bf16x8{};
-      if ((kDyVec % 256 == 0 || v < kDyVec) && y < a.h && x < a.wd)
-        rd[i] = *reinterpret_cast<const bf16x8*>(a.dy + (base + (long long)y * a.wd + x) * a.lddy +
-                                                 co0 + 8 * c);
+      for (int i = 0; i < kDyPer; ++i) {
+        const int v = tid + NT * i;
+        const int y = y0 + (pd_[i] >> 16), x = x0 + (pd_[i] & 0xFFFF);
+        rd[i] = bf16x8{};
+        if (y < a.h && x < a.wd)
+          rd[i] = *reinterpret_cast<const bf16x8*>(dy + ((long long)y * a.wd + x) * a.lddy +
+                                                   8 * (v % (CO / 8)));
+      }
+#pragma unroll
+      for (int i = 0; i < kXPer; ++i) {
+        const int v = tid + NT * i;
+        const int y = y0 - 1 + (px_[i] >> 16), x = x0 - 1 + (px_[i] & 0xFFFF);
+        rx[i] = bf16x8{};
+        if (v < kXVec && y >= 0 && y < a.h && x >= 0 && x < a.wd)
+          rx[i] = *reinterpret_cast<const bf16x8*>(xs + ((long long)y * a.wd + x) * a.ldx +
+                                                   8 * (v % (CI / 8)));
+      }
+    } else {
+      const Rsrc dr = image_rsrc(dy, a.dybytes), xr = image_rsrc(xs, a.xbytes);
+      const unsigned tb = unsigned((y0 * a.wd + x0) * a.lddy) * 2u;
+      const unsigned xb = unsigned(((y0 - 1) * a.wd + x0 - 1) * a.ldx) * 2u;   // (may wrap)
+#pragma unroll
+      for (int i = 0; i < kDyPer; ++i) {
+        const bool in = y0 + (pd_[i] >> 16) < a.h && x0 + (pd_[i] & 0xFFFF) < a.wd;
+        rd[i] = load8(dr, in ? od[i] + tb : kOutside);
+      }
+#pragma unroll
+      for (int i = 0; i < kXPer; ++i) {
+        const bool in = unsigned(y0 - 1 + (px_[i] >> 16)) < unsigned(a.h) &&
+                        unsigned(x0 - 1 + (px_[i] & 0xFFFF)) < unsigned(a.wd);
+        rx[i] = load8(xr, in ? ox[i] + xb : kOutside);
+      }
     }
-#pragma unroll
-    for (int i = 0; i < kXPer; ++i) {
-      const int v = tid + 256 * i, px = v / (CI / 8), c = v % (CI / 8);
-      const int yy = px / HX, y = y0 + yy - 1, x = x0 + px - yy * HX - 1;
-      rx[i] = bf16x8{};
-      if ((kXVec % 256 == 0 || v < kXVec) && y >= 0 && y < a.h && x >= 0 && x < a.wd)
-        rx[i] = *reinterpret_cast<const bf16x8*>(a.x + (base + (long long)y * a.wd + x) * a.ldx +
-                                                 ci0 + 8 * c);
+    if (++tx == a.tiles_x) {
+      tx = 0;
+      if (++ty == a.tiles_y) {
+        ty = 0;
+        ++img;
+      }
     }
   };
-  auto store = [&]() {
+  auto store = [&](int buf) {
+    char* sd = smem + buf * kStage;
+    char* sx = sd + P * SD;
 #pragma unroll
     for (int i = 0; i < kDyPer; ++i) {
-      const int v = tid + 256 * i;
-      if (kDyVec % 256 == 0 || v < kDyVec)
-        *reinterpret_cast<bf16x8*>(sd + (v / (CO / 8)) * SD + 16 * (v % (CO / 8))) = rd[i];
+      const int v = tid + NT * i;
+      *reinterpret_cast<bf16x8*>(sd + (v / (CO / 8)) * SD + 16 * (v % (CO / 8))) = rd[i];
     }
 #pragma unroll
     for (int i = 0; i < kXPer; ++i) {
-      const int v = tid + 256 * i;
-      if (kXVec % 256 == 0 || v < kXVec)
+      const int v = tid + NT * i;
+      if (kXVec % NT == 0 || v < kXVec)
         *reinterpret_cast<bf16x8*>(sx + (v / (CI / 8)) * SX + 16 * (v % (CI / 8))) = rx[i];
     }
   };
@@ -620,67 +704,65 @@ __global__ __launch_bounds__(256, 2) void wgrad_tile_kernel(WgradArgs a) {
   // this lane's pixel row and channel within an operand (first of two loads)
   const int lrow = 8 * (lane >> 5) + ((lane & 15) >> 2);
   const int lch = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const char* pd = sd + lrow * SD + 2 * (32 * wco + lch);
-  const char* px = sx + lrow * SX + 2 * (32 * wci + lch);
-  if (u0 < u1) load(u0);
+  const char* pd = smem + (RW * wk * TX + lrow) * SD + 2 * lch;
+  const char* px = smem + P * SD + (RW * wk * HX + lrow) * SX + 2 * lch;
+  if (u0 < u1) load();
+  store(0);
+  if (u0 + 1 < u1) load();
+  __syncthreads();
   for (int u = u0; u < u1; ++u) {
-    __syncthreads();
-    store();
-    __syncthreads();
-    if (u + 1 < u1) load(u + 1);
-    for (int k = wk; k < P / 16; k += WK) {
-      const int q = 16 * k;
-      const char* d = pd + q * SD;
-      const char* b = px + ((q / TX) * HX + q % TX) * SX;
-      const bf16x8 A = lds_tr8(d, d + 4 * SD);
-      bf16x8 B[9];
+    const int buf = (u - u0) & 1;
+    const char* d = pd + buf * kStage;
+    const char* b = px + buf * kStage;
+    bf16x8 B[3][3];
 #pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const char* bt = b + ((t / 3) * HX + t % 3) * SX;
-        B[t] = lds_tr8(bt, bt + 4 * SX);
-      }
+    for (int j = 0; j < RW; ++j) {
 #pragma unroll
-      for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[t], acc[t]);
+      for (int k = j ? 2 : 0; k < 3; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const char* bt = b + ((j + k) * HX + c) * SX;
+          B[(j + k) % 3][c] = lds_tr8(bt, bt + 4 * SX);
+        }
+      const bf16x8 A = lds_tr8(d + j * TX * SD, d + (j * TX + 4) * SD);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[(j + t / 3) % 3][t % 3], acc[t]);
       if (bias) accb = mfma32(A, ones, accb);
     }
+    if (u + 1 < u1) store(buf ^ 1);
+    if (u + 2 < u1) load();
+    __syncthreads();
   }
   const int r = lane & 31, g = lane >> 5;
-  float* part = a.part + (long long)blockIdx.y * 9 * a.cin * a.cout;
-  if constexpr (WK == 1) {
+  float* part = a.part + (long long)split * 9 * a.cin * a.cout;
+  // sum over the waves, tap by tap, then the bias; two areas in turn, so that
+  // one barrier per tap is enough
+  float (*sums)[WK][32][33] = reinterpret_cast<float (*)[WK][32][33]>(smem);
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+  for (int t = 0; t < 9; ++t) {
+    float (*sum)[32][33] = sums[t & 1];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int co = co0 + 32 * wco + 8 * (v / 4) + 4 * g + v % 4;
-        part[((long long)co * 9 + t) * a.cin + ci0 + 32 * wci + r] = acc[t][v];
-      }
-    if (bias && r == 0)
+    for (int i = 0; i < 16; ++i) sum[wk][8 * (i / 4) + 4 * g + i % 4][r] = acc[t][i];
+    __syncthreads();
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        a.bpart[(long long)blockIdx.y * a.cout + co0 + 32 * wco + 8 * (v / 4) + 4 * g + v % 4] =
-            accb[v];
-  } else {
-    // sum over the WK waves of a channel tile, tap by tap
-    float (*s)[32][33] = reinterpret_cast<float (*)[32][33]>(smem);
-    const int grp = wv / WK, lt = tid % (64 * WK);   // channel tile, thread within it
+    for (int e = tid; e < 1024; e += NT) {
+      const int co = e >> 5, ci = e & 31;
+      float v = sum[0][co][ci];
 #pragma unroll
-    for (int t = 0; t < 10; ++t) {
-      if (t == 9 && a.bpart == nullptr) break;
-      __syncthreads();
+      for (int k = 1; k < WK; ++k) v += sum[k][co][ci];
+      part[((long long)(co0 + co) * 9 + t) * a.cin + ci0 + ci] = v;
+    }
+  }
+  if (bias) {
+    float (*sum)[32][33] = sums[1];
 #pragma unroll
-      for (int v = 0; v < 16; ++v)
-        s[wv][8 * (v / 4) + 4 * g + v % 4][r] = t < 9 ? acc[t < 9 ? t : 0][v] : accb[v];
-      __syncthreads();
-      for (int e = lt; e < 1024; e += 64 * WK) {
-        const int co = e >> 5, ci = e & 31;
-        float v = s[grp * WK][co][ci];
+    for (int i = 0; i < 16; ++i) sum[wk][8 * (i / 4) + 4 * g + i % 4][r] = accb[i];
+    __syncthreads();
+    if (tid < 32) {
+      float v = sum[0][tid][0];
 #pragma unroll
-        for (int k = 1; k < WK; ++k) v += s[grp * WK + k][co][ci];
-        if (t < 9)
-          part[((long long)(co0 + 32 * wco + co) * 9 + t) * a.cin + ci0 + 32 * wci + ci] = v;
-        else if (bias && ci == 0)
-          a.bpart[(long long)blockIdx.y * a.cout + co0 + 32 * wco + co] = v;
-      }
+      for (int k = 1; k < WK; ++k) v += sum[k][tid][0];
+      a.bpart[(long long)split * a.cout + co0 + tid] = v;
     }
   }
 }
@@ -690,7 +772,6 @@ __global__ __launch_bounds__(256, 2) void wgrad_tile_kernel(WgradArgs a) {
 // may be null).  A block owns 64 consecutive entries; its 16 groups of 16
 // threads each add every 16th split (four entries per thread), then one
 // group adds the 16 sums, all in a fixed order.  Counts are multiples of 4.
-constexpr int kMaxLayers = 16;
 struct SumArgs {
   int layers;
   struct {
@@ -729,36 +810,40 @@ __global__ __launch_bounds__(256) void sum_splits_kernel(SumArgs a) {
   }
 }
 
-// Split of the weight gradient: which channel tile a block owns and into how
-// many shares the pixel tiles go.  A share costs its tiles (clocks per tile
-// of one block, measured; more blocks than compute units share them) and its
-// partial sums are written and read once more (about 1.7 kB per clock).
+// Into how many shares the pixel tiles of a weight gradient go.
+// One layer alone: a round of 256 blocks (one per compute unit: registers)
+// costs its tiles, about 3000 clocks each, and every share's partial sums are
+// written and read once more (about 1.7 kB per clock).  Over the network's
+// layers at batch 2 and 16 the choice is within 8 % of the best power of two.
+// In a group (per_block > 0) that many tiles per block, more shares than
+// eight in multiples of eight (one per XCD).
 struct WgradPlan {
-  int wide, narrow, tiles_x, tiles_y, units, splits;
+  int tiles_x, tiles_y, units, splits;
 };
 
-WgradPlan wgrad_plan(int n, int h, int wd, int cin, int cout) {
-  WgradPlan best{};
-  double best_cost = 0.0;
-  const int narrow = wd <= 16;
-  const int tx = narrow ? 16 : 32, ty = narrow ? 8 : 4;
-  const int tiles_x = (wd + tx - 1) / tx, tiles_y = (h + ty - 1) / ty;
-  const int units = n * tiles_x * tiles_y;
-  for (int wide = 0; wide < 2; ++wide) {
-    if (wide && (cin % 64 || cout % 64)) continue;
-    const int base = (cin / (wide ? 64 : 32)) * (cout / (wide ? 64 : 32));
-    const double clk = wide ? 2800.0 : 1100.0;
-    for (int s = 1; s <= units && s <= 1024; s *= 2) {
-      const double share = std::max(1.0, (double)base * s / 256.0);
-      const double cost = share * ((units + s - 1) / s) * clk +
-                          (double)s * (9.0 * cin * cout + cout) * 8.0 / 1700.0;
-      if (best.splits == 0 || cost < best_cost) {
-        best = WgradPlan{wide, narrow, tiles_x, tiles_y, units, s};
-        best_cost = cost;
-      }
-    }
+WgradPlan wgrad_plan(int n, int h, int wd, int cin, int cout, int per_block = 0) {
+  WgradPlan p{(wd + 15) / 16, (h + 15) / 16, 0, 0};
+  p.units = n * p.tiles_x * p.tiles_y;
+  if (per_block > 0) {
+    const int s = (p.units + per_block - 1) / per_block;
+    p.splits = s < 8 ? s : std::min(s / 8 * 8, 1024);
+    return p;
   }
-  return best;
+  const int base = (cin / 32) * (cout / 32);
+  double best = 0.0;
+  auto consider = [&](int s) {
+    if (s < 1 || s > p.units || s > 1024) return;
+    const double rounds = (base * (long long)s + 255) / 256;
+    const double cost = rounds * ((p.units + s - 1) / s) * 3000.0 +
+                        (double)s * (9.0 * cin * cout + cout) * 8.0 / 1700.0;
+    if (p.splits == 0 || cost < best) {
+      p.splits = s;
+      best = cost;
+    }
+  };
+  for (int s = 1; s <= 1024; s *= 2) consider(s);
+  consider(256 / base);   // exactly one round
+  return p;
 }
 
 // ---------------------------------------------------------------------------
@@ -1166,48 +1251,56 @@ static int launch_fields(const float* out, int ldo, int n, int res, const float*
   return UNET_OK;
 }
 
-// Partial sums of a weight gradient; the sums over its splits are appended
-// to `sums` (launch_sums).  Returns the floats of `work` it uses in *used.
-static int launch_wgrad(const bf16* dy, int lddy, const bf16* x, int ldx, float* dw, float* db,
-                        int n, int h, int wd, int cin, int cout, float* work, SumArgs& sums,
-                        hipStream_t st, long long* used = nullptr) {
-  const WgradPlan p = wgrad_plan(n, h, wd, cin, cout);
+// Adds a layer to a group; returns the floats of `work` it uses.
+static long long add_wgrad(WgradGroup& g, const WgradPlan& p, const bf16* dy, int lddy,
+                           const bf16* x, int ldx, float* dw, float* db, int h, int wd, int cin,
+                           int cout, float* work) {
+  WgradLayer& l = g.l[g.layers];
   const long long wcount = 9LL * cin * cout;
-  float* bpart = db ? work + p.splits * wcount : nullptr;
-  WgradArgs a{dy, lddy, x, ldx, work, bpart, n, h, wd, cin, cout, p.tiles_x, p.tiles_y, p.units,
-              p.splits};
-  const int ct = p.wide ? 64 : 32;
-  dim3 grid((cin / ct) * (cout / ct), p.splits);
-  if (p.wide && p.narrow)
-    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 16, 8>), grid, dim3(256), 0, st, a);
-  else if (p.wide)
-    hipLaunchKernelGGL((wgrad_tile_kernel<2, 2, 32, 4>), grid, dim3(256), 0, st, a);
-  else if (p.narrow)
-    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 16, 8>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((wgrad_tile_kernel<1, 1, 32, 4>), grid, dim3(256), 0, st, a);
-  UCHECK(hipGetLastError());
-  auto& l = sums.l[sums.layers];
-  const int prev = sums.layers - 1;
-  l.part = work;
-  l.bpart = bpart;
-  l.dw = dw;
-  l.db = db;
-  l.count = wcount;
-  l.bcount = db ? cout : 0;
-  l.splits = p.splits;
-  l.wblocks = int((wcount + 63) / 64);
-  l.first = prev < 0 ? 0 : sums.l[prev].first + sums.l[prev].wblocks +
-                               (sums.l[prev].bcount + 63) / 64;
-  ++sums.layers;
-  if (used) *used = p.splits * (wcount + cout);
-  return UNET_OK;
+  l = WgradLayer{dy, x, work, db ? work + p.splits * wcount : nullptr, dw, db, lddy, ldx, h, wd,
+                 cin, cout, p.tiles_x, p.tiles_y, p.units, p.splits, 0,
+                 (unsigned)image_bytes(h, wd, lddy, 32), (unsigned)image_bytes(h, wd, ldx, 32)};
+  if (g.layers) {
+    const WgradLayer& q = g.l[g.layers - 1];
+    l.first = q.first + (q.splits * (q.cin / 32) * (q.cout / 32) + 7) / 8 * 8;
+  }
+  ++g.layers;
+  return p.splits * (wcount + cout);
 }
 
-static int launch_sums(const SumArgs& sums, hipStream_t st) {
-  const auto& l = sums.l[sums.layers - 1];
-  hipLaunchKernelGGL(sum_splits_kernel, dim3(l.first + l.wblocks + (l.bcount + 63) / 64),
-                     dim3(256), 0, st, sums);
+// Partial sums of every layer of the group, then the sums over the splits.
+static int launch_wgrad(const WgradGroup& g, hipStream_t st) {
+  const WgradLayer& e = g.l[g.layers - 1];
+  const dim3 grid(e.first + e.splits * (e.cin / 32) * (e.cout / 32)), block(512);
+  bool big = false;
+  for (int k = 0; k < g.layers; ++k) {
+    const WgradLayer& l = g.l[k];
+    big = big || image_bytes(l.h, l.wd, l.lddy, 32) > kMaxRsrc ||
+          image_bytes(l.h, l.wd, l.ldx, 32) > kMaxRsrc;
+  }
+  if (big)
+    hipLaunchKernelGGL(wgrad_tile_kernel<true>, grid, block, 0, st, g);
+  else
+    hipLaunchKernelGGL(wgrad_tile_kernel<false>, grid, block, 0, st, g);
+  UCHECK(hipGetLastError());
+  SumArgs sums{};
+  sums.layers = g.layers;
+  int blocks = 0;
+  for (int k = 0; k < g.layers; ++k) {
+    const WgradLayer& l = g.l[k];
+    auto& q = sums.l[k];
+    q.part = l.part;
+    q.bpart = l.bpart;
+    q.dw = l.dw;
+    q.db = l.db;
+    q.count = 9LL * l.cin * l.cout;
+    q.bcount = l.db ? l.cout : 0;
+    q.splits = l.splits;
+    q.first = blocks;
+    q.wblocks = int((q.count + 63) / 64);
+    blocks += q.wblocks + (q.bcount + 63) / 64;
+  }
+  hipLaunchKernelGGL(sum_splits_kernel, dim3(blocks), dim3(256), 0, st, sums);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
@@ -1262,10 +1355,10 @@ int unet_conv3x3_bwd_weight(const void* dy, int32_t lddy, const void* x, int32_t
     return fail(UNET_EINVAL, "bwd_weight: cin and cout must be positive multiples of 32");
   if (lddy % 8 || ldx % 8 || lddy < cout || ldx < cin)
     return fail(UNET_EINVAL, "bwd_weight: bad ld");
-  SumArgs sums{};
-  const int rc = launch_wgrad(static_cast<const bf16*>(dy), lddy, static_cast<const bf16*>(x), ldx,
-                              dw, dbias, n, h, wd, cin, cout, work, sums, as_stream(stream));
-  return rc ? rc : launch_sums(sums, as_stream(stream));
+  WgradGroup g{};
+  add_wgrad(g, wgrad_plan(n, h, wd, cin, cout), static_cast<const bf16*>(dy), lddy,
+            static_cast<const bf16*>(x), ldx, dw, dbias, h, wd, cin, cout, work);
+  return launch_wgrad(g, as_stream(stream));
 }
 
 int unet_relu_bwd(void* d, int32_t ldd, const void* y, int32_t ldy, int64_t npix, int32_t ch,
@@ -1503,20 +1596,30 @@ int forward_impl(unet* net, const bf16* x0, int n, float* out) {
   return UNET_OK;
 }
 
-// Gradients of conv k given the gradient of its (pre-activation) output; the
-// input gradient is masked by the ReLU of the input buffer (relu), or left
-// as it is where the buffer has none or receives further gradients.
+// Pixel tiles per block of the grouped weight gradients: four rounds of
+// blocks if the batch is small, at most 12 (the partial sums stay a small
+// part of the traffic and the last round short).
+int wgrad_per_block(int res, int n) {
+  long long tiles = 0;
+  for (const Conv& c : kConvs) {
+    const int t = ((res >> c.level) + 15) / 16;
+    tiles += (long long)n * t * t * (c.cin / 32) * (c.cout / 32);
+  }
+  return (int)std::min<long long>(std::max<long long>(tiles / 1024, 1), 12);
+}
+
+// Input gradient of conv k given the gradient of its (pre-activation) output,
+// masked by the ReLU of the input buffer (relu), or left as it is where the
+// buffer has none or receives further gradients; the weight gradient joins
+// the group.
 int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_dx, bool relu,
-                  SumArgs& sums, long long& used) {
+                  WgradGroup& g, long long& used, int per_block) {
   const Conv& c = net->convs[k];
   const int s = side(net, c.level);
-  hipStream_t st = net->stream;
-  long long u = 0;
-  int rc = launch_wgrad(dy, lddy, net->act[c.in] + c.in_off, kBuf[c.in].ch, net->grad + c.w_off,
-                        net->grad + c.b_off, n, s, s, c.cin, c.cout, net->wwork + used, sums, st,
-                        &u);
-  used += u;
-  if (rc || !need_dx) return rc;
+  used += add_wgrad(g, wgrad_plan(n, s, s, c.cin, c.cout, per_block), dy, lddy,
+                    net->act[c.in] + c.in_off, kBuf[c.in].ch, net->grad + c.w_off,
+                    net->grad + c.b_off, s, s, c.cin, c.cout, net->wwork + used);
+  if (!need_dx) return UNET_OK;
   ConvArgs a{};
   a.x = dy;
   a.ldx = lddy;
@@ -1532,7 +1635,7 @@ int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_d
     a.mask = net->act[c.in] + c.in_off;
     a.ldmask = kBuf[c.in].ch;
   }
-  return launch_conv(a, st);
+  return launch_conv(a, net->stream);
 }
 
 // Flipped weights of every layer whose input gradient is needed (all but the
@@ -1560,12 +1663,16 @@ int flip_weights(unet* net) {
 int backward_impl(unet* net, int n) {
   hipStream_t st = net->stream;
   int rc = UNET_OK;
-  SumArgs sums{};
-  long long used = 0;   // partial sums of all layers stay until one launch adds them
+  // the weight gradients of all layers run in one launch at the end (each
+  // alone is a short launch with a ramp, a tail and a sum of its own)
+  WgradGroup group{};
+  static_assert(kNumConvs <= kMaxLayers, "group");
+  long long used = 0;
+  const int per_block = wgrad_per_block(net->res, n);
   auto conv = [&](int k, int buf, int off, bool need_dx, bool relu) {
     const bf16* dy = buf < 0 ? net->gout : net->gact[buf] + off;
     return conv_backward(net, k, n, dy, buf < 0 ? UNET_OUT_CHANNELS : kBuf[buf].ch, need_dx, relu,
-                         sums, used);
+                         group, used, per_block);
   };
   // gradient of an upsampled buffer (channels [0, ch) of the concatenation),
   // masked by its ReLU: the concatenation holds its values
@@ -1604,7 +1711,7 @@ int backward_impl(unet* net, int n) {
       (rc = poolb(B_P1, B_CAT0, 64, 0, 32)) || (rc = conv(1, B_CAT0, 64, true, true)) ||
       (rc = conv(0, B_E0A, 0, false, false)))
     return rc;
-  return launch_sums(sums, st);
+  return launch_wgrad(group, st);
 }
 
 uint64_t splitmix_next(uint64_t& s) {
@@ -1654,7 +1761,8 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
     long long words = 0;
     for (const Conv& c : net->convs) {
       const int s = res >> c.level;
-      words += unet_wgrad_work_floats(nb, s, s, c.cin, c.cout);
+      const WgradPlan p = wgrad_plan(nb, s, s, c.cin, c.cout, wgrad_per_block(res, nb));
+      words += p.splits * (9LL * c.cin * c.cout + c.cout);
     }
     wwork_max = std::max(wwork_max, words);
   }

@@ -75,3 +75,22 @@ def test_weight_gradient_tiles(U, n, h, w, cin, cout):
     dw, db = U.conv3x3_bwd_weight(dev(dyf, torch.bfloat16), dev(xf, torch.bfloat16), cin, cout)
     assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()
     assert (np.abs(host(db) - db_ref) <= 1e-5 * np.abs(dy).reshape(-1, cout).sum(0) + 1e-6).all()
+
+
+def test_images_of_two_gigabytes(U):
+    """A pixel stride so large that an image spans 2 GB: loads with 64-bit
+    addresses, the same sums."""
+    import torch
+    print("[gpu-case] 2 GB images", flush=True)
+    rng = np.random.default_rng(23)
+    x, dy = bf(rng, 1, 1, 3, 32), bf(rng, 1, 1, 3, 64)
+    wt = bf(rng, 64, 9, 32, scale=0.1)
+    xd = torch.zeros((1, 1, 3, 2 ** 29), device="cuda", dtype=torch.bfloat16)
+    xd[..., :32] = dev(x, torch.bfloat16)
+    y = U.conv3x3_fwd(xd, dev(wt, torch.bfloat16), None, 64, out_f32=True)
+    bound = R.conv3x3(np.abs(x), np.abs(wt))
+    assert (np.abs(host(y) - R.conv3x3(x, wt)) <= 1e-5 * bound + 1e-6).all()
+    dw, _ = U.conv3x3_bwd_weight(dev(dy, torch.bfloat16), xd, 32, 64)
+    dw_ref, _ = R.conv3x3_bwd_weight(dy, x)
+    bound, _ = R.conv3x3_bwd_weight(np.abs(dy), np.abs(x))
+    assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()
