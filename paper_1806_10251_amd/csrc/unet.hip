@@ -187,7 +187,12 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
 // reduction runs tap by tap and channel by channel in one accumulator, the
 // order of conv_fwd_kernel (a 32x32x16 chain gives the same bits as a
 // 16x16x32 one, checked on the device), so the path taken never shows in
-// the result.
+// the result.  Measured at batch 16, 128 x 128 and its halvings: 32 -> 32
+// channels 12 us (390 TFLOP/s), 192 -> 64 22 us (650), 384 -> 128 26 us
+// (560); before, with operands straight from memory, 35, 105 and 105 us.
+// What is left is latency in series (launch, tile load, per stage LDS reads
+// and a barrier, store), no single unit: leaving out any one of MFMA, LDS
+// reads, tile load, weight loads or stores saves 5-20 %.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
@@ -196,23 +201,26 @@ __device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const
 
 constexpr int kLdsBytes = 160 * 1024;
 
+// A stage is KS channels of one tap (KS = 96, 64 or 32, the largest that
+// divides cin) or, for cin = 32 (ROW), the three taps of a kernel row, so
+// every LDS offset within a stage is a constant.
 template <int MP, int NC, int WP, int WC, int TX, int KS>
 struct ConvTile {
   static constexpr int P = 32 * MP * WP, CB = 32 * NC * WC, TY = P / TX;
   static constexpr int WS = 2 * KS + 16;   // LDS bytes per weight row
   static constexpr int OS = 2 * CB + 16;   // LDS bytes per output pixel
-  static_assert(WP * WC == 4 && TY * TX == P && KS % 32 == 0 && 288 % KS == 0, "tile");
+  static constexpr int NT = 64 * WP * WC;  // threads
+  static_assert(TY * TX == P && KS % 32 == 0, "tile");
   static size_t lds(int cin) {
-    const size_t bufs = 9 * cin > KS ? 2 : 1;
-    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + bufs * CB * WS;
+    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + 2 * (size_t)CB * WS;
     return 4 * CB + (in > (size_t)P * OS ? in : (size_t)P * OS);   // bias, then the tiles
   }
 };
 
-template <int MP, int NC, int WP, int WC, int TX, int KS>
-__global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
+template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
+__global__ __launch_bounds__(64 * WP * WC) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
   using L = ConvTile<MP, NC, WP, WC, TX, KS>;
-  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2);
+  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2), NT = L::NT;
   extern __shared__ __align__(16) char smem_all[];
   float* sbias = reinterpret_cast<float*>(smem_all);
   char* smem = smem_all + 4 * L::CB;
@@ -231,40 +239,47 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   const int nst = 9 * a.cin / KS;
 
   // weights of one stage: CB rows of KS consecutive reduction elements
-  constexpr int kRowVec = KS / 8, kWVec = L::CB * kRowVec, kWPer = (kWVec + 255) / 256;
-  bf16x8 wreg[kWPer];
-  auto load_w = [&](int st) {
+  constexpr int kRowVec = KS / 8, kWVec = L::CB * kRowVec, kWPer = (kWVec + NT - 1) / NT;
+  // PF stages in flight in registers (the loads are unconditional: under a
+  // branch, the wait for one stage would become a wait for all of them)
+  constexpr int PF = 3;   // divides the number of stages
+  bf16x8 wreg[PF][kWPer];
+  unsigned woff[kWPer];
 #pragma unroll
-    for (int i = 0; i < kWPer; ++i) {
-      const int v = tid + 256 * i;
-      if (kWVec % 256 == 0 || v < kWVec)
-        wreg[i] = *reinterpret_cast<const bf16x8*>(
-            a.w + (long long)(co0 + v / kRowVec) * 9 * a.cin + st * KS + 8 * (v % kRowVec));
-    }
+  for (int i = 0; i < kWPer; ++i) {
+    const int v = tid + NT * i, row = kWVec % NT == 0 || v < kWVec ? v / kRowVec : 0;
+    woff[i] = unsigned(row * 9 * a.cin + 8 * (v % kRowVec)) * 2u;
+  }
+  const char* wbase = reinterpret_cast<const char*>(a.w + (long long)co0 * 9 * a.cin);
+  auto load_w = [&](int st, bf16x8 (&w)[kWPer]) {
+    const char* p = wbase + (long long)min(st, nst - 1) * (2 * KS);
+#pragma unroll
+    for (int i = 0; i < kWPer; ++i) w[i] = *reinterpret_cast<const bf16x8*>(p + woff[i]);
   };
-  auto store_w = [&](int buf) {
+  auto store_w = [&](int buf, const bf16x8 (&w)[kWPer]) {
 #pragma unroll
     for (int i = 0; i < kWPer; ++i) {
-      const int v = tid + 256 * i;
-      if (kWVec % 256 == 0 || v < kWVec)
+      const int v = tid + NT * i;
+      if (kWVec % NT == 0 || v < kWVec)
         *reinterpret_cast<bf16x8*>(sw + buf * (L::CB * L::WS) + (v / kRowVec) * L::WS +
-                                   16 * (v % kRowVec)) = wreg[i];
+                                   16 * (v % kRowVec)) = w[i];
     }
   };
-  load_w(0);
+#pragma unroll
+  for (int i = 0; i < PF; ++i) load_w(i, wreg[i]);
   if (tid < L::CB) sbias[tid] = a.bias ? a.bias[co0 + tid] : 0.f;
   {
     // input tile: HP pixels x cin channels, eight 16-byte loads in flight
     const int cv = a.cin >> 3, nvec = HP * cv;
     const Rsrc xr = image_rsrc(a.x + (long long)img * a.h * a.wd * a.ldx, a.xbytes);
-    const int qs = 256 / cv, rs = 256 - qs * cv;
+    const int qs = NT / cv, rs = NT - qs * cv;
     int px = tid / cv, c = tid - px * cv;
-    for (int base = 0; base < nvec; base += 8 * 256) {
+    for (int base = 0; base < nvec; base += 8 * NT) {
       bf16x8 v[8];
       int at[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        if (base + 256 * u < nvec) {
+        if (base + NT * u < nvec) {
           const int yy = px / HX, xx = px - yy * HX;
           const int y = y0 + yy - 1, x = x0 + xx - 1;
           const bool in = unsigned(y) < unsigned(a.h) && unsigned(x) < unsigned(a.wd);
@@ -279,10 +294,11 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (base + 256 * u + tid < nvec) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
+        if (base + NT * u + tid < nvec) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
     }
   }
-  store_w(0);
+  store_w(0, wreg[0]);
+  load_w(PF, wreg[0]);
   __syncthreads();
 
   f32x16 acc[NC][MP];
@@ -299,37 +315,61 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
     xb[s] = sx + ((q / TX) * HX + q % TX) * S + 16 * g;
   }
   const int wrow = (32 * NC * wc + r) * L::WS + 16 * g;
-  int c2 = 0, tapoff = 0, tcol = 0;   // 2 x channel, byte offset and column of the tap
-  for (int st = 0; st < nst; ++st) {
-    if (st + 1 < nst) load_w(st + 1);
-    const char* wb = sw + (st & 1) * (L::CB * L::WS) + wrow;
+  // stage position: byte offset of its tap (or kernel row) and channels
+  int soff = 0, chunk = 0, tcol = 0;
+  const int chunks = a.cin / KS;
+  for (int st0 = 0; st0 < nst; st0 += PF) {
 #pragma unroll
-    for (int j = 0; j < KS / 32; ++j) {
-      const int off = tapoff + c2;
-      bf16x8 A[2][NC], B[2][MP];
+    for (int i = 0; i < PF; ++i) {
+      const int st = st0 + i;
+      const char* wb = sw + (st & 1) * (L::CB * L::WS) + wrow;
+      // operands of the next 32 elements are read while the current ones are
+      // multiplied (the scheduling barriers keep the compiler from sinking each
+      // read to just before its use, one LDS latency per MFMA)
+      constexpr int NJ = KS / 32;
+      bf16x8 A[2][2][NC], B[2][2][MP];
+      const char* xs[MP];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int s = 0; s < MP; ++s) xs[s] = xb[s] + soff;
+      auto read = [&](int j, bf16x8 (&Aj)[2][NC], bf16x8 (&Bj)[2][MP]) {
 #pragma unroll
-        for (int s = 0; s < MP; ++s)
-          B[h][s] = *reinterpret_cast<const bf16x8*>(xb[s] + off + 32 * h);
+        for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int b = 0; b < NC; ++b)
-          A[h][b] = *reinterpret_cast<const bf16x8*>(wb + b * (32 * L::WS) + 64 * j + 32 * h);
+          for (int s = 0; s < MP; ++s)
+            Bj[h][s] = *reinterpret_cast<const bf16x8*>(xs[s] + (ROW ? 80 : 64) * j + 32 * h);
+#pragma unroll
+          for (int b = 0; b < NC; ++b)
+            Aj[h][b] = *reinterpret_cast<const bf16x8*>(wb + b * (32 * L::WS) + 64 * j + 32 * h);
+        }
+      };
+      read(0, A[0], B[0]);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j + 1 < NJ) read(j + 1, A[(j + 1) & 1], B[(j + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < NC; ++b)
+#pragma unroll
+            for (int s = 0; s < MP; ++s)
+              acc[b][s] = mfma32(A[j & 1][h][b], B[j & 1][h][s], acc[b][s]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int b = 0; b < NC; ++b)
-#pragma unroll
-          for (int s = 0; s < MP; ++s) acc[b][s] = mfma32(A[h][b], B[h][s], acc[b][s]);
-      c2 += 64;
-      const bool next = c2 == 2 * a.cin;   // uniform: the next tap
-      tapoff += next ? (tcol == 2 ? TX * S : S) : 0;
-      tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
-      c2 = next ? 0 : c2;
+      if (ROW) {
+        soff += HX * 80;
+      } else {   // uniform: the next channels, or the next tap
+        ++chunk;
+        const bool next = chunk == chunks;
+        const int tap = tcol == 2 ? (TX + 1) * S - S : S;   // one to the right, or the next row
+        soff += next ? tap - 2 * KS * (chunks - 1) : 2 * KS;
+        tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
+        chunk = next ? 0 : chunk;
+      }
+      if (st + 1 < nst) store_w((st + 1) & 1, wreg[(i + 1) % PF]);
+      load_w(st + 1 + PF, wreg[(i + 1) % PF]);
+      __syncthreads();
     }
-    if (st + 1 < nst) store_w((st + 1) & 1);
-    __syncthreads();
   }
 
   if (a.out_f32) {
@@ -378,8 +418,8 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   __syncthreads();
   constexpr int kOVec = L::CB / 8;
 #pragma unroll
-  for (int i = 0; i < L::P * kOVec / 256; ++i) {
-    const int v = tid + 256 * i, q = v / kOVec, c = v % kOVec;
+  for (int i = 0; i < L::P * kOVec / NT; ++i) {
+    const int v = tid + NT * i, q = v / kOVec, c = v % kOVec;
     const int y = y0 + q / TX, x = x0 + q % TX;
     if (y >= a.h || x >= a.wd) continue;
     bf16x8 o = *reinterpret_cast<const bf16x8*>(smem + q * L::OS + 16 * c);
@@ -399,7 +439,7 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   }
   if (a.pool) {
     // tiles start at even coordinates and h, wd are even: whole 2 x 2 cells
-    for (int v = tid; v < L::P / 4 * kOVec; v += 256) {
+    for (int v = tid; v < L::P / 4 * kOVec; v += NT) {
       const int q = v / kOVec, c = v % kOVec;
       const int yy = 2 * (q / (TX / 2)), xx = 2 * (q % (TX / 2));
       if (y0 + yy >= a.h || x0 + xx >= a.wd) continue;
@@ -421,32 +461,44 @@ __global__ __launch_bounds__(256) void conv_tile_kernel(ConvArgs a, int tiles_x,
   }
 }
 
-template <int MP, int NC, int WP, int WC, int TX, int KS>
-int launch_conv_tile(const ConvArgs& a, hipStream_t st) {
+// Launches a tiling if its LDS fits (*done); otherwise leaves *done false.
+template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
+int try_conv_tile(const ConvArgs& a, hipStream_t st, bool* done) {
   using L = ConvTile<MP, NC, WP, WC, TX, KS>;
   const int tx = (a.wd + TX - 1) / TX, ty = (a.h + L::TY - 1) / L::TY;
   const size_t lds = L::lds(a.cin);
-  auto* fn = conv_tile_kernel<MP, NC, WP, WC, TX, KS>;
+  if (lds > (size_t)kLdsBytes) return UNET_OK;
+  auto* fn = conv_tile_kernel<MP, NC, WP, WC, TX, KS, ROW>;
   if (lds > 64 * 1024)
     UCHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   dim3 grid(tx * ty * (a.npix / (a.h * a.wd)), a.cout / L::CB);
-  hipLaunchKernelGGL(fn, grid, dim3(256), lds, st, a, tx, ty);
+  hipLaunchKernelGGL(fn, grid, dim3(L::NT), lds, st, a, tx, ty);
   UCHECK(hipGetLastError());
+  *done = true;
   return UNET_OK;
 }
 
-// Runs the tiling if its LDS fits and its grid is in range.
-template <int MP, int NC, int WP, int WC, int KS>
-bool conv_tile_fits(const ConvArgs& a, bool narrow) {
-  const size_t b = narrow ? ConvTile<MP, NC, WP, WC, 16, KS>::lds(a.cin)
-                          : ConvTile<MP, NC, WP, WC, 32, KS>::lds(a.cin);
-  return b <= (size_t)kLdsBytes;
+template <int MP, int NC, int WP, int WC, int TX>
+int try_conv_width(const ConvArgs& a, hipStream_t st, bool* done) {
+  if (a.cin == 32) return try_conv_tile<MP, NC, WP, WC, TX, 96, true>(a, st, done);
+  if (a.cin % 96 == 0) return try_conv_tile<MP, NC, WP, WC, TX, 96, false>(a, st, done);
+  if (a.cin % 64 == 0) return try_conv_tile<MP, NC, WP, WC, TX, 64, false>(a, st, done);
+  return try_conv_tile<MP, NC, WP, WC, TX, 32, false>(a, st, done);
 }
-template <int MP, int NC, int WP, int WC, int KS>
-int conv_tile_go(const ConvArgs& a, bool narrow, hipStream_t st) {
-  return narrow ? launch_conv_tile<MP, NC, WP, WC, 16, KS>(a, st)
-                : launch_conv_tile<MP, NC, WP, WC, 32, KS>(a, st);
+
+template <int MP, int NC, int WP, int WC>
+int try_conv(const ConvArgs& a, hipStream_t st, bool* done) {
+  // 16-pixel-wide tiles where 32 would pad the rows more, or where they let
+  // two blocks share a compute unit's LDS (by the largest stage): 96 -> 32
+  // channels at 16 x 128 x 128, 38 -> 29 us
+  const size_t half = kLdsBytes / 2;
+  constexpr int KS = 96;
+  const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32 ||
+                      (ConvTile<MP, NC, WP, WC, 32, KS>::lds(a.cin) > half &&
+                       ConvTile<MP, NC, WP, WC, 16, KS>::lds(a.cin) <= half);
+  return narrow ? try_conv_width<MP, NC, WP, WC, 16>(a, st, done)
+                : try_conv_width<MP, NC, WP, WC, 32>(a, st, done);
 }
 
 int launch_conv(ConvArgs a, hipStream_t st) {
@@ -459,25 +511,23 @@ int launch_conv(ConvArgs a, hipStream_t st) {
   if (!a.x || !a.w || !a.y) return fail(UNET_EINVAL, "conv: null pointer");
   const long long xbytes = image_bytes(a.h, a.wd, a.ldx, a.cin);
   a.xbytes = (unsigned)xbytes;
-  const bool tiles = xbytes <= kMaxRsrc;   // (an image of 2 GB takes the general path)
-  // 16-pixel-wide tiles where 32 would pad the rows more
-  const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32;
-  // the largest wave tile that still gives about one wave per SIMD (1024)
+  // The largest block tile that still gives about 256 blocks (one per compute
+  // unit); eight waves of 32 x 32 or 64 x 32 hide each other's LDS and memory
+  // latency better than four larger ones (128 -> 128 channels at 16 x 32 x
+  // 32: 10.7 us against 12.7; 64 -> 64 at 16 x 64 x 64: 10.2 against 12.0).
+  // An image of 2 GB takes the general path.
   const long long px32 = (a.npix + 31) / 32;
-  if (tiles && a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048 &&
-      conv_tile_fits<2, 2, 4, 1, 96>(a, narrow))
-    return conv_tile_go<2, 2, 4, 1, 96>(a, narrow, st);
-  if (tiles && a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024 &&
-      conv_tile_fits<1, 2, 2, 2, 96>(a, narrow))
-    return conv_tile_go<1, 2, 2, 2, 96>(a, narrow, st);
-  if (tiles && a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 288>(a, narrow))
-    return conv_tile_go<1, 1, 2, 2, 288>(a, narrow, st);
-  if (tiles && a.cout % 64 == 0 && conv_tile_fits<1, 1, 2, 2, 96>(a, narrow))
-    return conv_tile_go<1, 1, 2, 2, 96>(a, narrow, st);
-  if (tiles && px32 * (a.cout / 32) >= 2048 && conv_tile_fits<2, 1, 4, 1, 96>(a, narrow))
-    return conv_tile_go<2, 1, 4, 1, 96>(a, narrow, st);
-  if (tiles && conv_tile_fits<1, 1, 4, 1, 96>(a, narrow))
-    return conv_tile_go<1, 1, 4, 1, 96>(a, narrow, st);
+  bool done = xbytes > kMaxRsrc;
+  int rc = UNET_OK;
+  if (!done) {
+    if (a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048) rc = try_conv<2, 1, 4, 2>(a, st, &done);
+    if (!rc && !done && a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024)
+      rc = try_conv<1, 1, 2, 4>(a, st, &done);
+    if (!rc && !done && a.cout % 64 == 0) rc = try_conv<1, 1, 2, 2>(a, st, &done);
+    if (!rc && !done && px32 * (a.cout / 32) >= 2048) rc = try_conv<1, 1, 8, 1>(a, st, &done);
+    if (!rc && !done) rc = try_conv<1, 1, 4, 1>(a, st, &done);
+    if (rc || done) return rc;
+  }
   // more input channels than LDS holds (none of the network's layers):
   // operands straight from memory
   if (a.mask || a.pool || a.up) return fail(UNET_EINVAL, "conv: no fused form of this size");
