@@ -32,8 +32,10 @@ HIPFLAGS = [
 # runs that differ only in their check cadence or driver stay bit-identical.
 LBM_FLAGS = ["-ffp-contract=on"]
 
-# Compiled once per storage type and flavour of the step (see its header).
+# Compiled once per storage type (and, the single step, per flavour; see their
+# headers).
 STEP_SRC = "lbm_step.hip"
+MULTI_SRC = "lbm_multi.hip"
 JOBS = max(1, min(16, os.cpu_count() or 1))
 
 
@@ -48,6 +50,9 @@ def build(verbose: bool = False) -> str:
                 for fl in range(3):
                     jobs.append((src, f"{name}.s{st}f{fl}.o",
                                  [f"-DLBM_STEP_STORAGE={st}", f"-DLBM_STEP_FLAVOR={fl}"]))
+        elif name == MULTI_SRC:
+            for st in range(4):
+                jobs.append((src, f"{name}.s{st}.o", [f"-DLBM_STEP_STORAGE={st}"]))
         else:
             jobs.append((src, name + ".o", []))
 

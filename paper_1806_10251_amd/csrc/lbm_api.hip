@@ -17,7 +17,7 @@
 #include "lbm_aux.h"
 #include "lbm_ctx.h"
 #include "lbm_host.h"
-#include "lbm_kernels.h"
+#include "lbm_multi.h"
 
 using namespace lbmk;
 using namespace lbmh;
@@ -115,13 +115,99 @@ int configure_tiles(lbm_ctx* c) {
 
 constexpr size_t kLastLevelCacheBytes = size_t(256) << 20;
 
-// Queue one step (flavor by its 1-based index), then swap lattices.
-void enqueue_step(lbm_ctx* c, hipStream_t st) {
-  const int64_t idx = c->t + 1;
+int flavor_of(const lbm_ctx* c, int64_t idx) {
   const int K = c->p.check_every;
-  int flavor = kPlain;
-  if (idx % K == 0) flavor = kCheck;
-  else if (K >= 2 && idx % K == K - 1) flavor = kStore;
+  if (idx % K == 0) return kCheck;
+  return K >= 2 && idx % K == K - 1 ? kStore : kPlain;
+}
+
+constexpr int kMultiRing = 2 * kMultiSteps - 1;
+int multi_rows(int shape) { return kMultiShapes[shape].nw * kMultiShapes[shape].rpw; }
+int multi_tiles_x(const lbm_ctx* c) {
+  const int txo = kLanes - 2 * kMultiRing;
+  return (c->grid.nx + txo - 1) / txo;
+}
+int multi_tiles_y(const lbm_ctx* c, int shape) {
+  const int tyo = multi_rows(shape) - 2 * kMultiRing;
+  return (c->grid.ny + tyo - 1) / tyo;
+}
+long long multi_tiles(const lbm_ctx* c, int shape) {
+  return (long long)multi_tiles_x(c) * multi_tiles_y(c, shape);
+}
+
+// Shape of the two-step kernel for this lattice, or -1 (step by step: the
+// variants, a launch shape other than the default, and where two steps at
+// once do not pay).  Times are per step, cavities, one step | two steps.
+// - Up to one block per compute unit a launch costs its latency, whatever
+//   the size: the lowest blocks that still fit (2, 6, 10 output rows, one row
+//   per wavefront): 128^2 FP64 3.6 | 2.7 us, 256^2 FP32 3.4 | 2.6 us, 320^2
+//   FP32 3.9 | 3.1 us; two rounds of the 6-row blocks up to 512 tiles: 384^2
+//   FP32 4.4 | 3.5 us.
+// - Larger lattices: two rows per wavefront (10 output rows: 1024^2 FP32
+//   13.3 | 10.9, FP64 24.0 | 19.0 us, 2048^2 FP64 117 | 73.5 us); beyond the
+//   last-level cache, except in FP64 (registers), four rows (26 output rows:
+//   4096^2 FP32 264 | 151 us, channel 4096 x 1024 FP16 52.5 | 46.5 us).
+// - The ring costs instructions (1.2 to 1.4 times those of single steps).
+//   16-bit storages in cache are bound by theirs: beyond about 1.1 M nodes
+//   one step at a time is up to 3 % faster (1280^2 FP16 17.4 | 18.1 us, 2048^2
+//   38.1 | 38.8 us), except with a mask or an outlet, whose tests the
+//   two-step kernel leaves out where a tile has none.  Nor does it pay where
+//   the tiles fit the lattice badly (narrow strips).
+int multi_shape(const lbm_ctx* c) {
+  if (c->by != 4 || c->rows != 1 || c->p.strain_fd || c->p.mrt) return -1;
+  const int nx = c->grid.nx, ny = c->grid.ny;
+  if (nx < 16 || ny < 16) return -1;
+  // 16-bit storages: the copies across a periodic side are rounded to nearest,
+  // the node's own values stochastically; a region that continues across the
+  // side has only the latter
+  if (c->esize == 2 && (c->grid.side[0] == LBM_SIDE_PERIODIC ||
+                        c->grid.side[2] == LBM_SIDE_PERIODIC))
+    return -1;
+  for (int s = 0; s < 3; ++s)
+    if (multi_tiles(c, s) <= 256) return s;
+  if (multi_tiles(c, 1) <= 512) return 1;
+  const Geom g = make_geom(c);
+  const bool cached = 2 * 9 * (size_t)g.plane * c->esize <= kLastLevelCacheBytes;
+  const bool big16 = c->esize == 2 && cached && (long long)nx * ny > 1100000;
+  if (big16 && !c->d_solid && c->grid.side[1] != LBM_SIDE_OUTLET) return -1;
+  const int shape = (cached && !big16) || c->esize == 8 ? 3 : 4;
+  const int nr = multi_rows(shape);
+  const double rows = multi_tiles(c, shape) * (2.0 * nr - 8.0);   // collided, both steps
+  if (rows > 1.6 * 2.0 * ((nx + kLanes - 1) / kLanes) * ny) return -1;
+  return shape;
+}
+
+// fluid[tile] = 1 where the region of the tile (64 x nr nodes from (x0, y0),
+// inside the lattice) holds no solid node; one wavefront per tile.
+__global__ __launch_bounds__(kLanes) void multi_fluid_kernel(const uint8_t* __restrict__ solid,
+                                                             int nx, int ny, int tiles_x, int txo,
+                                                             int tyo, int h, int nr,
+                                                             uint8_t* __restrict__ fluid) {
+  const int tile = blockIdx.x, x = tile % tiles_x * txo - h + int(threadIdx.x);
+  const int y0 = tile / tiles_x * tyo - h;
+  int any = 0;
+  if (x >= 0 && x < nx)
+    for (int y = y0 < 0 ? 0 : y0; y < y0 + nr && y < ny; ++y) any |= solid[y * nx + x];
+  const bool some = __builtin_amdgcn_ballot_w64(any != 0) != 0;
+  if (threadIdx.x == 0) fluid[tile] = some ? 0 : 1;
+}
+
+// Choose the two-step shape of the current configuration and mark its tiles
+// without solid nodes.  Called where the configuration changes, on the
+// context's stream.
+int configure_multi(lbm_ctx* c) {
+  c->multi = multi_shape(c);
+  if (c->multi < 0 || !c->d_solid) return LBM_OK;
+  const int tx = multi_tiles_x(c), n = tx * multi_tiles_y(c, c->multi);
+  hipLaunchKernelGGL(multi_fluid_kernel, dim3(n), dim3(kLanes), 0, c->stream, c->d_solid,
+                     c->grid.nx, c->grid.ny, tx, kLanes - 2 * kMultiRing,
+                     multi_rows(c->multi) - 2 * kMultiRing, kMultiRing, multi_rows(c->multi),
+                     c->d_fluid);
+  HIPCHECK(hipGetLastError());
+  return LBM_OK;
+}
+
+StepArgs step_args(const lbm_ctx* c) {
   StepArgs a{};
   a.g = make_geom(c);
   a.tiles_x = c->tiles_x;
@@ -136,8 +222,42 @@ void enqueue_step(lbm_ctx* c, hipStream_t st) {
   a.has_force = c->d_force != nullptr;
   a.rng = c->rng;
   a.rng_slot = c->cur;
+  return a;
+}
+
+const void* consts_of(const lbm_ctx* c) {
+  return c->p.storage == LBM_STORE_F64 ? static_cast<const void*>(&c->kd)
+                                       : static_cast<const void*>(&c->kf);
+}
+
+// Queue the next step, or kMultiSteps plain steps in one launch, then swap
+// lattices; returns the steps taken.  left: steps still to take.  The last
+// step of a call is always a step of its own, so that the two lattices then
+// hold the states of the last two steps.
+int enqueue_steps(lbm_ctx* c, int64_t left, hipStream_t st) {
+  const int64_t idx = c->t + 1;
+  const int flavor = flavor_of(c, idx);
+  StepArgs a = step_args(c);
   const void* src = c->lat[c->cur];
   void* dst = c->lat[c->cur ^ 1];
+  const void* k = consts_of(c);
+  const int shape = c->multi;
+  if (shape >= 0 && left > kMultiSteps && flavor == kPlain && flavor_of(c, idx + 1) == kPlain) {
+    a.tiles_x = multi_tiles_x(c);
+    a.ntiles = a.tiles_x * multi_tiles_y(c, shape);
+    bool ok;
+    switch (c->p.storage) {
+      case 0: ok = launch_multi<0>(shape, src, dst, a, c->d_fluid, k, st); break;
+      case 1: ok = launch_multi<1>(shape, src, dst, a, c->d_fluid, k, st); break;
+      case 2: ok = launch_multi<2>(shape, src, dst, a, c->d_fluid, k, st); break;
+      default: ok = launch_multi<3>(shape, src, dst, a, c->d_fluid, k, st); break;
+    }
+    if (ok) {
+      c->cur ^= 1;
+      c->t += kMultiSteps;
+      return kMultiSteps;
+    }
+  }
   int var = (c->p.strain_fd ? kVarFds : 0) | (c->p.mrt ? kVarMrt : 0);
   // When the two lattices together outgrow MI355X's 256 MiB Infinity Cache
   // the default kernel stores non-temporally: measured 6 % faster at 4096^2
@@ -145,8 +265,6 @@ void enqueue_step(lbm_ctx* c, hipStream_t st) {
   // faster.
   const size_t elem = c->p.storage == LBM_STORE_F64 ? 8 : c->p.storage == LBM_STORE_F32 ? 4 : 2;
   if (var == 0 && 2 * 9 * (size_t)a.g.plane * elem > kLastLevelCacheBytes) var = kVarNts;
-  const void* k = c->p.storage == LBM_STORE_F64 ? static_cast<const void*>(&c->kd)
-                                                 : static_cast<const void*>(&c->kf);
   switch (c->p.storage * 3 + flavor) {
     case 0: launch_step<0, kPlain>(c->by, c->rows, var, src, dst, a, k, st); break;
     case 1: launch_step<0, kStore>(c->by, c->rows, var, src, dst, a, k, st); break;
@@ -168,6 +286,7 @@ void enqueue_step(lbm_ctx* c, hipStream_t st) {
   }
   c->cur ^= 1;
   c->t = idx;
+  return 1;
 }
 
 template <class S, class FT>
@@ -344,8 +463,11 @@ int lbm_create(const lbm_grid* grid, const uint8_t* solid_mask, const lbm_params
     if (any) {
       c->h_solid.assign(solid_mask, solid_mask + n);
       for (auto& v : c->h_solid) v = v ? 1 : 0;
-      ok = dev(hipMalloc(&c->d_solid, n), "hipMalloc mask") &&
+      // followed by one byte per tile of the two-step kernel (two output rows
+      // or more each)
+      ok = dev(hipMalloc(&c->d_solid, n + (size_t)multi_tiles(c, 0)), "hipMalloc mask") &&
            dev(hipMemcpy(c->d_solid, c->h_solid.data(), n, hipMemcpyHostToDevice), "copy mask");
+      c->d_fluid = c->d_solid + n;
     }
   }
   if (!ok) {
@@ -353,6 +475,7 @@ int lbm_create(const lbm_grid* grid, const uint8_t* solid_mask, const lbm_params
     return LBM_EDEVICE;
   }
   rc = configure_tiles(c);
+  if (!rc) rc = configure_multi(c);
   if (!rc) rc = init_common<double>(c, nullptr, nullptr, nullptr);
   if (!rc) {
     hipError_t e = hipStreamSynchronize(c->stream);
@@ -426,7 +549,9 @@ int lbm_step(lbm_ctx* c, int64_t n) {
         const int cur0 = c->cur;
         const bool chk0 = c->checked;
         HIPCHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        for (int i = 0; i < K; ++i) enqueue_step(c, st);
+        int launches = 0;
+        for (int i = 0; i < K; ++launches) i += enqueue_steps(c, K - i, st);
+        c->graph_flips = launches & 1;
         hipError_t e = hipStreamEndCapture(st, &gr);
         c->t = t0;
         c->cur = cur0;
@@ -441,12 +566,11 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       }
       HIPCHECK(hipGraphLaunch(c->graph[par], st));
       c->t += K;
-      if (K % 2) c->cur ^= 1;
+      c->cur ^= c->graph_flips;
       c->checked = true;
       left -= K;
     } else {
-      enqueue_step(c, st);
-      --left;
+      left -= enqueue_steps(c, left, st);
     }
   }
   HIPCHECK(hipGetLastError());
@@ -707,7 +831,8 @@ int lbm_set_storage(lbm_ctx* c, int32_t storage, double storage_scale) {
       hipGraphExecDestroy(c->graph[i]);
       c->graph[i] = nullptr;
     }
-  return apply_force(c);
+  const int rc = configure_multi(c);
+  return rc ? rc : apply_force(c);
 }
 
 int lbm_set_force_field(lbm_ctx* c, const double* fx, const double* fy) {
@@ -741,7 +866,8 @@ int lbm_set_launch(lbm_ctx* c, int32_t by, int32_t rows) {
   HIPCHECK(hipStreamSynchronize(c->stream));
   c->by = by;
   c->rows = rows;
-  return configure_tiles(c);
+  const int rc = configure_tiles(c);
+  return rc ? rc : configure_multi(c);
 }
 
 int lbm_get_launch(lbm_ctx* c, int32_t* by, int32_t* rows) {

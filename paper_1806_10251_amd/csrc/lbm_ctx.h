@@ -41,6 +41,9 @@ struct lbm_ctx {
   lbmk::Consts<double> kd{};
   lbmk::Consts<float> kf{};
   hipGraphExec_t graph[2] = {nullptr, nullptr};
+  int graph_flips = 0;  // lattice swaps of a captured window, modulo 2
+  int multi = -1;       // shape of the two-step kernel, -1: step by step
+  uint8_t* d_fluid = nullptr;   // its tiles without solid nodes (behind d_solid)
   bool timing = false;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   double last_ms = -1.0;

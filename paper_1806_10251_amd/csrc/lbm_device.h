@@ -506,8 +506,29 @@ __device__ __forceinline__ unsigned outlet_mask(const Geom& g, int y) {
 }
 
 // Outlet links of node (nx-1, y): non-equilibrium extrapolation from node
-// (nx-2, y) at the same time level, with the convective outlet velocity
+// (nx-2, y) at the same time level (its pulled populations d2; fx, fy: its
+// body force), with the convective outlet velocity
 // u* = (u*_old + U u(nx-2)) / (1 + U) and density rho0.  Returns u*.
+template <class C>
+__device__ __forceinline__ void outlet_complete(const C d2[9], const Geom& g, const Consts<C>& k,
+                                                C fx, C fy, C us_old, C vs_old, int y, C d[9],
+                                                C& us, C& vs) {
+  C r2, u2, v2;
+  macro<C>(d2, k, fx, fy, r2, u2, v2);
+  const C U = k.u_in_max;
+  const C invU = C(1) / (C(1) + U);
+  us = (us_old + U * u2) * invU;
+  vs = (vs_old + U * v2) * invU;
+  C e2[9], eo[9];
+  equilibrium_dev<C>(r2, u2, v2, k, e2);
+  equilibrium_dev<C>(C(0), us, vs, k, eo);
+  const unsigned m = outlet_mask(g, y);
+#pragma unroll
+  for (int a = 0; a < 9; ++a)
+    if (m & (1u << a)) d[a] = eo[a] + (d2[a] - e2[a]);
+}
+
+// The same with the pull of node (nx-2, y) from the lattice.
 // force: a readable [2][ny][nx] buffer of the compute type, always loaded
 // (a conditional load here miscompiles for gfx950 inside the halo-row
 // lambda); its values are the per-node body force when has_force, else the
@@ -525,19 +546,7 @@ __device__ __forceinline__ void outlet_links(const typename S::T* __restrict__ f
   const int fi = y * g.nx + g.nx - 2;
   const C ffx = force[fi], ffy = force[g.nx * g.ny + fi];
   const C fx = has_force ? ffx : k.fx, fy = has_force ? ffy : k.fy;
-  C r2, u2, v2;
-  macro<C>(d2, k, fx, fy, r2, u2, v2);
-  const C U = k.u_in_max;
-  const C invU = C(1) / (C(1) + U);
-  us = (hist_in[y] + U * u2) * invU;
-  vs = (hist_in[g.ny + y] + U * v2) * invU;
-  C e2[9], eo[9];
-  equilibrium_dev<C>(r2, u2, v2, k, e2);
-  equilibrium_dev<C>(C(0), us, vs, k, eo);
-  const unsigned m = outlet_mask(g, y);
-#pragma unroll
-  for (int a = 0; a < 9; ++a)
-    if (m & (1u << a)) d[a] = eo[a] + (d2[a] - e2[a]);
+  outlet_complete<C>(d2, g, k, fx, fy, hist_in[y], hist_in[g.ny + y], y, d, us, vs);
 }
 
 // Region node (x, y) of a tile (x in -1..nx, y in -1..ny): wrap periodic
@@ -677,29 +686,15 @@ __device__ __forceinline__ void ghost_writes(typename S::T* __restrict__ fb, con
 // Periodic sides: the population d_a that leaves across a periodic side goes
 // to the frame slot its wrapped target pulls from; corners that wrap on both
 // axes are written by the x handler.
-template <class S, bool CL = false>
-__device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const Geom& g,
-                                           const Consts<typename S::C>& k, int x, int y,
-                                           bool wcol, bool ecol, const typename S::C d[9]) {
-  using C = typename S::C;
-  using T = typename S::T;
+// put(on, a, sx, sy, v): slot (x + sx, y + sy) of plane a receives v where on.
+// PER: also the copies across periodic sides (a lattice in memory; a region
+// held in LDS extends past them instead).
+template <class C, bool CL, bool PER, class Put>
+__device__ __forceinline__ void side_slots_to(const Geom& g, const Consts<C>& k, int x, int y,
+                                              bool wcol, bool ecol, const C d[9], Put put) {
   const bool srow = y == 0, nrow = y == g.ny - 1;
   if (!(wcol || ecol || srow || nrow)) return;
   const bool px = periodic_x<CL>(g), py = periodic_y<CL>(g);
-  const Rsrc r = lattice_rsrc(fb);
-  const int node = gidx(g, x, y);
-  // slot (x + sx, y + sy) of plane a: the plane in the scalar offset (as in
-  // every population access), the shift in the vector offset
-  struct Slot {
-    uint32_t vo, so;
-  };
-  auto shift = [&](int a, int sx, int sy) {
-    return Slot{uint32_t(node + sx + sy * g.pitch) * uint32_t(sizeof(T)),
-                uint32_t(a * g.plane) * uint32_t(sizeof(T))};
-  };
-  auto put = [&](bool on, Slot sl, C v) {
-    if (on) Buf<T>::template st<0>(r, sl.vo, sl.so, S::enc(v, k.scale));
-  };
   // inlet profile at this row (uniform)
   auto u_inlet = [&]() {
     const C H = C(g.ny), yy = C(y) + C(0.5);
@@ -718,7 +713,7 @@ __device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const
       const bool corner = !py && ((ey > 0 && srow) || (ey < 0 && nrow));
       if (!CL && !corner && kind == kOutlet) continue;
       const C corr = corner ? C(0) : C(6) * w_of<C>(a) * k.rho0 * (C(ex) * ux + C(ey) * uy);
-      put(on, shift(a, -ex, -ey), d[opp_of(a)] + corr);
+      put(on, a, -ex, -ey, d[opp_of(a)] + corr);
     }
   };
   auto bounce_y = [&](int sd) {
@@ -731,13 +726,13 @@ __device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const
       // lanes whose source also lies beyond a non-periodic W/E side: corner
       const bool on = px || !((ex > 0 && x == 0) || (ex < 0 && x == g.nx - 1));
       const C corr = C(6) * w_of<C>(a) * k.rho0 * C(ex) * ux;
-      put(on, shift(a, -ex, -ey), d[opp_of(a)] + corr);
+      put(on, a, -ex, -ey, d[opp_of(a)] + corr);
     }
   };
   if (!px) {
     if (wcol) bounce_x(kW, x == 0);
     if (ecol) bounce_x(kE, x == g.nx - 1);
-  } else {
+  } else if constexpr (PER) {
     // x-periodic: d_a leaving across W (e_x < 0) or E (e_x > 0)
 #pragma unroll
     for (int a = 1; a < 9; ++a) {
@@ -747,13 +742,13 @@ __device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const
       const bool on = ex < 0 ? x == 0 : x == g.nx - 1;
       const bool cy = (ey > 0 && nrow) || (ey < 0 && srow);
       if (cy && !py) continue;   // target beyond a wall: bounce-back takes it
-      put(on, shift(a, -ex * g.nx, cy ? -ey * g.ny : 0), d[a]);
+      put(on, a, -ex * g.nx, cy ? -ey * g.ny : 0, d[a]);
     }
   }
   if (!py) {
     if (srow) bounce_y(kS);
     if (nrow) bounce_y(kN);
-  } else {
+  } else if constexpr (PER) {
     // y-periodic: d_a leaving across S (e_y < 0) or N (e_y > 0); lanes whose
     // target also crosses a W/E side are left to the x handler or to the
     // bounce-back of that side
@@ -763,9 +758,26 @@ __device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const
       if (ey == 0) continue;
       if (ey < 0 ? !srow : !nrow) continue;
       const bool on = !((ex > 0 && x == g.nx - 1) || (ex < 0 && x == 0));
-      put(on, shift(a, 0, -ey * g.ny), d[a]);
+      put(on, a, 0, -ey * g.ny, d[a]);
     }
   }
+}
+
+// The same into a lattice in memory: the plane in the scalar offset (as in
+// every population access), the shift in the vector offset.
+template <class S, bool CL = false>
+__device__ __forceinline__ void side_slots(typename S::T* __restrict__ fb, const Geom& g,
+                                           const Consts<typename S::C>& k, int x, int y,
+                                           bool wcol, bool ecol, const typename S::C d[9]) {
+  using C = typename S::C;
+  using T = typename S::T;
+  const Rsrc r = lattice_rsrc(fb);
+  const int node = gidx(g, x, y);
+  side_slots_to<C, CL, true>(g, k, x, y, wcol, ecol, d, [&](bool on, int a, int sx, int sy, C v) {
+    if (on)
+      Buf<T>::template st<0>(r, uint32_t(node + sx + sy * g.pitch) * uint32_t(sizeof(T)),
+                             uint32_t(a * g.plane) * uint32_t(sizeof(T)), S::enc(v, k.scale));
+  });
 }
 
 // Half-way bounce-back from solid nodes inside the lattice (stationary):

@@ -217,6 +217,37 @@ __device__ __forceinline__ void store_velocity(const C dd[9], bool on, int gx, i
   sv = on ? v_ : C(0);
 }
 
+// Density gradient of the node at (ry, c) of the LDS density tile (rho - rho0;
+// the sentinel HUGE_VAL marks a solid node, whose density is replaced by the
+// node's own), with the isotropic (stencil 0: d rho = 3 sum_a w_a e_a
+// rho(x + e_a)) or the central stencil.  solid_src: bit a set when the source
+// of link a (the neighbour at -e_a) is solid.
+template <class C, bool SOLID, int W>
+__device__ __forceinline__ void density_gradient(const C (*s_rho)[W], int ry, int c, int stencil,
+                                                 C& drx, C& dry, unsigned& solid_src) {
+  const C SENT = C(HUGE_VALF);
+  const C nE = s_rho[ry][c + 1], nW = s_rho[ry][c - 1];
+  const C nN = s_rho[ry + 1][c], nS = s_rho[ry - 1][c];
+  const C nNE = s_rho[ry + 1][c + 1], nNW = s_rho[ry + 1][c - 1];
+  const C nSE = s_rho[ry - 1][c + 1], nSW = s_rho[ry - 1][c - 1];
+  const C own = s_rho[ry][c];
+  auto sub = [&](C v) { return (SOLID && v == SENT) ? own : v; };
+  if (stencil == 0) {
+    const C ne = sub(nNE), nw = sub(nNW), se = sub(nSE), sw = sub(nSW);
+    drx = (sub(nE) - sub(nW)) * (C(1) / C(3)) + ((ne - nw) + (se - sw)) * (C(1) / C(12));
+    dry = (sub(nN) - sub(nS)) * (C(1) / C(3)) + ((ne - se) + (nw - sw)) * (C(1) / C(12));
+  } else {
+    drx = C(0.5) * (sub(nE) - sub(nW));
+    dry = C(0.5) * (sub(nN) - sub(nS));
+  }
+  solid_src = 0;
+  if (SOLID)
+    solid_src = (nW == SENT ? 1u << 1 : 0u) | (nS == SENT ? 1u << 2 : 0u) |
+                (nE == SENT ? 1u << 3 : 0u) | (nN == SENT ? 1u << 4 : 0u) |
+                (nSW == SENT ? 1u << 5 : 0u) | (nSE == SENT ? 1u << 6 : 0u) |
+                (nNE == SENT ? 1u << 7 : 0u) | (nNW == SENT ? 1u << 8 : 0u);
+}
+
 // One tile of the fused step (the body of both the single-lattice kernel and
 // the batch kernel).  LDS: s_rho[(BY*R + 2) * 66] of type C, s_red[BY * 4];
 // with FDS (strain rates of the corrections by finite differences of the
@@ -429,24 +460,11 @@ __device__ __forceinline__ void step_tile(const typename S::T* __restrict__ fa,
     const int y = y0 + r;
     if (!INT && (x >= g.nx || y >= g.ny)) continue;
     const int c = lane + 1;
-    // the eight neighbours (sentinel = solid node)
-    const C nE = s_rho[ry][c + 1], nW = s_rho[ry][c - 1];
-    const C nN = s_rho[ry + 1][c], nS = s_rho[ry - 1][c];
-    const C nNE = s_rho[ry + 1][c + 1], nNW = s_rho[ry + 1][c - 1];
-    const C nSE = s_rho[ry - 1][c + 1], nSW = s_rho[ry - 1][c - 1];
     const C own = s_rho[ry][c];
     if (OBST && !INT && own == SENT) continue;  // solid node
-    auto sub = [&](C v) { return (OBST && !INT && v == SENT) ? own : v; };
     C drx, dry;
-    if (uflag(k.stencil) == 0) {
-      // isotropic: d rho = 3 sum_a w_a e_a rho(x + e_a)
-      const C ne = sub(nNE), nw = sub(nNW), se = sub(nSE), sw = sub(nSW);
-      drx = (sub(nE) - sub(nW)) * (C(1) / C(3)) + ((ne - nw) + (se - sw)) * (C(1) / C(12));
-      dry = (sub(nN) - sub(nS)) * (C(1) / C(3)) + ((ne - se) + (nw - sw)) * (C(1) / C(12));
-    } else {
-      drx = C(0.5) * (sub(nE) - sub(nW));
-      dry = C(0.5) * (sub(nN) - sub(nS));
-    }
+    unsigned solid_src;
+    density_gradient<C, OBST && !INT>(s_rho, ry, c, uflag(k.stencil), drx, dry, solid_src);
     C sxx = C(0), syy = C(0);
     if (FDS) {
       // d_x u_x and d_y u_y with the density-gradient stencil and neighbour rule
@@ -478,14 +496,10 @@ __device__ __forceinline__ void step_tile(const typename S::T* __restrict__ fa,
     if (!INT) {
       side_slots<S, CL>(fb, g, kc, x, y, x0 == 0, x0 + kLanes >= g.nx, d[r]);
       if (OBST) {
-        unsigned src = (nW == SENT ? 1u << 1 : 0u) | (nS == SENT ? 1u << 2 : 0u) |
-                       (nE == SENT ? 1u << 3 : 0u) | (nN == SENT ? 1u << 4 : 0u) |
-                       (nSW == SENT ? 1u << 5 : 0u) | (nSE == SENT ? 1u << 6 : 0u) |
-                       (nNE == SENT ? 1u << 7 : 0u) | (nNW == SENT ? 1u << 8 : 0u);
         // a mirrored halo node that is solid is not a source: the link
         // crosses the side
-        src &= ~side_links<CL>(g, x, y);
-        solid_slots<S>(fb, g, kc, x, y, d[r], src);
+        solid_src &= ~side_links<CL>(g, x, y);
+        solid_slots<S>(fb, g, kc, x, y, d[r], solid_src);
       }
     }
     if (OUTL && x == g.nx - 1) {

@@ -1,0 +1,137 @@
+"""Two plain steps in one launch against the same steps one by one: a call of
+n steps pairs them, n calls of one step never do, and the states must be the
+same bit for bit (same arithmetic and the same storage rounding between the
+steps), for every side kind, storage and launch shape of the two-step kernel
+(chosen by size)."""
+import numpy as np
+import pytest
+
+from workloads import hartmann_force
+
+pytestmark = pytest.mark.gpu
+
+PERIODIC, WALL, LID, INLET, OUTLET = 0, 1, 2, 3, 4
+CAVITY = (WALL, WALL, WALL, LID)
+CHANNEL = (INLET, OUTLET, WALL, WALL)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lbm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1806_10251_amd import lbm as L
+    L.load()
+    return L
+
+
+def pair(nx, ny, sides, storage, mask=None, force=None, **kw):
+    from paper_1806_10251_amd import lbm
+    p = dict(nu=0.03, gamma=0.6, u_lid=0.05, u_in_max=0.03, check_every=1000, storage=storage)
+    p.update(kw)
+    out = []
+    rng = np.random.default_rng(5)
+    y, x = np.mgrid[0:ny, 0:nx]
+    start = (1 + 1e-3 * np.sin(0.3 * x + 0.1 * y), 0.01 * np.sin(0.2 * y), 0.01 * rng.random((ny, nx)))
+    for _ in range(2):
+        lat = lbm.Lattice(nx, ny, sides, solid=mask, **p)
+        if force is not None:
+            lat.set_force_field(*force)
+        lat.init_fields(*start)
+        out.append(lat)
+    return out
+
+
+def same_after(nx, ny, sides, storage, steps=7, **kw):
+    print("[gpu-case] two-step", nx, ny, sides, storage, sorted(kw), flush=True)
+    a, b = pair(nx, ny, sides, storage, **kw)
+    a.step(steps)
+    for _ in range(steps):
+        b.step(1)
+    assert a.steps == b.steps == steps
+    mask = kw.get("mask")
+    fluid = np.ones((ny, nx), bool) if mask is None else np.asarray(mask) == 0
+    fa, fb = a.populations(), b.populations()
+    assert np.isfinite(fa[:, fluid]).all()
+    np.testing.assert_array_equal(fa[:, fluid], fb[:, fluid])
+    # the other lattice holds the step before: the mean of the last two agrees
+    a.average_last_two()
+    b.average_last_two()
+    np.testing.assert_array_equal(a.populations()[:, fluid], b.populations()[:, fluid])
+    # and the next steps start from consistent boundary slots and history
+    a.step(3)
+    for _ in range(3):
+        b.step(1)
+    for p, q in zip(a.fields(), b.fields()):
+        np.testing.assert_array_equal(p, q)
+
+
+def obstacles(nx, ny):
+    m = np.zeros((ny, nx), np.uint8)
+    m[ny // 3:ny // 3 + max(3, ny // 6), nx // 4:nx // 4 + 5] = 1
+    m[ny - 4:ny - 2, nx // 2:nx // 2 + 7] = 1
+    m[0:2, nx // 3] = 1          # on the south side
+    m[ny // 2, nx - 9] = 1       # a single node
+    return m
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "bf16", "f16"])
+@pytest.mark.parametrize("sides", [CAVITY, CHANNEL, (PERIODIC,) * 4, (PERIODIC, PERIODIC, WALL, LID),
+                                   (LID, WALL, PERIODIC, PERIODIC),
+                                   (INLET, OUTLET, PERIODIC, PERIODIC)])
+@pytest.mark.parametrize("solid", [False, True])
+def test_every_side_kind(sides, storage, solid):
+    nx, ny = 123, 37
+    same_after(nx, ny, sides, storage, mask=obstacles(nx, ny) if solid else None)
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 16), (58, 22), (59, 23), (61, 17), (116, 52), (1000, 16)])
+@pytest.mark.parametrize("sides", [CAVITY, (PERIODIC,) * 4, CHANNEL])
+def test_tile_edges(nx, ny, sides):
+    same_after(nx, ny, sides, "f32")
+
+
+@pytest.mark.parametrize("nx,ny,storage", [
+    (230, 190, "f64"), (330, 310, "f64"), (401, 390, "f32"),   # 6- and 10-row tiles, two rounds
+    (700, 333, "f64"), (650, 640, "f32"), (900, 700, "bf16"),  # two rows per wavefront
+    (1930, 1901, "f32"), (4100, 1101, "f16"),                  # four, beyond the last-level cache
+])
+def test_launch_shapes(nx, ny, storage):
+    same_after(nx, ny, CHANNEL, storage, steps=5, mask=obstacles(nx, ny))
+    same_after(nx, ny, CAVITY, storage, steps=5)
+
+
+@pytest.mark.parametrize("kw", [dict(gi_correct=0), dict(drho_stencil=1), dict(fx=1e-5, fy=-2e-5),
+                                dict(force=True)])
+def test_options(kw):
+    nx, ny = 100, 41
+    if kw.pop("force", False):
+        kw["force"] = hartmann_force(nx, ny, 1e-5, 2.0)
+    for sides in (CHANNEL, (PERIODIC, PERIODIC, WALL, WALL)):
+        same_after(nx, ny, sides, "f64", **kw)
+
+
+@pytest.mark.parametrize("check_every", [1, 2, 3, 4, 5, 7, 100])
+def test_windows_and_checkpoints(check_every, tmp_path):
+    """Captured windows of any length (their lattice swaps are odd or even),
+    residuals, and a checkpoint in the middle of a pair."""
+    from paper_1806_10251_amd import lbm
+    print("[gpu-case] two-step windows", check_every, flush=True)
+    nx, ny = 90, 45
+    kw = dict(nu=0.03, gamma=0.6, u_in_max=0.03, check_every=check_every, storage="f16")
+    m = obstacles(nx, ny)
+    a = lbm.Lattice(nx, ny, CHANNEL, solid=m, **kw)
+    b = lbm.Lattice(nx, ny, CHANNEL, solid=m, **kw)
+    for n in (201, 13, 2 * check_every, 3):
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        if a.steps >= check_every:
+            assert a.residual == b.residual and a.mass == b.mass
+    a.save(tmp_path / "c")
+    c = lbm.Lattice(nx, ny, CHANNEL, solid=m, **kw)
+    c.load_checkpoint(tmp_path / "c")
+    c.step(9)
+    b.step(9)
+    for p, q in zip(c.fields(), b.fields()):
+        np.testing.assert_array_equal(p, q)
