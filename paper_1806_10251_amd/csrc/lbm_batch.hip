@@ -29,7 +29,7 @@
 #include "../../include/lbm.h"
 #include "lbm_aux.h"
 #include "lbm_host.h"
-#include "lbm_kernels.h"
+#include "lbm_multi.h"
 
 using namespace lbmk;
 using namespace lbmh;
@@ -46,6 +46,7 @@ struct CaseDev {
   void* lat[2];
   int outlet;
   int ntiles;
+  int mtiles_x;        // tiles per row of the two-step kernel
 };
 
 template <class C>
@@ -188,6 +189,7 @@ struct BatchArgs {
   const int* item_tile;
   int n_items;
   long long t0;           // steps done before this window
+  int par0;               // lattice that holds the state at t0
   int nsteps;             // steps in this window
   int K;                  // check cadence
   unsigned* ticket;       // ticket counter (zero at launch)
@@ -221,6 +223,48 @@ __global__ __launch_bounds__(kLanes* BY) void batch_step_kernel(StepLaunch L) {
   if (!L.active[c]) return;
   run_item<S, BY, R, FL, NTS ? kVarNts : 0, CLS>(L.cases[c], L.par, L.item_tile[it], s_rho,
                                                  s_red);
+}
+
+// Two plain steps of every active case in one launch (see lbm_multi.h): one
+// block per tile of the two-step kernel, the path per item.  Cases retire at
+// check steps only, and the host then drops their items, so no item needs a
+// look at the active flags (one dependent load less before the populations).
+// Bound: small FP64 batches by the latency of a block (item, descriptor and
+// population loads in a row, one or two blocks per compute unit by registers),
+// large FP32 ones by vector instructions.  Per step, one step | two steps per
+// launch: 12 FP64 cases with sides of 64 to 128 26.4 | 13.9 us, 20 FP32 cases
+// with sides of 64 to 512 115 | 71 us.
+template <class S, int NW, int RPW>
+__global__ __launch_bounds__(kLanes* NW, (multi_waves<S, NW, RPW>()))
+void batch_multi_kernel(const CaseDev* __restrict__ cases, const int2* __restrict__ items,
+                        int par) {
+  using T = typename S::T;
+  using C = typename S::C;
+  extern __shared__ __align__(16) char smem[];
+  using F = T[NW * RPW - 2][kLanes];
+  using R = C[kLanes + 2];
+  F* s_f = reinterpret_cast<F*>(smem);
+  R* s_rho = reinterpret_cast<R*>(smem + 9 * sizeof(F));
+  const int2 it = items[blockIdx.x];
+  const int c = __builtin_amdgcn_readfirstlane(it.x);
+  if (c < 0) return;
+  const int code = __builtin_amdgcn_readfirstlane(it.y);
+  const CaseDev& cd = cases[c];
+  const T* fa = static_cast<const T*>(cd.lat[par]);
+  T* fb = static_cast<T*>(cd.lat[par ^ 1]);
+  StepArgs args = cd.a[par];
+  args.tiles_x = cd.mtiles_x;
+  const Consts<C> k = case_consts<C>(cd);
+  const int tile = code & kTileMask;
+  if (code >> kInteriorBit)
+    multi_tile<S, NW, RPW, kMultiSteps, false, false, false, true>(fa, fb, args, k, tile, s_f,
+                                                                   s_rho);
+  else if (cd.outlet)
+    multi_tile<S, NW, RPW, kMultiSteps, true, true, false, false>(fa, fb, args, k, tile, s_f,
+                                                                  s_rho);
+  else
+    multi_tile<S, NW, RPW, kMultiSteps, true, false, false, false>(fa, fb, args, k, tile, s_f,
+                                                                   s_rho);
 }
 
 // one block per case: residual of the check step that ends the window
@@ -274,7 +318,7 @@ __global__ __launch_bounds__(kLanes* BY) void batch_kernel(BatchArgs b) {
     __syncthreads();
     if (__hip_atomic_load(b.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
     const long long t = b.t0 + s;   // steps done before this one
-    const int par = int(t & 1);
+    const int par = (b.par0 + s) & 1;
     const long long idx = (t + 1) % b.K;
     const int flavor = idx == 0 ? kCheck : ((b.K >= 2 && idx == b.K - 1) ? kStore : kPlain);
     if (flavor == kCheck) run_item<S, BY, R, kCheck>(cd, par, tile, s_rho, s_red);
@@ -331,6 +375,7 @@ struct HostCase {
   size_t fluid = 0;
   std::vector<uint8_t> h_mask;      // [ny][nx], 1 = solid
   std::vector<uint8_t> tile_int;    // per tile: region all fluid, away from the sides
+  std::vector<uint8_t> multi_int[kNumMultiShapes];   // the same per two-step shape (on demand)
   int state_par = 0;  // which lattice holds the case's current state
 };
 
@@ -355,6 +400,11 @@ struct lbm_batch {
   int cls_off[kNumClasses + 1] = {0, 0, 0, 0, 0};  // graph schedule: items of class k
                                                    // are [cls_off[k], cls_off[k + 1])
   bool merged = false;  // graph schedule with few items: one launch per step
+  int multi = -1;       // shape of the two-step kernel, -1: step by step
+  int2* d_mitems = nullptr;   // its items (case, tile and interior bit)
+  int n_mitems = 0, mitem_cap = 0;
+  int par = 0;          // lattice that holds the state of the advancing cases
+  int window_flips = 0; // lattice swaps of a captured window, modulo 2
   double* d_partials = nullptr;
   double* d_case_res = nullptr;
   int* d_active = nullptr;
@@ -387,6 +437,7 @@ void free_batch(lbm_batch* b) {
   hipFree(b->d_cases);
   hipFree(b->d_item_case);
   hipFree(b->d_item_tile);
+  hipFree(b->d_mitems);
   hipFree(b->d_partials);
   hipFree(b->d_case_res);
   hipFree(b->d_active);
@@ -401,6 +452,132 @@ void free_batch(lbm_batch* b) {
   hipFree(b->d_err);
   if (b->own_stream) hipStreamDestroy(b->own_stream);
   delete b;
+}
+
+// Bytes of the two lattices of every active case.  Beyond the 256 MiB
+// Infinity Cache a written lattice is evicted before the next step reads it,
+// so the step stores it non-temporally (as the single-lattice path does).
+constexpr size_t kLastLevelCacheBytes = size_t(256) << 20;
+size_t active_lattice_bytes(const lbm_batch* b) {
+  const size_t es = b->storage == LBM_STORE_F64 ? 8 : 4;
+  size_t bytes = 0;
+  for (int i = 0; i < b->n; ++i)
+    if (b->h_active[i]) bytes += 2 * 9 * (size_t)b->cs[i].g.plane * es;
+  return bytes;
+}
+
+constexpr int kMultiRing = 2 * kMultiSteps - 1, kMultiCols = kLanes - 2 * kMultiRing;
+int multi_tiles_x(const HostCase& c) { return (c.grid.nx + kMultiCols - 1) / kMultiCols; }
+int multi_tiles_y(const HostCase& c, int shape) {
+  const int tyo = kMultiShapes[shape].nw * kMultiShapes[shape].rpw - 2 * kMultiRing;
+  return (c.grid.ny + tyo - 1) / tyo;
+}
+
+// Per tile of a two-step shape: region all fluid and one node away from every
+// side.
+const std::vector<uint8_t>& multi_interior(HostCase& c, int shape) {
+  std::vector<uint8_t>& f = c.multi_int[shape];
+  if (!f.empty()) return f;
+  const int nx = c.grid.nx, ny = c.grid.ny, tx = multi_tiles_x(c), ty = multi_tiles_y(c, shape);
+  const int nr = kMultiShapes[shape].nw * kMultiShapes[shape].rpw, tyo = nr - 2 * kMultiRing;
+  f.assign((size_t)tx * ty, 0);
+  for (int j = 0; j < ty; ++j)
+    for (int i = 0; i < tx; ++i) {
+      const int x0 = i * kMultiCols - kMultiRing, y0 = j * tyo - kMultiRing;
+      if (x0 < 1 || x0 + kLanes > nx - 1 || y0 < 1 || y0 + nr > ny - 1) continue;
+      bool fluid = true;
+      for (int y = y0; fluid && y < y0 + nr; ++y)
+        fluid = std::memchr(&c.h_mask[(size_t)y * nx + x0], 1, kLanes) == nullptr;
+      f[(size_t)j * tx + i] = fluid ? 1 : 0;
+    }
+  return f;
+}
+
+// Tiles of region length len along a side of length n whose region keeps one
+// node away from both ends.
+int multi_inner(int n, int tiles, int len) {
+  int inner = 0;
+  for (int i = 0; i < tiles; ++i) {
+    const int lo = i * (len - 2 * kMultiRing) - kMultiRing;
+    inner += lo >= 1 && lo + len <= n - 1;
+  }
+  return inner;
+}
+
+// Shape of the two-step kernel for the active cases, or -1: as for a single
+// lattice, from the sum of their tiles.  Times per step, one step | two steps
+// per launch:
+// - Up to one block per compute unit (or 512 of the 6-row blocks) the launch
+//   is what counts: 4 cavities 64^2 FP64 9.3 | 4.5 us, 20 of them 11.0 | 8.9,
+//   FP32 9.3 | 5.3.
+// - More tiles: as long as a quarter of them keep away from the sides (20 cavities 128^2
+//   FP64 21.3 | 14.9 us, FP32 11.8 | 8.9; 20 channels 400 x 100 FP64 38.1 |
+//   25.6; 20 cavities 512^2 FP64 157 | 128, FP32 96.3 | 60.7).  Many small
+//   lattices have none, and the boundary work is done on the ring as well (200
+//   cavities 64^2 FP64 25.7 | 40.3 us, FP32 16.6 | 23.2).
+int batch_multi_shape(lbm_batch* b) {
+  if (b->schedule != 0 || b->by != 4) return -1;
+  long long tiles[kNumMultiShapes] = {};
+  bool any = false;
+  for (int i = 0; i < b->n; ++i) {
+    if (!b->h_active[i]) continue;
+    const HostCase& c = b->cs[i];
+    if (c.grid.nx < 16 || c.grid.ny < 16) return -1;
+    any = true;
+    for (int s = 0; s < kNumMultiShapes; ++s)
+      tiles[s] += (long long)multi_tiles_x(c) * multi_tiles_y(c, s);
+  }
+  if (!any) return -1;
+  for (int s = 0; s < 3; ++s)
+    if (tiles[s] <= 256) return s;
+  if (tiles[1] <= 512) return 1;
+  const bool cached = active_lattice_bytes(b) <= kLastLevelCacheBytes;
+  const int shape = cached || b->storage == LBM_STORE_F64 ? 3 : 4;
+  long long inner = 0;
+  for (int i = 0; i < b->n; ++i) {
+    if (!b->h_active[i]) continue;
+    const HostCase& c = b->cs[i];
+    const int nr = kMultiShapes[shape].nw * kMultiShapes[shape].rpw;
+    inner += (long long)multi_inner(c.grid.nx, multi_tiles_x(c), kLanes) *
+             multi_inner(c.grid.ny, multi_tiles_y(c, shape), nr);
+  }
+  return 4 * inner >= tiles[shape] ? shape : -1;
+}
+
+// Cost of an item of the two-step kernel relative to the others (12 FP64 cases
+// with sides of 64 to 128, channels among them: 17.3 us per step with equal
+// weights, 13.8 with these, 14.9 with 2 : 3 : 4).
+int multi_weight(const lbm_batch* b, const int2& it) {
+  if ((unsigned(it.y) >> kInteriorBit) & 1) return 1;
+  const HostCase& c = b->cs[it.x];
+  const int tx = multi_tiles_x(c);
+  return c.grid.side[1] == LBM_SIDE_OUTLET && (it.y & kTileMask) % tx == tx - 1 ? 3 : 2;
+}
+
+// The items (case by case) in launch order.  Block i runs on XCD i mod 8: every
+// XCD gets a contiguous range of about the same cost, so that neighbouring
+// tiles share its L2, the dearest items first, so that the last blocks are
+// short ones.  Ranges that end earlier are padded with empty items (case -1).
+std::vector<int2> multi_launch_order(const lbm_batch* b, const std::vector<int2>& items) {
+  long long total = 0;
+  for (const int2& it : items) total += multi_weight(b, it);
+  std::vector<int2> part[8];
+  long long sum = 0;
+  for (const int2& it : items) {
+    part[std::min<long long>(7, sum * 8 / total)].push_back(it);
+    sum += multi_weight(b, it);
+  }
+  size_t longest = 0;
+  for (auto& v : part) {
+    std::stable_sort(v.begin(), v.end(), [&](const int2& p, const int2& q) {
+      return multi_weight(b, p) > multi_weight(b, q);
+    });
+    longest = std::max(longest, v.size());
+  }
+  std::vector<int2> out(8 * longest, int2{-1, 0});
+  for (size_t k = 0; k < 8; ++k)
+    for (size_t i = 0; i < part[k].size(); ++i) out[8 * i + k] = part[k][i];
+  return out;
 }
 
 // (Re)build the tiling of every case for the current launch shape, the
@@ -457,6 +634,7 @@ int configure(lbm_batch* b) {
     d.lat[1] = c.lat[1];
     d.outlet = c.grid.side[1] == LBM_SIDE_OUTLET;
     d.ntiles = c.ntiles;
+    d.mtiles_x = multi_tiles_x(c);
     desc[i] = d;
   }
   if (!b->d_cases) HIPCHECK(hipMalloc(&b->d_cases, sizeof(CaseDev) * b->n));
@@ -530,6 +708,25 @@ int rebuild_items(lbm_batch* b) {
     HIPCHECK(hipMalloc(&b->d_item_tile, sizeof(int) * b->n_items));
     b->item_cap = b->n_items;
   }
+  b->multi = batch_multi_shape(b);
+  if (b->multi >= 0) {
+    std::vector<int2> mi;
+    for (int i = 0; i < b->n; ++i) {
+      if (!b->h_active[i]) continue;
+      const std::vector<uint8_t>& f = multi_interior(b->cs[i], b->multi);
+      for (size_t t = 0; t < f.size(); ++t)
+        mi.push_back(int2{i, int(t) | (int(f[t]) << kInteriorBit)});
+    }
+    mi = multi_launch_order(b, mi);
+    b->n_mitems = (int)mi.size();
+    if (b->n_mitems > b->mitem_cap) {
+      hipFree(b->d_mitems);
+      b->d_mitems = nullptr;
+      HIPCHECK(hipMalloc(&b->d_mitems, sizeof(int2) * b->n_mitems));
+      b->mitem_cap = b->n_mitems;
+    }
+    HIPCHECK(hipMemcpy(b->d_mitems, mi.data(), sizeof(int2) * b->n_mitems, hipMemcpyHostToDevice));
+  }
   if (b->n_items) {
     HIPCHECK(hipMemcpy(b->d_item_case, ic.data(), sizeof(int) * b->n_items, hipMemcpyHostToDevice));
     HIPCHECK(hipMemcpy(b->d_item_tile, itl.data(), sizeof(int) * b->n_items, hipMemcpyHostToDevice));
@@ -557,21 +754,21 @@ int init_case(lbm_batch* b, int ci, const FT* rho, const FT* ux, const FT* uy) {
   if (b->storage == LBM_STORE_F64) launch_case_init<StoreF64, FT>(b, c, rho, ux, uy);
   else launch_case_init<StoreF32, FT>(b, c, rho, ux, uy);
   HIPCHECK(hipGetLastError());
-  // lattice parity of the batch: state lives in lat[t & 1]; copy when t is odd
-  if (b->t & 1) {
+  // the batch's current lattice: copy when it is the second one
+  if (b->par) {
     const size_t es = b->storage == LBM_STORE_F64 ? 8 : 4;
     const size_t bytes = 9 * (size_t)c.g.plane * es;
     HIPCHECK(hipMemcpyAsync(c.lat[1], c.lat[0], bytes, hipMemcpyDeviceToDevice, b->stream));
     HIPCHECK(hipMemcpyAsync(c.hist[1], c.hist[0], 2 * es * c.grid.ny, hipMemcpyDeviceToDevice,
                             b->stream));
   }
-  c.state_par = int(b->t & 1);
+  c.state_par = b->par;
   return LBM_OK;
 }
 
-// Before a run: every enabled case must hold its state in lat[t & 1].
+// Before a run: every enabled case must hold its state in lat[par].
 int align_parity(lbm_batch* b) {
-  const int par = int(b->t & 1);
+  const int par = b->par;
   const size_t es = b->storage == LBM_STORE_F64 ? 8 : 4;
   for (int i = 0; i < b->n; ++i) {
     HostCase& c = b->cs[i];
@@ -622,18 +819,6 @@ void launch_step_storage(int by, int flavor, int cls, bool nts, const StepLaunch
   else launch_step_by<S, 4>(flavor, cls, nts, L, st);
 }
 
-// Bytes of the two lattices of every active case.  Beyond the 256 MiB
-// Infinity Cache a written lattice is evicted before the next step reads it,
-// so the step stores it non-temporally (as the single-lattice path does).
-constexpr size_t kLastLevelCacheBytes = size_t(256) << 20;
-size_t active_lattice_bytes(const lbm_batch* b) {
-  const size_t es = b->storage == LBM_STORE_F64 ? 8 : 4;
-  size_t bytes = 0;
-  for (int i = 0; i < b->n; ++i)
-    if (b->h_active[i]) bytes += 2 * 9 * (size_t)b->cs[i].g.plane * es;
-  return bytes;
-}
-
 RetireArgs retire_args(lbm_batch* b, double tol, long long min_steps) {
   RetireArgs r{};
   r.cases = b->d_cases;
@@ -650,10 +835,40 @@ RetireArgs retire_args(lbm_batch* b, double tol, long long min_steps) {
   return r;
 }
 
-// Enqueue nsteps steps starting at step counter t (graph schedule): the step
-// kernels, and when the last one is a check step, the per-case reduction and
-// the step-counter tick.
-void enqueue_window(lbm_batch* b, long long t, int nsteps, const RetireArgs& r, hipStream_t st) {
+template <class S, int NW, int RPW>
+bool launch_batch_multi(const lbm_batch* b, int par, hipStream_t st) {
+  constexpr size_t lds = multi_lds<S, NW, RPW>();
+  auto* fn = batch_multi_kernel<S, NW, RPW>;
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return false;
+  hipLaunchKernelGGL(fn, dim3(b->n_mitems), dim3(kLanes, NW), lds, st, b->d_cases, b->d_mitems,
+                     par);
+  return true;
+}
+
+template <class S>
+bool launch_batch_multi_shape(const lbm_batch* b, int par, hipStream_t st) {
+  switch (b->multi) {
+    case 0: return launch_batch_multi<S, 8, 1>(b, par, st);
+    case 1: return launch_batch_multi<S, 12, 1>(b, par, st);
+    case 2: return launch_batch_multi<S, 16, 1>(b, par, st);
+    case 3: return launch_batch_multi<S, 8, 2>(b, par, st);
+    default:
+      if constexpr (sizeof(typename S::C) == 4) return launch_batch_multi<S, 8, 4>(b, par, st);
+      return false;
+  }
+}
+
+// Enqueue nsteps steps starting at step counter t in lattice par (graph
+// schedule): the step kernels, pairs of plain steps in one launch (never the
+// last step of the window, so that the two lattices hold the last two states),
+// and when the last one is a check step, the per-case reduction and the
+// step-counter tick.  Returns the lattice swaps.
+int enqueue_window(lbm_batch* b, long long t, int nsteps, int par, const RetireArgs& r,
+                   hipStream_t st) {
+  int launches = 0;
   StepLaunch L{};
   L.cases = b->d_cases;
   L.item_case = b->d_item_case;
@@ -662,11 +877,21 @@ void enqueue_window(lbm_batch* b, long long t, int nsteps, const RetireArgs& r, 
   L.active = b->d_active;
   int last_flavor = kPlain;
   const bool nts = active_lattice_bytes(b) > kLastLevelCacheBytes;
-  for (int i = 0; i < nsteps; ++i) {
-    const long long tt = t + i;
+  auto flavor_at = [&](long long tt) {
     const long long idx = (tt + 1) % b->K;
-    const int flavor = idx == 0 ? kCheck : ((b->K >= 2 && idx == b->K - 1) ? kStore : kPlain);
-    L.par = int(tt & 1);
+    return idx == 0 ? kCheck : ((b->K >= 2 && idx == b->K - 1) ? kStore : kPlain);
+  };
+  for (int i = 0; i < nsteps; ++i, ++launches, par ^= 1) {
+    const int flavor = flavor_at(t + i);
+    if (b->multi >= 0 && nsteps - i > kMultiSteps && flavor == kPlain &&
+        flavor_at(t + i + 1) == kPlain &&
+        (b->storage == LBM_STORE_F64 ? launch_batch_multi_shape<StoreF64>(b, par, st)
+                                     : launch_batch_multi_shape<StoreF32>(b, par, st))) {
+      i += kMultiSteps - 1;
+      last_flavor = kPlain;
+      continue;
+    }
+    L.par = par;
     if (b->merged) {
       if (b->n_items > 0) {
         if (b->storage == LBM_STORE_F64)
@@ -694,6 +919,7 @@ void enqueue_window(lbm_batch* b, long long t, int nsteps, const RetireArgs& r, 
     hipLaunchKernelGGL(batch_reduce_kernel, dim3(b->n), dim3(kLanes), 0, st, r, b->n,
                        (const long long*)b->d_tnow, nsteps);
   hipLaunchKernelGGL(batch_tick_kernel, dim3(1), dim3(64), 0, st, b->d_tnow, nsteps);
+  return launches;
 }
 
 }  // namespace
@@ -917,6 +1143,7 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
       a.item_tile = b->d_item_tile;
       a.n_items = b->n_items;
       a.t0 = b->t;
+      a.par0 = b->par;
       a.nsteps = (int)ns;
       a.K = b->K;
       a.ticket = b->d_sync;
@@ -928,13 +1155,14 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
       void* kargs[] = {&a};
       HIPCHECK(hipLaunchKernel(kfn, dim3(G), dim3(kLanes, b->by), kargs, 0, b->stream));
       hipLaunchKernelGGL(batch_tick_kernel, dim3(1), dim3(64), 0, b->stream, b->d_tnow, (int)ns);
+      b->par ^= int(ns & 1);
     } else if (ns == b->K && b->K >= 4) {
       // full window: captured once per start parity, replayed
-      const int par = int(b->t & 1);
+      const int par = b->par;
       if (!b->graph[par]) {
         hipGraph_t gr = nullptr;
         HIPCHECK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-        enqueue_window(b, b->t, (int)ns, ret, b->stream);
+        b->window_flips = enqueue_window(b, b->t, (int)ns, par, ret, b->stream) & 1;
         hipError_t e = hipStreamEndCapture(b->stream, &gr);
         if (e != hipSuccess) return fail(LBM_EDEVICE, hipGetErrorString(e));
         e = hipGraphInstantiate(&b->graph[par], gr, nullptr, nullptr, 0);
@@ -945,8 +1173,9 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
         }
       }
       HIPCHECK(hipGraphLaunch(b->graph[par], b->stream));
+      b->par ^= b->window_flips;
     } else {
-      enqueue_window(b, b->t, (int)ns, ret, b->stream);
+      b->par ^= enqueue_window(b, b->t, (int)ns, b->par, ret, b->stream) & 1;
     }
     HIPCHECK(hipGetLastError());
     b->t += ns;
@@ -961,6 +1190,8 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
       int now = 0;
       for (int v : act) now += v;
       if (now < active_n) {  // drop retired cases from the work list
+        for (int i = 0; i < n; ++i)
+          if (b->h_active[i] && !act[i]) b->cs[i].state_par = b->par;
         b->h_active = act;
         rc = rebuild_items(b);
         if (rc) return rc;
@@ -971,11 +1202,9 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
   HIPCHECK(hipStreamSynchronize(b->stream));
   HIPCHECK(hipMemcpy(done.data(), b->d_done, sizeof(long long) * n, hipMemcpyDeviceToHost));
   HIPCHECK(hipMemcpy(b->h_status.data(), b->d_status, sizeof(int) * n, hipMemcpyDeviceToHost));
-  for (int i = 0; i < n; ++i) {
-    if (!b->enabled[i]) continue;
-    // retired at step |done|: state in lat[|done| & 1]; else in lat[t & 1]
-    b->cs[i].state_par = done[i] != 0 ? int((done[i] < 0 ? -done[i] : done[i]) & 1) : int(b->t & 1);
-  }
+  // (cases that retired hold their state where the batch was then)
+  for (int i = 0; i < n; ++i)
+    if (b->enabled[i] && b->h_active[i]) b->cs[i].state_par = b->par;
   bool diverged = false;
   for (int i = 0; i < n; ++i) {
     long long v = done[i];

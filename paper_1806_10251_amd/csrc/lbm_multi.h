@@ -72,7 +72,7 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
   }
 
   // ---- the region from memory: all loads before any use
-  C d[RPW][9], us[RPW], vs[RPW];
+  C d[RPW][9];
   bool sol[RPW];
   int gy[RPW];
 #pragma unroll
@@ -80,19 +80,42 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
     gy[q] = INT ? yb + w * RPW + q : row_of<CL>(g, yb + w * RPW + q);
     pull9<S>(fa, g, k, gx, gy[q], d[q]);
     sol[q] = OBST && !INT && args.solid[gy[q] * g.nx + gx];
-    us[q] = vs[q] = C(0);
   }
   __builtin_amdgcn_sched_barrier(0);
+  // the outlet column's velocity per row (in LDS: one node per row has one,
+  // registers for it in every lane cost FP64 spills)
+  C(*s_uv)[2] = reinterpret_cast<C(*)[2]>(s_rho + NR);
   if (OUTL && !INT) {
 #pragma unroll
     for (int q = 0; q < RPW; ++q)
-      if (!sol[q] && gx == g.nx - 1)
-        outlet_links<S>(fa, g, k, has_force, force, hist_in, gy[q], d[q], us[q], vs[q]);
+      if (!sol[q] && gx == g.nx - 1) {
+        C us, vs;
+        outlet_links<S>(fa, g, k, has_force, force, hist_in, gy[q], d[q], us, vs);
+        s_uv[w * RPW + q][0] = us;
+        s_uv[w * RPW + q][1] = vs;
+      }
   }
+  // rows with a solid node: the others and their neighbours take the density
+  // gradient without its tests (uniform per wavefront)
+  int* s_any = reinterpret_cast<int*>(s_uv + NR);
 #pragma unroll
-  for (int q = 0; q < RPW; ++q)
+  for (int q = 0; q < RPW; ++q) {
     s_rho[w * RPW + q][lane + 1] = sol[q] ? SENT : sum9<C>(d[q]);
+    if (OBST && !INT) {
+      const bool any = __builtin_amdgcn_ballot_w64(sol[q]) != 0;
+      if (lane == 0) s_any[w * RPW + q] = any;
+    }
+  }
   __syncthreads();
+  bool near[RPW];
+#pragma unroll
+  for (int q = 0; q < RPW; ++q) {
+    near[q] = false;
+    if (OBST && !INT) {
+      const int r = w * RPW + q, r0 = r < 1 ? 0 : r - 1, r1 = r > NR - 2 ? NR - 1 : r + 1;
+      near[q] = __builtin_amdgcn_readfirstlane(s_any[r0] | s_any[r] | s_any[r1]) != 0;
+    }
+  }
 
 #pragma unroll
   for (int t = 0; t < T; ++t) {
@@ -110,9 +133,11 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
       if (OBST && !INT) on = on && !sol[q];
       if (!on) continue;
       C drx, dry;
-      unsigned solid_src;
-      density_gradient<C, OBST && !INT>(s_rho, r, lane + 1, uflag(k.stencil), drx, dry,
-                                        solid_src);
+      unsigned solid_src = 0;
+      if (OBST && !INT && near[q])
+        density_gradient<C, true>(s_rho, r, lane + 1, uflag(k.stencil), drx, dry, solid_src);
+      else
+        density_gradient<C, false>(s_rho, r, lane + 1, uflag(k.stencil), drx, dry, solid_src);
       C fx = k.fx, fy = k.fy;
       if (has_force) {
         fx = force[ly * g.nx + gx];
@@ -120,19 +145,19 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
       }
       C drho, ux, uy;
       collide<C, 0>(d[q], drx, dry, k, fx, fy, drho, ux, uy);
-      if (OBST && !INT) solid_src &= ~side_links<CL>(g, gx, ly);
+      if (OBST && !INT && near[q]) solid_src &= ~side_links<CL>(g, gx, ly);
       if (last) {
         double acc[4];
         finish_node<S, kPlain>(fb, args, k, d[q], gidx(g, x, y), y * g.nx + x, drho, ux, uy,
                                     0, acc, rng_step + uint32_t(t));
         if (!INT) {
           side_slots<S, CL>(fb, g, k, x, y, xb + H == 0, xb + kLanes - H >= g.nx, d[q]);
-          if (OBST) solid_slots<S>(fb, g, k, x, y, d[q], solid_src);
+          if (OBST && near[q]) solid_slots<S>(fb, g, k, x, y, d[q], solid_src);
         }
         if (OUTL && !INT && x == g.nx - 1) {
           C* ho = static_cast<C*>(args.hist_out);
-          ho[y] = us[q];
-          ho[g.ny + y] = vs[q];
+          ho[y] = s_uv[r][0];
+          ho[g.ny + y] = s_uv[r][1];
         }
       } else {
         if constexpr (S::kSR) {
@@ -154,7 +179,7 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
               s_f[a][rr][cc] = S::enc(v, k.scale);
           };
           side_slots_to<C, CL, false>(g, k, gx, ly, xb <= 0, xb + kLanes >= g.nx, d[q], put);
-          if (OBST) {
+          if (OBST && near[q]) {
 #pragma unroll
             for (int a = 1; a < 9; ++a)
               put((solid_src >> a) & 1u, a, -ex_of(a), -ey_of(a), d[q][opp_of(a)]);
@@ -187,8 +212,11 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
         pull(c2, d2);
         const int fi = gy[q] * g.nx + g.nx - 2;
         const C ffx = force[fi], ffy = force[np + fi];
-        outlet_complete<C>(d2, g, k, has_force ? ffx : k.fx, has_force ? ffy : k.fy, us[q], vs[q],
-                           gy[q], d[q], us[q], vs[q]);
+        C us, vs;
+        outlet_complete<C>(d2, g, k, has_force ? ffx : k.fx, has_force ? ffy : k.fy, s_uv[r][0],
+                           s_uv[r][1], gy[q], d[q], us, vs);
+        s_uv[r][0] = us;
+        s_uv[r][1] = vs;
       }
       s_rho[r][lane + 1] = sol[q] ? SENT : sum9<C>(d[q]);
     }
@@ -201,6 +229,15 @@ __device__ __forceinline__ void multi_tile(const typename S::T* __restrict__ fa,
 template <class S, int NW, int RPW>
 constexpr int multi_waves() {
   return sizeof(typename S::C) == 8 && RPW == 2 ? 4 : 1;
+}
+
+// LDS bytes of a block: populations between the steps, densities, outlet
+// velocities, rows with solid nodes.
+template <class S, int NW, int RPW>
+constexpr size_t multi_lds() {
+  constexpr int NR = NW * RPW;
+  return 9 * sizeof(typename S::T) * (NR - 2) * kLanes +
+         sizeof(typename S::C) * NR * (kLanes + 2 + 2) + sizeof(int) * NR;
 }
 
 template <class S, int NW, int RPW, int T, bool OBST, bool OUTL, bool CL>

@@ -28,8 +28,7 @@ using C = S::C;
 template <int NW, int RPW, bool OBST, bool OUTL, bool CL>
 bool go_kernel(const void* src, void* dst, const StepArgs& a, const uint8_t* fluid,
                const Consts<C>& k, hipStream_t st) {
-  constexpr int NR = NW * RPW;
-  constexpr size_t lds = 9 * sizeof(T) * (NR - 2) * kLanes + sizeof(C) * NR * (kLanes + 2);
+  constexpr size_t lds = multi_lds<S, NW, RPW>();
   if constexpr (lds > 160 * 1024) return false;
   auto* fn = multi_kernel<S, NW, RPW, kMultiSteps, OBST, OUTL, CL>;
   if (lds > 64 * 1024 &&

@@ -135,3 +135,77 @@ def test_windows_and_checkpoints(check_every, tmp_path):
     b.step(9)
     for p, q in zip(c.fields(), b.fields()):
         np.testing.assert_array_equal(p, q)
+
+
+def batch_of(shapes, storage, check_every, masks):
+    from paper_1806_10251_amd import lbm
+    grids = [lbm.make_grid(nx, ny, s) for nx, ny, s in shapes]
+    params = [lbm.make_params(nu=0.02 + 0.002 * i, gamma=0.5, u_lid=0.05, u_in_max=0.03,
+                              storage=storage, check_every=check_every)
+              for i in range(len(shapes))]
+    b = lbm.Batch(grids, masks, params)
+    lats = [lbm.Lattice(nx, ny, s, solid=m, nu=0.02 + 0.002 * i, gamma=0.5, u_lid=0.05,
+                        u_in_max=0.03, storage=storage, check_every=check_every)
+            for i, ((nx, ny, s), m) in enumerate(zip(shapes, masks))]
+    for i, (nx, ny, _) in enumerate(shapes):
+        y, x = np.mgrid[0:ny, 0:nx]
+        start = (1 + 1e-3 * np.sin(0.3 * x), 0.01 * np.sin(0.2 * y), 0.01 * np.cos(0.1 * x + y))
+        b.init_fields(i, *start)
+        lats[i].init_fields(*start)
+    return b, lats
+
+
+# one entry per launch shape of a batch, and one that stays step by step
+BATCHES = {
+    "2 rows": [(40, 31, CAVITY), (16, 16, (PERIODIC,) * 4), (90, 33, CHANNEL)],
+    "6 rows": [(64, 64, CAVITY)] * 6 + [(130, 61, CHANNEL), (59, 23, (PERIODIC, PERIODIC, WALL, LID))],
+    "10 rows": [(190, 200, CHANNEL)] * 2 + [(190, 200, CAVITY)],
+    "two rows per wavefront": [(400, 260, CHANNEL)] * 2 + [(300, 210, CAVITY)] * 2 + [(40, 20, CAVITY)],
+    "beyond the last-level cache": [(1100, 900, CHANNEL)] * 3 + [(1000, 1000, CAVITY)],
+    "step by step": [(64, 64, CAVITY)] * 30,
+    "narrow": [(15, 40, CAVITY), (40, 31, CAVITY)],
+}
+
+
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("key", BATCHES)
+def test_batch_launch_shapes(key, storage):
+    shapes = BATCHES[key]
+    masks = [obstacles(nx, ny) if i % 2 == 0 and min(nx, ny) > 25 else None
+             for i, (nx, ny, _) in enumerate(shapes)]
+    print("[gpu-case] two-step batch", key, storage, flush=True)
+    b, lats = batch_of(shapes, storage, 10, masks)
+    for n in (7, 24, 30, 2, 1):   # partial windows, whole ones, odd starts
+        b.run(0.0, n)
+        for i, (nx, ny, _) in enumerate(shapes):
+            for _ in range(n):
+                lats[i].step(1)
+            fluid = np.ones((ny, nx), bool) if masks[i] is None else masks[i] == 0
+            for p, q in zip(b.fields(i, ny, nx), lats[i].fields()):
+                np.testing.assert_array_equal(np.asarray(p)[fluid], np.asarray(q)[fluid])
+
+
+@pytest.mark.parametrize("check_every", [1, 2, 3, 5, 8, 9])
+def test_batch_windows(check_every):
+    """Windows of odd and even lattice swaps, cases that retire at different
+    checks, and a later run that takes them up again."""
+    shapes = [(40, 31, CAVITY), (33, 40, CAVITY), (90, 33, CHANNEL)]
+    b, lats = batch_of(shapes, "f64", check_every, [None] * 3)
+    n = 3 * check_every
+    b.run(0.0, n)
+    for lat in lats:
+        for _ in range(n):
+            lat.step(1)
+    for lat in lats:                  # the first check at which a run retires cases
+        for _ in range(2 * check_every):
+            lat.step(1)
+    res = sorted(lat.residual for lat in lats)
+    assert res[0] < res[1]
+    done = b.run(0.5 * (res[0] + res[1]), 5 * check_every)
+    more = b.run(0.0, check_every + 1)
+    assert len(set(int(d) for d in done)) > 1
+    for i, (nx, ny, _) in enumerate(shapes):
+        for _ in range(int(done[i]) + int(more[i]) - 2 * check_every):
+            lats[i].step(1)
+        for p, q in zip(b.fields(i, ny, nx), lats[i].fields()):
+            np.testing.assert_array_equal(np.asarray(p), np.asarray(q))
