@@ -32,6 +32,7 @@ typedef __bf16 bf16;
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 thread_local std::string g_err;
 
@@ -515,13 +516,16 @@ int launch_conv(ConvArgs a, hipStream_t st) {
   // unit); eight waves of 32 x 32 or 64 x 32 hide each other's LDS and memory
   // latency better than four larger ones (128 -> 128 channels at 16 x 32 x
   // 32: 10.7 us against 12.7; 64 -> 64 at 16 x 64 x 64: 10.2 against 12.0).
+  // The 64 x 128 tile also where it leaves some units idle: four waves of a
+  // 64 x 64 tile then run two rounds, and with many input channels each alone
+  // on its unit (384 -> 128 channels at 12 x 32 x 32: 31.7 us against 23.0).
   // An image of 2 GB takes the general path.
   const long long px32 = (a.npix + 31) / 32;
   bool done = xbytes > kMaxRsrc;
   int rc = UNET_OK;
   if (!done) {
     if (a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048) rc = try_conv<2, 1, 4, 2>(a, st, &done);
-    if (!rc && !done && a.cout % 128 == 0 && px32 * (a.cout / 64) >= 1024)
+    if (!rc && !done && a.cout % 128 == 0 && px32 * (a.cout / 64) > 512)
       rc = try_conv<1, 1, 2, 4>(a, st, &done);
     if (!rc && !done && a.cout % 64 == 0) rc = try_conv<1, 1, 2, 2>(a, st, &done);
     if (!rc && !done && px32 * (a.cout / 32) >= 2048) rc = try_conv<1, 1, 8, 1>(a, st, &done);
@@ -1129,9 +1133,26 @@ __global__ void to_bf16_kernel(const float* p, bf16* pb, long long n) {
 // floor((I + 1) fine / res) (at least the node floor(I fine / res)); its
 // solid fraction is the mean of the mask over those nodes.
 __device__ __forceinline__ void cell_range(int I, int fine, int res, int& a, int& b) {
-  a = int((long long)I * fine / res);
-  b = int((long long)(I + 1) * fine / res);
+  if ((long long)res * fine < 1LL << 32) {   // uniform; 64-bit divisions are slow
+    a = int(unsigned(I) * unsigned(fine) / unsigned(res));
+    b = int(unsigned(I + 1) * unsigned(fine) / unsigned(res));
+  } else {
+    a = int((long long)I * fine / res);
+    b = int((long long)(I + 1) * fine / res);
+  }
   if (b <= a) b = a + 1;
+}
+
+// Row and column of element k of an array with rows of nx, without a 64-bit
+// division where 32 bits hold k (uniform).
+__device__ __forceinline__ void row_col(long long k, int nx, bool small, int& j, int& i) {
+  if (small) {
+    j = int(unsigned(k) / unsigned(nx));
+    i = int(unsigned(k) - unsigned(j) * unsigned(nx));
+  } else {
+    j = int(k / nx);
+    i = int(k - (long long)j * nx);
+  }
 }
 
 // The case kind (case_params[cps c + 3] when cps == 4, else a cavity)
@@ -1141,73 +1162,114 @@ __device__ __forceinline__ int case_kind(const float* cp, int cps, long long c) 
   return cps > 3 ? int(cp[cps * c + 3]) : UNET_KIND_CAVITY;
 }
 
-__global__ void make_input_kernel(const uint8_t* solid, int nx, int ny, const float* cp, int cps,
-                                  int n, int res, bf16* x0) {
-  const long long total = (long long)n * res * res;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int i = int(e % res), j = int((e / res) % res);
-    const long long c = e / ((long long)res * res);
-    int i0, i1, j0, j1;
-    cell_range(i, nx, res, i0, i1);
-    cell_range(j, ny, res, j0, j1);
-    int cnt = 0;
-    for (int b = j0; b < j1; ++b)
-      for (int a = i0; a < i1; ++a) cnt += solid[(c * ny + b) * nx + a] != 0;
-    float v[UNET_IN_CHANNELS];
+// Grid: pixels of a case in x, cases in y.  Bound by the stores (64 bytes per
+// pixel); one index over all cases with 64-bit divisions took 15.1 us for 12
+// cases of 128 x 128.
+__global__ __launch_bounds__(256) void make_input_kernel(const uint8_t* solid, int nx, int ny,
+                                                         const float* cp, int cps, int n, int res,
+                                                         bf16* x0) {
+  const long long per = (long long)res * res;
+  const bool small = per <= 0xffffffffLL;
+  const int lane = threadIdx.x & 63;
+  static_assert(UNET_IN_CHANNELS == 32, "four lanes per pixel");
+  for (long long c = blockIdx.y; c < n; c += gridDim.y) {
+    for (long long p = blockIdx.x * 256LL + threadIdx.x; p - lane < per; p += gridDim.x * 256LL) {
+      bf16x8 o = bf16x8{};
+      if (p < per) {
+        int i, j;
+        row_col(p, res, small, j, i);
+        int i0, i1, j0, j1;
+        cell_range(i, nx, res, i0, i1);
+        cell_range(j, ny, res, j0, j1);
+        int cnt = 0;
+        for (int b = j0; b < j1; ++b)
+          for (int a = i0; a < i1; ++a) cnt += solid[(c * ny + b) * nx + a] != 0;
+        o[0] = (bf16)(float(cnt) / float((i1 - i0) * (j1 - j0)));
+        o[1] = (bf16)(cp[cps * c + 0] / 500.f);
+        o[2] = (bf16)cp[cps * c + 1];
+        o[3] = (bf16)(cp[cps * c + 2] / 0.1f);
+        o[4] = (bf16)((i + 0.5f) / res);
+        o[5] = (bf16)((j + 0.5f) / res);
+        const bool channel = case_kind(cp, cps, c) == UNET_KIND_CHANNEL;
+        o[6] = (bf16)((channel ? i == 0 : j == res - 1) ? 1.f : 0.f);
+        o[7] = (bf16)1.f;
+      }
+      // the wavefront's 64 pixels, 16 at a time: lane l stores channels 8 (l % 4)
+      // .. of pixel l / 4, so a store is 1 KB in one piece (64 bytes per lane
+      // apart: 14.4 us)
+      const i32x4 v = __builtin_bit_cast(i32x4, o);
+      const long long first = p - lane;
 #pragma unroll
-    for (int k = 0; k < UNET_IN_CHANNELS; ++k) v[k] = 0.f;
-    v[0] = float(cnt) / float((i1 - i0) * (j1 - j0));
-    v[1] = cp[cps * c + 0] / 500.f;
-    v[2] = cp[cps * c + 1];
-    v[3] = cp[cps * c + 2] / 0.1f;
-    v[4] = (i + 0.5f) / res;
-    v[5] = (j + 0.5f) / res;
-    v[6] = (case_kind(cp, cps, c) == UNET_KIND_CHANNEL ? i == 0 : j == res - 1) ? 1.f : 0.f;
-    v[7] = 1.f;
+      for (int q = 0; q < 4; ++q) {
+        const int from = 16 * q + lane / 4;
+        i32x4 w;
 #pragma unroll
-    for (int q = 0; q < UNET_IN_CHANNELS / 8; ++q) {
-      bf16x8 o;
-#pragma unroll
-      for (int u = 0; u < 8; ++u) o[u] = (bf16)v[8 * q + u];
-      *reinterpret_cast<bf16x8*>(x0 + e * UNET_IN_CHANNELS + 8 * q) = o;
+        for (int u = 0; u < 4; ++u) w[u] = __shfl(v[u], from, 64);
+        if (lane % 4) w = i32x4{};
+        if (first + from < per)
+          *reinterpret_cast<i32x4*>(x0 + (c * per + first + from) * UNET_IN_CHANNELS +
+                                    8 * (lane % 4)) = w;
+      }
     }
   }
 }
 
-__device__ float bilinear(const float* out, int ldo, long long c, int res, int ch, float u,
-                          float v) {
-  // (u, v): position in coarse pixel-centre coordinates
+// Bilinear values of three channels at (u, v), in coarse pixel-centre
+// coordinates.  vec: a pixel's channels can be read as four floats (one load
+// instead of three: neighbouring lanes' pixels lie in different lines).
+__device__ __forceinline__ void bilinear3(const float* out, int ldo, bool vec, long long c, int res,
+                                          float u, float v, float r[3]) {
   u = fminf(fmaxf(u, 0.f), float(res - 1));
   v = fminf(fmaxf(v, 0.f), float(res - 1));
   const int i0 = min(int(u), res - 2 < 0 ? 0 : res - 2), j0 = min(int(v), res - 2 < 0 ? 0 : res - 2);
   const int i1 = min(i0 + 1, res - 1), j1 = min(j0 + 1, res - 1);
   const float fu = u - i0, fv = v - j0;
-  auto at = [&](int i, int j) { return out[((c * res + j) * res + i) * ldo + ch]; };
-  return (1 - fv) * ((1 - fu) * at(i0, j0) + fu * at(i1, j0)) +
-         fv * ((1 - fu) * at(i0, j1) + fu * at(i1, j1));
+  float p[4][3];
+  const int pi[4] = {i0, i1, i0, i1}, pj[4] = {j0, j0, j1, j1};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float* at = out + ((c * res + pj[q]) * res + pi[q]) * ldo;
+    if (vec) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(at);
+      for (int ch = 0; ch < 3; ++ch) p[q][ch] = w[ch];
+    } else {
+      for (int ch = 0; ch < 3; ++ch) p[q][ch] = at[ch];
+    }
+  }
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch)
+    r[ch] = (1 - fv) * ((1 - fu) * p[0][ch] + fu * p[1][ch]) +
+            fv * ((1 - fu) * p[2][ch] + fu * p[3][ch]);
 }
 
-__global__ void fields_kernel(const float* out, int ldo, int n, int res, const float* cp,
-                              int cps, const uint8_t* solid, int nx, int ny, float* rho,
-                              float* ux, float* uy) {
-  const long long total = (long long)n * nx * ny;
+// Grid as above.
+__global__ __launch_bounds__(256) void fields_kernel(const float* out, int ldo, int n, int res,
+                                                     const float* cp, int cps,
+                                                     const uint8_t* solid, int nx, int ny,
+                                                     float* rho, float* ux, float* uy) {
+  const long long per = (long long)nx * ny;
+  const bool small = per <= 0xffffffffLL;
+  const bool vec = ldo % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
   const float scx = float(res) / float(nx), scy = float(res) / float(ny);
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
-       e += (long long)gridDim.x * blockDim.x) {
-    const int i = int(e % nx), j = int((e / nx) % ny);
-    const long long c = e / ((long long)nx * ny);
-    if (solid[e]) {
-      rho[e] = 1.f;
-      ux[e] = 0.f;
-      uy[e] = 0.f;
-      continue;
+  for (long long c = blockIdx.y; c < n; c += gridDim.y) {
+    for (long long p = blockIdx.x * 256LL + threadIdx.x; p < per; p += gridDim.x * 256LL) {
+      const long long e = c * per + p;
+      int i, j;
+      row_col(p, nx, small, j, i);
+      if (solid[e]) {
+        rho[e] = 1.f;
+        ux[e] = 0.f;
+        uy[e] = 0.f;
+        continue;
+      }
+      const float U = cp[cps * c + 2];
+      const float u = (i + 0.5f) * scx - 0.5f, v = (j + 0.5f) * scy - 0.5f;
+      float r[3];
+      bilinear3(out, ldo, vec, c, res, u, v, r);
+      rho[e] = 1.f + 3.f * U * U * r[0];
+      ux[e] = U * r[1];
+      uy[e] = U * r[2];
     }
-    const float U = cp[cps * c + 2];
-    const float u = (i + 0.5f) * scx - 0.5f, v = (j + 0.5f) * scy - 0.5f;
-    rho[e] = 1.f + 3.f * U * U * bilinear(out, ldo, c, res, 0, u, v);
-    ux[e] = U * bilinear(out, ldo, c, res, 1, u, v);
-    uy[e] = U * bilinear(out, ldo, c, res, 2, u, v);
   }
 }
 
@@ -1222,53 +1284,113 @@ __global__ void fields_kernel(const float* out, int ldo, int n, int res, const f
 // both zero, as they are for the state at rest.  Closed lattices (cavities)
 // only: a channel's inlet and outlet change its mass and do not keep these
 // sums, so its prediction is left as it is.
-__global__ __launch_bounds__(256) void mass_fix_kernel(float* rho, float* ux, float* uy,
-                                                       const uint8_t* solid, int nx, int ny,
-                                                       const float* cp, int cps) {
-  __shared__ double s[4][256];
+//
+// Bound by latency (three dependent passes over the case): 1024 threads with
+// 16 independent loads each in flight per field, kept in registers from pass to
+// pass where they hold the case (256 threads with one load: 96 us for 12 cases
+// of 128 x 128; eight loads and every pass from memory: 19.2 us).
+constexpr int kMassThreads = 1024, kMassLoads = 16;
+__global__ __launch_bounds__(kMassThreads) void mass_fix_kernel(float* rho, float* ux, float* uy,
+                                                                const uint8_t* solid, int nx,
+                                                                int ny, const float* cp, int cps) {
+  constexpr int kWaves = kMassThreads / 64;
+  __shared__ double s[2][3][kWaves];
   if (case_kind(cp, cps, blockIdx.x) != UNET_KIND_CAVITY) return;
-  const long long base = (long long)blockIdx.x * nx * ny;
+  const int tid = threadIdx.x;
   const long long cnt = (long long)nx * ny;
-  auto block_sum = [&](int q) {
+  const bool small = cnt <= 0xffffffffLL;
+  const long long base = (long long)blockIdx.x * cnt;
+  rho += base;
+  ux += base;
+  uy += base;
+  solid += base;
+  auto block_sums = [&](double (*t)[kWaves], double v[3]) {
+    for (int q = 0; q < 3; ++q) {
+      for (int w = 32; w > 0; w >>= 1) v[q] += __shfl_xor(v[q], w, 64);
+      if (tid % 64 == 0) t[q][tid / 64] = v[q];
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if ((int)threadIdx.x < w) s[q][threadIdx.x] += s[q][threadIdx.x + w];
-      __syncthreads();
+    for (int q = 0; q < 3; ++q) {
+      v[q] = 0.0;
+      for (int w = 0; w < kWaves; ++w) v[q] += t[q][w];
     }
-    return s[q][0];
   };
-  double acc = 0.0, nf = 0.0;
-  for (long long k = threadIdx.x; k < cnt; k += 256)
-    if (!solid[base + k]) {
-      acc += (double)rho[base + k] - 1.0;
-      nf += 1.0;
+  // calls f(u, k) for the thread's nodes, load(u, k) (k clamped into the case)
+  // for a group of them first, unless the registers already hold them all
+  const bool kept = cnt <= kMassThreads * kMassLoads;
+  auto nodes = [&](bool fresh, auto load, auto f) {
+    for (long long k0 = tid; k0 < cnt; k0 += kMassThreads * kMassLoads) {
+      if (fresh || !kept)
+#pragma unroll
+      for (int u = 0; u < kMassLoads; ++u) {
+        const long long k = k0 + u * kMassThreads;
+        load(u, k < cnt ? k : cnt - 1);
+      }
+#pragma unroll
+      for (int u = 0; u < kMassLoads; ++u)
+        if (k0 + u * kMassThreads < cnt) f(u, k0 + u * kMassThreads);
     }
-  s[0][threadIdx.x] = acc;
-  s[1][threadIdx.x] = nf;
-  const double sum_dr = block_sum(0), n_fluid = block_sum(1);
-  const float mean = n_fluid > 0 ? float(sum_dr / n_fluid) : 0.f;
-  double sx = 0.0, sy = 0.0, sr = 0.0;
-  for (long long k = threadIdx.x; k < cnt; k += 256)
-    if (!solid[base + k]) {
-      const float r = rho[base + k] - mean;
-      rho[base + k] = r;
-      const int i = int(k % nx), j = int(k / nx);
-      sx += (i & 1 ? -1.0 : 1.0) * (double)r * (double)ux[base + k];
-      sy += (j & 1 ? -1.0 : 1.0) * (double)r * (double)uy[base + k];
-      sr += (double)r;
-    }
-  __syncthreads();
-  s[0][threadIdx.x] = sx;
-  s[1][threadIdx.x] = sy;
-  s[2][threadIdx.x] = sr;
-  const double Ix = block_sum(0), Iy = block_sum(1), R = block_sum(2);
-  const float mx = R > 0 ? float(Ix / R) : 0.f, my = R > 0 ? float(Iy / R) : 0.f;
-  for (long long k = threadIdx.x; k < cnt; k += 256)
-    if (!solid[base + k]) {
-      const int i = int(k % nx), j = int(k / nx);
-      ux[base + k] -= (i & 1) ? -mx : mx;
-      uy[base + k] -= (j & 1) ? -my : my;
-    }
+  };
+  float r[kMassLoads], a[kMassLoads], b[kMassLoads];
+  unsigned sol = 0;   // bit u: node u is solid
+  auto load_mask = [&](int u, long long k) {
+    sol = (sol & ~(1u << u)) | (solid[k] ? 1u << u : 0u);
+  };
+  double sum[3] = {};
+  nodes(
+      true,
+      [&](int u, long long k) {
+        r[u] = rho[k];
+        load_mask(u, k);
+        if (kept) {
+          a[u] = ux[k];
+          b[u] = uy[k];
+        }
+      },
+      [&](int u, long long) {
+        if (!(sol >> u & 1)) {
+          sum[0] += (double)r[u] - 1.0;
+          sum[1] += 1.0;
+        }
+      });
+  block_sums(s[0], sum);
+  const float mean = sum[1] > 0 ? float(sum[0] / sum[1]) : 0.f;
+  sum[0] = sum[1] = sum[2] = 0.0;
+  nodes(
+      false,
+      [&](int u, long long k) {
+        r[u] = rho[k];
+        a[u] = ux[k];
+        b[u] = uy[k];
+        load_mask(u, k);
+      },
+      [&](int u, long long k) {
+        if (sol >> u & 1) return;
+        const float rm = r[u] - mean;
+        rho[k] = rm;
+        int i, j;
+        row_col(k, nx, small, j, i);
+        sum[0] += (i & 1 ? -1.0 : 1.0) * (double)rm * (double)a[u];
+        sum[1] += (j & 1 ? -1.0 : 1.0) * (double)rm * (double)b[u];
+        sum[2] += (double)rm;
+      });
+  block_sums(s[1], sum);
+  const double R = sum[2];
+  const float mx = R > 0 ? float(sum[0] / R) : 0.f, my = R > 0 ? float(sum[1] / R) : 0.f;
+  nodes(
+      false,
+      [&](int u, long long k) {
+        a[u] = ux[k];
+        b[u] = uy[k];
+        load_mask(u, k);
+      },
+      [&](int u, long long k) {
+        if (sol >> u & 1) return;
+        int i, j;
+        row_col(k, nx, small, j, i);
+        ux[k] = a[u] - ((i & 1) ? -mx : mx);
+        uy[k] = b[u] - ((j & 1) ? -my : my);
+      });
 }
 
 }  // namespace
@@ -1276,11 +1398,15 @@ __global__ __launch_bounds__(256) void mass_fix_kernel(float* rho, float* ux, fl
 // ===========================================================================
 // Input and output maps of either shape (cps: floats per case in case_params)
 // ===========================================================================
+static dim3 case_grid(long long per, int n) {
+  return dim3(unsigned(std::min<long long>((per + 255) / 256, 65535)), std::min(n, 65535));
+}
+
 static int launch_make_input(const uint8_t* solid, int nx, int ny, const float* cp, int cps, int n,
                       int res, void* x0, void* stream) {
   if (!solid || !cp || !x0 || n <= 0 || res <= 0 || nx <= 0 || ny <= 0)
     return fail(UNET_EINVAL, "make_input: bad arguments");
-  hipLaunchKernelGGL(make_input_kernel, dim3(grid_for((long long)n * res * res)), dim3(256), 0,
+  hipLaunchKernelGGL(make_input_kernel, case_grid((long long)res * res, n), dim3(256), 0,
                      as_stream(stream), solid, nx, ny, cp, cps, n, res, static_cast<bf16*>(x0));
   UCHECK(hipGetLastError());
   return UNET_OK;
@@ -1293,10 +1419,10 @@ static int launch_fields(const float* out, int ldo, int n, int res, const float*
       ldo < 3)
     return fail(UNET_EINVAL, "fields_from_output: bad arguments");
   hipStream_t st = as_stream(stream);
-  hipLaunchKernelGGL(fields_kernel, dim3(grid_for((long long)n * nx * ny)), dim3(256), 0, st,
+  hipLaunchKernelGGL(fields_kernel, case_grid((long long)nx * ny, n), dim3(256), 0, st,
                      out, ldo, n, res, cp, cps, solid, nx, ny, rho, ux, uy);
-  hipLaunchKernelGGL(mass_fix_kernel, dim3(n), dim3(256), 0, st, rho, ux, uy, solid, nx, ny, cp,
-                     cps);
+  hipLaunchKernelGGL(mass_fix_kernel, dim3(n), dim3(kMassThreads), 0, st, rho, ux, uy, solid, nx,
+                     ny, cp, cps);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
