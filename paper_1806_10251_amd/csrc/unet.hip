@@ -829,7 +829,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
 // 1024 entries per block, four per thread, split by split, which is the same
 // order (the network's bottom layers hold most of the weights in few splits;
 // with 64 entries per block their 27 000 short blocks bounded the launch, 35.4
-// us for the network at batch 16, now 13.3).  Counts are multiples of 4.
+// us for the network at batch 16, now 12.1).  Counts are multiples of 4.
 constexpr int kFewSplits = 16;
 __host__ __device__ constexpr int sum_entries(int splits) {
   return splits > kFewSplits ? 64 : 1024;
