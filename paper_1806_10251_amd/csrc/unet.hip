@@ -90,6 +90,7 @@ struct ConvArgs {
   int ldpool;
   int up;              // write each pixel to its four fine pixels (2h x 2wd image)
   unsigned xbytes;     // image_bytes of x (set by launch_conv)
+  const bf16* wf;      // w in fragment order (see fragment_kernel), or null
 };
 
 __device__ __forceinline__ bf16x8 relu_mask(bf16x8 d, const bf16x8& y) {
@@ -216,163 +217,58 @@ struct ConvTile {
     const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16) + 2 * (size_t)CB * WS;
     return 4 * CB + (in > (size_t)P * OS ? in : (size_t)P * OS);   // bias, then the tiles
   }
+  static size_t lds_direct(int cin) {
+    const size_t in = (size_t)(TX + 2) * (TY + 2) * (2 * cin + 16);
+    return 4 * CB + (in > (size_t)P * OS ? in : (size_t)P * OS);
+  }
 };
 
-template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
-__global__ __launch_bounds__(64 * WP * WC) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
+// Input tile of a block: HP pixels x cin channels into LDS (S bytes per
+// pixel), eight 16-byte loads in flight per thread.
+template <int NT, int HX, int HP>
+__device__ __forceinline__ void load_tile(const ConvArgs& a, int img, int x0, int y0, int S,
+                                          char* sx) {
+  const int tid = threadIdx.x;
+  const int cv = a.cin >> 3, nvec = HP * cv;
+  const Rsrc xr = image_rsrc(a.x + (long long)img * a.h * a.wd * a.ldx, a.xbytes);
+  const int qs = NT / cv, rs = NT - qs * cv;
+  int px = tid / cv, c = tid - px * cv;
+  for (int base = 0; base < nvec; base += 8 * NT) {
+    bf16x8 v[8];
+    int at[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (base + NT * u < nvec) {
+        const int yy = px / HX, xx = px - yy * HX;
+        const int y = y0 + yy - 1, x = x0 + xx - 1;
+        const bool in = unsigned(y) < unsigned(a.h) && unsigned(x) < unsigned(a.wd);
+        v[u] = load8(xr, in ? unsigned((y * a.wd + x) * a.ldx + 8 * c) * 2u : kOutside);
+        at[u] = px * S + 16 * c;
+        px += qs;
+        c += rs;
+        const bool wrap = c >= cv;
+        px += wrap ? 1 : 0;
+        c -= wrap ? cv : 0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (base + NT * u + tid < nvec) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
+  }
+}
+
+// Results of a block: bias and ReLU, then FP32 from the registers or bf16
+// through LDS (free by then), masked, pooled or upsampled.
+template <int MP, int NC, int WP, int WC, int TX, int KS>
+__device__ __forceinline__ void store_tile(const ConvArgs& a, const f32x16 (&acc)[NC][MP], int img,
+                                           int x0, int y0, int co0, const float* sbias,
+                                           char* smem) {
   using L = ConvTile<MP, NC, WP, WC, TX, KS>;
-  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2), NT = L::NT;
-  extern __shared__ __align__(16) char smem_all[];
-  float* sbias = reinterpret_cast<float*>(smem_all);
-  char* smem = smem_all + 4 * L::CB;
+  constexpr int NT = L::NT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wp = wv % WP, wc = wv / WP;
   const int r = lane & 31, g = lane >> 5;
-  int tile = blockIdx.x;
-  const int tx = tile % tiles_x;
-  tile /= tiles_x;
-  const int ty = tile % tiles_y, img = tile / tiles_y;
-  const int x0 = tx * TX, y0 = ty * TY, co0 = blockIdx.y * L::CB;
-  const int S = 2 * a.cin + 16;
-  char* sx = smem;
-  char* sw = smem + HP * S;
-  const int nst = 9 * a.cin / KS;
-
-  // weights of one stage: CB rows of KS consecutive reduction elements
-  constexpr int kRowVec = KS / 8, kWVec = L::CB * kRowVec, kWPer = (kWVec + NT - 1) / NT;
-  // PF stages in flight in registers (the loads are unconditional: under a
-  // branch, the wait for one stage would become a wait for all of them)
-  constexpr int PF = 3;   // divides the number of stages
-  bf16x8 wreg[PF][kWPer];
-  unsigned woff[kWPer];
-#pragma unroll
-  for (int i = 0; i < kWPer; ++i) {
-    const int v = tid + NT * i, row = kWVec % NT == 0 || v < kWVec ? v / kRowVec : 0;
-    woff[i] = unsigned(row * 9 * a.cin + 8 * (v % kRowVec)) * 2u;
-  }
-  const char* wbase = reinterpret_cast<const char*>(a.w + (long long)co0 * 9 * a.cin);
-  auto load_w = [&](int st, bf16x8 (&w)[kWPer]) {
-    const char* p = wbase + (long long)min(st, nst - 1) * (2 * KS);
-#pragma unroll
-    for (int i = 0; i < kWPer; ++i) w[i] = *reinterpret_cast<const bf16x8*>(p + woff[i]);
-  };
-  auto store_w = [&](int buf, const bf16x8 (&w)[kWPer]) {
-#pragma unroll
-    for (int i = 0; i < kWPer; ++i) {
-      const int v = tid + NT * i;
-      if (kWVec % NT == 0 || v < kWVec)
-        *reinterpret_cast<bf16x8*>(sw + buf * (L::CB * L::WS) + (v / kRowVec) * L::WS +
-                                   16 * (v % kRowVec)) = w[i];
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < PF; ++i) load_w(i, wreg[i]);
-  if (tid < L::CB) sbias[tid] = a.bias ? a.bias[co0 + tid] : 0.f;
-  {
-    // input tile: HP pixels x cin channels, eight 16-byte loads in flight
-    const int cv = a.cin >> 3, nvec = HP * cv;
-    const Rsrc xr = image_rsrc(a.x + (long long)img * a.h * a.wd * a.ldx, a.xbytes);
-    const int qs = NT / cv, rs = NT - qs * cv;
-    int px = tid / cv, c = tid - px * cv;
-    for (int base = 0; base < nvec; base += 8 * NT) {
-      bf16x8 v[8];
-      int at[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (base + NT * u < nvec) {
-          const int yy = px / HX, xx = px - yy * HX;
-          const int y = y0 + yy - 1, x = x0 + xx - 1;
-          const bool in = unsigned(y) < unsigned(a.h) && unsigned(x) < unsigned(a.wd);
-          v[u] = load8(xr, in ? unsigned((y * a.wd + x) * a.ldx + 8 * c) * 2u : kOutside);
-          at[u] = px * S + 16 * c;
-          px += qs;
-          c += rs;
-          const bool wrap = c >= cv;
-          px += wrap ? 1 : 0;
-          c -= wrap ? cv : 0;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (base + NT * u + tid < nvec) *reinterpret_cast<bf16x8*>(sx + at[u]) = v[u];
-    }
-  }
-  store_w(0, wreg[0]);
-  load_w(PF, wreg[0]);
-  __syncthreads();
-
-  f32x16 acc[NC][MP];
-#pragma unroll
-  for (int b = 0; b < NC; ++b)
-#pragma unroll
-    for (int s = 0; s < MP; ++s)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[b][s][v] = 0.f;
-  const char* xb[MP];
-#pragma unroll
-  for (int s = 0; s < MP; ++s) {
-    const int q = 32 * (wp * MP + s) + r;
-    xb[s] = sx + ((q / TX) * HX + q % TX) * S + 16 * g;
-  }
-  const int wrow = (32 * NC * wc + r) * L::WS + 16 * g;
-  // stage position: byte offset of its tap (or kernel row) and channels
-  int soff = 0, chunk = 0, tcol = 0;
-  const int chunks = a.cin / KS;
-  for (int st0 = 0; st0 < nst; st0 += PF) {
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      const int st = st0 + i;
-      const char* wb = sw + (st & 1) * (L::CB * L::WS) + wrow;
-      // operands of the next 32 elements are read while the current ones are
-      // multiplied (the scheduling barriers keep the compiler from sinking each
-      // read to just before its use, one LDS latency per MFMA)
-      constexpr int NJ = KS / 32;
-      bf16x8 A[2][2][NC], B[2][2][MP];
-      const char* xs[MP];
-#pragma unroll
-      for (int s = 0; s < MP; ++s) xs[s] = xb[s] + soff;
-      auto read = [&](int j, bf16x8 (&Aj)[2][NC], bf16x8 (&Bj)[2][MP]) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-          for (int s = 0; s < MP; ++s)
-            Bj[h][s] = *reinterpret_cast<const bf16x8*>(xs[s] + (ROW ? 80 : 64) * j + 32 * h);
-#pragma unroll
-          for (int b = 0; b < NC; ++b)
-            Aj[h][b] = *reinterpret_cast<const bf16x8*>(wb + b * (32 * L::WS) + 64 * j + 32 * h);
-        }
-      };
-      read(0, A[0], B[0]);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (j + 1 < NJ) read(j + 1, A[(j + 1) & 1], B[(j + 1) & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int b = 0; b < NC; ++b)
-#pragma unroll
-            for (int s = 0; s < MP; ++s)
-              acc[b][s] = mfma32(A[j & 1][h][b], B[j & 1][h][s], acc[b][s]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (ROW) {
-        soff += HX * 80;
-      } else {   // uniform: the next channels, or the next tap
-        ++chunk;
-        const bool next = chunk == chunks;
-        const int tap = tcol == 2 ? (TX + 1) * S - S : S;   // one to the right, or the next row
-        soff += next ? tap - 2 * KS * (chunks - 1) : 2 * KS;
-        tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
-        chunk = next ? 0 : chunk;
-      }
-      if (st + 1 < nst) store_w((st + 1) & 1, wreg[(i + 1) % PF]);
-      load_w(st + 1 + PF, wreg[(i + 1) % PF]);
-      __syncthreads();
-    }
-  }
-
   if (a.out_f32) {
 #pragma unroll
     for (int b = 0; b < NC; ++b)
@@ -462,6 +358,243 @@ __global__ __launch_bounds__(64 * WP * WC) void conv_tile_kernel(ConvArgs a, int
   }
 }
 
+template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
+__global__ __launch_bounds__(64 * WP * WC) void conv_tile_kernel(ConvArgs a, int tiles_x, int tiles_y) {
+  using L = ConvTile<MP, NC, WP, WC, TX, KS>;
+  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2), NT = L::NT;
+  extern __shared__ __align__(16) char smem_all[];
+  float* sbias = reinterpret_cast<float*>(smem_all);
+  char* smem = smem_all + 4 * L::CB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = wv % WP, wc = wv / WP;
+  const int r = lane & 31, g = lane >> 5;
+  int tile = blockIdx.x;
+  const int tx = tile % tiles_x;
+  tile /= tiles_x;
+  const int ty = tile % tiles_y, img = tile / tiles_y;
+  const int x0 = tx * TX, y0 = ty * TY, co0 = blockIdx.y * L::CB;
+  const int S = 2 * a.cin + 16;
+  char* sx = smem;
+  char* sw = smem + HP * S;
+  const int nst = 9 * a.cin / KS;
+
+  // weights of one stage: CB rows of KS consecutive reduction elements
+  constexpr int kRowVec = KS / 8, kWVec = L::CB * kRowVec, kWPer = (kWVec + NT - 1) / NT;
+  // PF stages in flight in registers (the loads are unconditional: under a
+  // branch, the wait for one stage would become a wait for all of them)
+  constexpr int PF = 3;   // divides the number of stages
+  bf16x8 wreg[PF][kWPer];
+  unsigned woff[kWPer];
+#pragma unroll
+  for (int i = 0; i < kWPer; ++i) {
+    const int v = tid + NT * i, row = kWVec % NT == 0 || v < kWVec ? v / kRowVec : 0;
+    woff[i] = unsigned(row * 9 * a.cin + 8 * (v % kRowVec)) * 2u;
+  }
+  const char* wbase = reinterpret_cast<const char*>(a.w + (long long)co0 * 9 * a.cin);
+  auto load_w = [&](int st, bf16x8 (&w)[kWPer]) {
+    const char* p = wbase + (long long)min(st, nst - 1) * (2 * KS);
+#pragma unroll
+    for (int i = 0; i < kWPer; ++i) w[i] = *reinterpret_cast<const bf16x8*>(p + woff[i]);
+  };
+  auto store_w = [&](int buf, const bf16x8 (&w)[kWPer]) {
+#pragma unroll
+    for (int i = 0; i < kWPer; ++i) {
+      const int v = tid + NT * i;
+      if (kWVec % NT == 0 || v < kWVec)
+        *reinterpret_cast<bf16x8*>(sw + buf * (L::CB * L::WS) + (v / kRowVec) * L::WS +
+                                   16 * (v % kRowVec)) = w[i];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < PF; ++i) load_w(i, wreg[i]);
+  if (tid < L::CB) sbias[tid] = a.bias ? a.bias[co0 + tid] : 0.f;
+  load_tile<NT, HX, HP>(a, img, x0, y0, S, sx);
+  store_w(0, wreg[0]);
+  load_w(PF, wreg[0]);
+  __syncthreads();
+
+  f32x16 acc[NC][MP];
+#pragma unroll
+  for (int b = 0; b < NC; ++b)
+#pragma unroll
+    for (int s = 0; s < MP; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][s][v] = 0.f;
+  const char* xb[MP];
+#pragma unroll
+  for (int s = 0; s < MP; ++s) {
+    const int q = 32 * (wp * MP + s) + r;
+    xb[s] = sx + ((q / TX) * HX + q % TX) * S + 16 * g;
+  }
+  const int wrow = (32 * NC * wc + r) * L::WS + 16 * g;
+  // stage position: byte offset of its tap (or kernel row) and channels
+  int soff = 0, chunk = 0, tcol = 0;
+  const int chunks = a.cin / KS;
+  for (int st0 = 0; st0 < nst; st0 += PF) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      const int st = st0 + i;
+      const char* wb = sw + (st & 1) * (L::CB * L::WS) + wrow;
+      // operands of the next 32 elements are read while the current ones are
+      // multiplied (the scheduling barriers keep the compiler from sinking each
+      // read to just before its use, one LDS latency per MFMA)
+      constexpr int NJ = KS / 32;
+      bf16x8 A[2][2][NC], B[2][2][MP];
+      const char* xs[MP];
+#pragma unroll
+      for (int s = 0; s < MP; ++s) xs[s] = xb[s] + soff;
+      auto read = [&](int j, bf16x8 (&Aj)[2][NC], bf16x8 (&Bj)[2][MP]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int s = 0; s < MP; ++s)
+            Bj[h][s] = *reinterpret_cast<const bf16x8*>(xs[s] + (ROW ? 80 : 64) * j + 32 * h);
+#pragma unroll
+          for (int b = 0; b < NC; ++b)
+            Aj[h][b] = *reinterpret_cast<const bf16x8*>(wb + b * (32 * L::WS) + 64 * j + 32 * h);
+        }
+      };
+      read(0, A[0], B[0]);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j + 1 < NJ) read(j + 1, A[(j + 1) & 1], B[(j + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < NC; ++b)
+#pragma unroll
+            for (int s = 0; s < MP; ++s)
+              acc[b][s] = mfma32(A[j & 1][h][b], B[j & 1][h][s], acc[b][s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (ROW) {
+        soff += HX * 80;
+      } else {   // uniform: the next channels, or the next tap
+        ++chunk;
+        const bool next = chunk == chunks;
+        const int tap = tcol == 2 ? (TX + 1) * S - S : S;   // one to the right, or the next row
+        soff += next ? tap - 2 * KS * (chunks - 1) : 2 * KS;
+        tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
+        chunk = next ? 0 : chunk;
+      }
+      if (st + 1 < nst) store_w((st + 1) & 1, wreg[(i + 1) % PF]);
+      load_w(st + 1 + PF, wreg[(i + 1) % PF]);
+      __syncthreads();
+    }
+  }
+
+  store_tile<MP, NC, WP, WC, TX, KS>(a, acc, img, x0, y0, co0, sbias, smem);
+}
+
+// The same with weights in fragment order (ConvArgs::wf) straight from memory
+// into registers, PF stages of KS channels ahead: no barrier and no LDS round
+// trip between the stages, so a wavefront runs at its own pace.  Bound by the
+// chain of MFMAs of a wavefront and the latency of its start and end where a
+// layer has one tile per SIMD (256 -> 256 channels at 16 x 16 x 16: 15.0 ->
+// 9.7 us, 128 -> 256 8.9 -> 6.8), by LDS reads and the same latencies beyond
+// (384 -> 128 at 16 x 32 x 32: 25.6 -> 21.2, 128 -> 384 26.5 -> 21.4).
+// Fragments read from rows of 9 cin weights (32 lines per load) cost the
+// address unit 80 clocks each, twice the time of the LDS stages.
+template <int MP, int NC, int WP, int WC, int TX, int KS>
+__global__ __launch_bounds__(64 * WP * WC) void conv_direct_kernel(ConvArgs a, int tiles_x, int tiles_y) {
+  using L = ConvTile<MP, NC, WP, WC, TX, KS>;
+  constexpr int TY = L::TY, HX = TX + 2, HP = (TX + 2) * (TY + 2), NT = L::NT;
+  extern __shared__ __align__(16) char smem_all[];
+  float* sbias = reinterpret_cast<float*>(smem_all);
+  char* smem = smem_all + 4 * L::CB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = wv % WP, wc = wv / WP;
+  const int r = lane & 31, g = lane >> 5;
+  int tile = blockIdx.x;
+  const int tx = tile % tiles_x;
+  tile /= tiles_x;
+  const int ty = tile % tiles_y, img = tile / tiles_y;
+  const int x0 = tx * TX, y0 = ty * TY, co0 = blockIdx.y * L::CB;
+  const int S = 2 * a.cin + 16;
+  char* sx = smem;
+  const int nst = 9 * a.cin / KS;
+  constexpr int PF = 3, NK = KS / 16;   // PF divides the number of stages
+  bf16x8 wreg[PF][NK][NC];
+  const char* wbase = reinterpret_cast<const char*>(a.wf + (long long)co0 * 9 * a.cin);
+  unsigned woff[NC];
+#pragma unroll
+  for (int b = 0; b < NC; ++b)
+    woff[b] = unsigned((NC * wc + b) * (32 * 9 * a.cin) + 8 * lane) * 2u;
+  auto load_w = [&](int st, bf16x8 (&w)[NK][NC]) {
+    const char* p = wbase + (long long)min(st, nst - 1) * (64 * KS);
+#pragma unroll
+    for (int j = 0; j < NK; ++j)
+#pragma unroll
+      for (int b = 0; b < NC; ++b)
+        w[j][b] = *reinterpret_cast<const bf16x8*>(p + woff[b] + 1024 * j);
+  };
+#pragma unroll
+  for (int i = 0; i < PF; ++i) load_w(i, wreg[i]);
+  if (tid < L::CB) sbias[tid] = a.bias ? a.bias[co0 + tid] : 0.f;
+  load_tile<NT, HX, HP>(a, img, x0, y0, S, sx);
+  __syncthreads();
+
+  f32x16 acc[NC][MP];
+#pragma unroll
+  for (int b = 0; b < NC; ++b)
+#pragma unroll
+    for (int s = 0; s < MP; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][s][v] = 0.f;
+  const char* xb[MP];
+#pragma unroll
+  for (int s = 0; s < MP; ++s) {
+    const int q = 32 * (wp * MP + s) + r;
+    xb[s] = sx + ((q / TX) * HX + q % TX) * S + 16 * g;
+  }
+  int soff = 0, chunk = 0, tcol = 0;
+  const int chunks = a.cin / KS;
+  constexpr int NJ = KS / 32;
+  static_assert(NJ % 2 == 0, "the next stage's first operands go to buffer 0");
+  bf16x8 B[2][2][MP];
+  auto read = [&](int off, bf16x8 (&Bj)[2][MP]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int s = 0; s < MP; ++s)
+        Bj[h][s] = *reinterpret_cast<const bf16x8*>(xb[s] + off + 32 * h);
+  };
+  read(0, B[0]);
+  for (int st0 = 0; st0 < nst; st0 += PF) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+      // uniform: the next channels, or the next tap
+      const int here = soff;
+      ++chunk;
+      const bool next = chunk == chunks;
+      const int tap = tcol == 2 ? (TX + 1) * S - S : S;
+      soff += next ? tap - 2 * KS * (chunks - 1) : 2 * KS;
+      tcol = next ? (tcol == 2 ? 0 : tcol + 1) : tcol;
+      chunk = next ? 0 : chunk;
+      if (st0 + i + 1 == nst) soff = here;   // (nothing follows)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        read(j + 1 < NJ ? here + 64 * (j + 1) : soff, B[(j + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int b = 0; b < NC; ++b)
+#pragma unroll
+            for (int s = 0; s < MP; ++s)
+              acc[b][s] = mfma32(wreg[i][2 * j + h][b], B[j & 1][h][s], acc[b][s]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      load_w(st0 + i + PF, wreg[i]);
+    }
+  }
+  __syncthreads();
+  store_tile<MP, NC, WP, WC, TX, KS>(a, acc, img, x0, y0, co0, sbias, smem);
+}
+
 // Launches a tiling if its LDS fits (*done); otherwise leaves *done false.
 template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
 int try_conv_tile(const ConvArgs& a, hipStream_t st, bool* done) {
@@ -502,6 +635,31 @@ int try_conv(const ConvArgs& a, hipStream_t st, bool* done) {
                 : try_conv_width<MP, NC, WP, WC, 32>(a, st, done);
 }
 
+template <int MP, int NC, int WP, int WC, int TX>
+int try_direct_width(const ConvArgs& a, hipStream_t st, bool* done) {
+  using L = ConvTile<MP, NC, WP, WC, TX, 64>;
+  if (a.cin % 64 || a.cout % L::CB) return UNET_OK;
+  const int tx = (a.wd + TX - 1) / TX, ty = (a.h + L::TY - 1) / L::TY;
+  const size_t lds = L::lds_direct(a.cin);
+  if (lds > (size_t)kLdsBytes) return UNET_OK;
+  auto* fn = conv_direct_kernel<MP, NC, WP, WC, TX, 64>;
+  if (lds > 64 * 1024)
+    UCHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  dim3 grid(tx * ty * (a.npix / (a.h * a.wd)), a.cout / L::CB);
+  hipLaunchKernelGGL(fn, grid, dim3(L::NT), lds, st, a, tx, ty);
+  UCHECK(hipGetLastError());
+  *done = true;
+  return UNET_OK;
+}
+
+template <int MP, int NC, int WP, int WC>
+int try_direct(const ConvArgs& a, hipStream_t st, bool* done) {
+  const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32;
+  return narrow ? try_direct_width<MP, NC, WP, WC, 16>(a, st, done)
+                : try_direct_width<MP, NC, WP, WC, 32>(a, st, done);
+}
+
 int launch_conv(ConvArgs a, hipStream_t st) {
   if (a.cin <= 0 || a.cout <= 0 || a.cin % 32 || a.cout % 32)
     return fail(UNET_EINVAL, "conv: cin and cout must be positive multiples of 32");
@@ -523,6 +681,15 @@ int launch_conv(ConvArgs a, hipStream_t st) {
   const long long px32 = (a.npix + 31) / 32;
   bool done = xbytes > kMaxRsrc;
   int rc = UNET_OK;
+  // Weights in fragment order (the network's layers): one 32 x 32 tile per
+  // wavefront up to one wavefront per SIMD, else two.  Times of the LDS-staged
+  // tiles below and of these: at conv_direct_kernel; 192 -> 64 channels at 9 x
+  // 64 x 64 21.7 | 17.1 us, 128 -> 128 at 3 x 32 x 32 8.5 | 6.6.
+  if (!done && a.wf) {
+    if (px32 * (a.cout / 32) > 1024) rc = try_direct<2, 1, 2, 2>(a, st, &done);
+    if (!rc && !done) rc = try_direct<1, 1, 2, 2>(a, st, &done);
+    if (rc || done) return rc;
+  }
   if (!done) {
     if (a.cout % 64 == 0 && px32 * (a.cout / 64) >= 2048) rc = try_conv<2, 1, 4, 2>(a, st, &done);
     if (!rc && !done && a.cout % 128 == 0 && px32 * (a.cout / 64) > 512)
@@ -584,6 +751,33 @@ __global__ __launch_bounds__(256) void flip_tiles_kernel(FlipArgs a) {
 }
 
 int flip_tiles(int cin, int cout) { return 9 * (cin / 32) * (cout / 32); }
+
+// Weights [rows][k] of one or more layers in fragment order: for every 32 rows
+// and 16 reduction elements the 1 KB that a wavefront's lanes take for one
+// MFMA, 16 bytes per lane, reduction elements in order.  Rows are multiples of
+// 64 and k of 9 * 64, so a layer is whole blocks.
+constexpr int kMaxFragment = 32;
+struct FragmentArgs {
+  int layers;
+  struct {
+    const bf16* src;
+    bf16* dst;
+    int k, first;   // first: index of the layer's first block
+  } l[kMaxFragment];
+};
+
+__global__ __launch_bounds__(256) void fragment_kernel(FragmentArgs a) {
+  int q = 0;
+  while (q + 1 < a.layers && int(blockIdx.x) >= a.l[q + 1].first) ++q;
+  const int v = (blockIdx.x - a.l[q].first) * 256 + threadIdx.x;
+  const int lane = v & 63, steps = a.l[q].k / 16, s = (v >> 6) % steps, block = (v >> 6) / steps;
+  *reinterpret_cast<bf16x8*>(a.l[q].dst + 8LL * v) = *reinterpret_cast<const bf16x8*>(
+      a.l[q].src + (long long)(32 * block + (lane & 31)) * a.l[q].k + 16 * s + 8 * (lane >> 5));
+}
+
+// Layers whose convolutions (forward and input gradient) take weights in
+// fragment order.
+bool fragment_layer(int cin, int cout) { return cin % 64 == 0 && cout % 64 == 0; }
 
 // ---------------------------------------------------------------------------
 // Convolution, weight and bias gradients
@@ -1732,6 +1926,8 @@ struct unet {
   float* out = nullptr;  // FP32 network output (training)
   bf16* gout = nullptr;  // bf16 gradient of the output
   bf16* wt = nullptr;    // flipped, transposed weights (input gradients), kept with pb
+  bf16* wf = nullptr;    // pb and wt in fragment order (fragment_layer), kept with pb
+  bf16* wtf = nullptr;
   float* wwork = nullptr;
   double* lwork = nullptr;
   double* host_loss = nullptr;       // pinned; valid when loss_done has passed
@@ -1759,6 +1955,7 @@ int forward_impl(unet* net, const bf16* x0, int n, float* out) {
     a.x = net->act[c.in] + c.in_off;
     a.ldx = kBuf[c.in].ch;
     a.w = net->pb + c.w_off;
+    if (fragment_layer(c.cin, c.cout)) a.wf = net->wf + c.w_off;
     a.bias = net->p + c.b_off;
     if (c.out < 0) {
       a.y = out;
@@ -1821,6 +2018,7 @@ int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_d
   a.x = dy;
   a.ldx = lddy;
   a.w = net->wt + c.w_off;
+  if (fragment_layer(c.cin, c.cout)) a.wf = net->wtf + c.w_off;
   a.y = net->gact[c.in] + c.in_off;
   a.ldy = kBuf[c.in].ch;
   a.npix = n * s * s;
@@ -1836,8 +2034,9 @@ int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_d
 }
 
 // Flipped weights of every layer whose input gradient is needed (all but the
-// first), after each change of pb: one launch.
-int flip_weights(unet* net) {
+// first) and the weights in fragment order, after each change of pb: two
+// launches.
+int lay_out_weights(unet* net) {
   static_assert(kNumConvs <= kMaxFlip, "flip table");
   FlipArgs f{};
   f.w = net->pb;
@@ -1853,6 +2052,22 @@ int flip_weights(unet* net) {
     tiles += flip_tiles(c.cin, c.cout);
   }
   hipLaunchKernelGGL(flip_tiles_kernel, dim3(tiles), dim3(256), 0, net->stream, f);
+  static_assert(2 * kNumConvs <= kMaxFragment, "fragment table");
+  FragmentArgs g{};
+  int blocks = 0;
+  for (int k = 0; k < kNumConvs; ++k) {
+    const Conv& c = net->convs[k];
+    if (!fragment_layer(c.cin, c.cout)) continue;
+    for (int dx = 0; dx < (k ? 2 : 1); ++dx) {
+      auto& l = g.l[g.layers++];
+      l.src = (dx ? net->wt : net->pb) + c.w_off;
+      l.dst = (dx ? net->wtf : net->wf) + c.w_off;
+      l.k = 9 * (dx ? c.cout : c.cin);
+      l.first = blocks;
+      blocks += 9 * c.cin * c.cout / (8 * 256);
+    }
+  }
+  hipLaunchKernelGGL(fragment_kernel, dim3(blocks), dim3(256), 0, net->stream, g);
   UCHECK(hipGetLastError());
   return UNET_OK;
 }
@@ -1922,7 +2137,8 @@ uint64_t splitmix_next(uint64_t& s) {
 double splitmix_uniform(uint64_t& s) { return (splitmix_next(s) >> 11) * (1.0 / 9007199254740992.0); }
 
 void free_net(unet* net) {
-  void* ptrs[] = {net->p, net->pb, net->grad, net->m, net->v, net->out, net->gout, net->wt,
+  void* ptrs[] = {net->p, net->pb, net->grad, net->m, net->v, net->out, net->gout, net->wt, net->wf,
+                  net->wtf,
                   net->wwork, net->lwork};
   for (void* q : ptrs) (void)hipFree(q);
   (void)hipHostFree(net->host_loss);
@@ -1974,7 +2190,9 @@ int unet_create(int32_t max_batch, int32_t res, uint64_t seed, unet** out) {
             alloc((void**)&net->v, sizeof(float) * off) &&
             alloc((void**)&net->out, sizeof(float) * (size_t)max_batch * res * res * UNET_OUT_CHANNELS) &&
             alloc((void**)&net->gout, 2ULL * max_batch * res * res * UNET_OUT_CHANNELS) &&
-            alloc((void**)&net->wt, 2 * off) && alloc((void**)&net->wwork, sizeof(float) * wwork_max) &&
+            alloc((void**)&net->wt, 2 * off) && alloc((void**)&net->wf, 2 * off) &&
+            alloc((void**)&net->wtf, 2 * off) &&
+            alloc((void**)&net->wwork, sizeof(float) * wwork_max) &&
             alloc((void**)&net->lwork, sizeof(double) * unet_loss_work_doubles(0));
   for (int b = 0; ok && b < B_COUNT; ++b) {
     const long long s = res >> kBuf[b].level;
@@ -2044,7 +2262,7 @@ int unet_set_params(unet* net, const float* host) {
   hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(net->nparams)), dim3(256), 0, net->stream,
                      net->p, net->pb, net->nparams);
   UCHECK(hipGetLastError());
-  const int rc = flip_weights(net);
+  const int rc = lay_out_weights(net);
   if (rc) return rc;
   UCHECK(hipStreamSynchronize(net->stream));
   return UNET_OK;
@@ -2094,7 +2312,7 @@ int unet_train_step(unet* net, const void* x0, const float* target, const uint8_
   net->t += 1;
   rc = unet_adam(net->p, net->m, net->v, net->grad, net->pb, net->nparams, lr, 0.9, 0.999, 1e-8,
                  net->t, net->stream);
-  return rc ? rc : flip_weights(net);
+  return rc ? rc : lay_out_weights(net);
 }
 
 }  // extern "C"

@@ -94,3 +94,67 @@ def test_images_of_two_gigabytes(U):
     dw_ref, _ = R.conv3x3_bwd_weight(dy, x)
     bound, _ = R.conv3x3_bwd_weight(np.abs(dy), np.abs(x))
     assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()
+
+
+def layered_forward(U, params, x0):
+    """The network from the single-layer functions (weights as rows)."""
+    import torch
+    lay, _ = R.param_layout()
+
+    def conv(k, x, relu=True):
+        w_off, b_off, ci, co = lay[k]
+        w = params[w_off:w_off + 9 * ci * co].to(torch.bfloat16).reshape(co, 9, ci).contiguous()
+        return U.conv3x3_fwd(x.contiguous(), w, params[b_off:b_off + co].contiguous(), co,
+                             relu=relu, out_f32=not relu)
+
+    def up_cat(a, skip):
+        return torch.cat([U.up2_fwd(a), skip], dim=3)
+
+    e0 = conv(1, conv(0, x0))
+    e1 = conv(3, conv(2, U.pool2_fwd(e0)))
+    e2 = conv(5, conv(4, U.pool2_fwd(e1)))
+    b3 = conv(7, conv(6, U.pool2_fwd(e2)))
+    d2 = conv(9, conv(8, up_cat(b3, e2)))
+    d1 = conv(11, conv(10, up_cat(d2, e1)))
+    return conv(14, conv(13, conv(12, up_cat(d1, e0))), relu=False)
+
+
+@pytest.mark.parametrize("res,n", [(8, 1), (24, 3), (128, 1), (128, 3), (128, 16)])
+def test_network_equals_its_layers(U, res, n):
+    """The network's forms of a convolution (weights in fragment order, fused
+    pooling and upsampling, one or two tiles per wavefront by batch) give the
+    bits of the single layers, also after the weights have changed."""
+    import torch
+    print("[gpu-case] network layers", res, n, flush=True)
+    rng = np.random.default_rng(res + n)
+    net = U.UNet(max_batch=n, res=res, seed=5)
+    x0 = dev(bf(rng, n, res, res, 32), torch.bfloat16)
+    target = dev(rng.standard_normal((n, res, res, 3)), torch.float32)
+    fluid = torch.ones((n, res, res), dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        want = layered_forward(U, dev(net.params(), torch.float32), x0)
+        assert torch.equal(net.forward(x0), want)
+        net.train_step(x0, target, fluid, 1e-3)
+    net.close()
+
+
+@pytest.mark.parametrize("side", [3, 8, 127, 128, 129, 200])
+def test_mass_fix_and_maps_sizes(U, side):
+    """Cases below, at and above what the threads of a case keep in registers
+    (16384 nodes), ragged ones among them; bounds as in test_gpu_unet."""
+    import torch
+    rng = np.random.default_rng(side)
+    solid = (rng.random((3, side, side)) > 0.8).astype(np.uint8)
+    solid[2] = 1                      # a case without fluid nodes
+    cp = np.array([[100.0, 0.3, 0.05], [450.0, 1.0, 0.1], [50.0, 0.5, 0.1]], np.float32)
+    for res in (8, 40):
+        x0 = host(U.make_input(dev(solid, torch.uint8), dev(cp, torch.float32), res))
+        np.testing.assert_allclose(x0, R.bf16(R.make_input(solid, cp.astype(np.float64), res)),
+                                   rtol=2 ** -8, atol=0)
+    for ld in (3, 8, 32):             # pixels read as single floats and as four
+        out = rng.standard_normal((3, 16, 16, ld)).astype(np.float32).astype(np.float64)
+        got = U.fields_from_output(dev(out, torch.float32), dev(cp, torch.float32),
+                                   dev(solid, torch.uint8))
+        ref = R.fields_from_output(out, cp.astype(np.float64), solid)
+        for g, r, tol in zip(got, ref, (2e-6, 1e-6, 1e-6)):
+            np.testing.assert_allclose(host(g), r, rtol=0, atol=tol)
