@@ -381,6 +381,8 @@ struct HostCase {
 
 }  // namespace
 
+constexpr size_t kKeptStage = 64ull << 20;
+
 struct lbm_batch {
   std::vector<HostCase> cs;
   int n = 0;
@@ -403,6 +405,8 @@ struct lbm_batch {
   int multi = -1;       // shape of the two-step kernel, -1: step by step
   int2* d_mitems = nullptr;   // its items (case, tile and interior bit)
   int n_mitems = 0, mitem_cap = 0;
+  double* d_stage = nullptr;   // staging of lbm_batch_fields (see there)
+  size_t stage_bytes = 0;
   int par = 0;          // lattice that holds the state of the advancing cases
   int window_flips = 0; // lattice swaps of a captured window, modulo 2
   double* d_partials = nullptr;
@@ -438,6 +442,7 @@ void free_batch(lbm_batch* b) {
   hipFree(b->d_item_case);
   hipFree(b->d_item_tile);
   hipFree(b->d_mitems);
+  hipFree(b->d_stage);
   hipFree(b->d_partials);
   hipFree(b->d_case_res);
   hipFree(b->d_active);
@@ -1335,8 +1340,20 @@ int lbm_batch_fields(lbm_batch* b, int32_t ci, double* rho, double* ux, double* 
   if (!b || ci < 0 || ci >= b->n) return fail(LBM_EINVAL, "bad batch or case index");
   HostCase& c = b->cs[ci];
   const size_t np = (size_t)c.grid.nx * c.grid.ny;
-  double* d = nullptr;
-  HIPCHECK(hipMalloc(&d, 3 * np * sizeof(double)));
+  // Staging of up to kKeptStage bytes stays with the batch (an allocation and a
+  // free per call cost as much as the copies of a small case), larger ones
+  // last for the call.
+  const size_t bytes = 3 * np * sizeof(double);
+  const bool kept = bytes <= kKeptStage;
+  if (kept && bytes > b->stage_bytes) {
+    hipFree(b->d_stage);
+    b->d_stage = nullptr;
+    b->stage_bytes = 0;
+    HIPCHECK(hipMalloc(&b->d_stage, bytes));
+    b->stage_bytes = bytes;
+  }
+  double* d = b->d_stage;
+  if (!kept) HIPCHECK(hipMalloc(&d, bytes));
   const int blocks = int((np + 255) / 256);
   if (b->storage == LBM_STORE_F64)
     hipLaunchKernelGGL((export_kernel<StoreF64>), dim3(blocks), dim3(256), 0, b->stream,
@@ -1354,7 +1371,7 @@ int lbm_batch_fields(lbm_batch* b, int32_t ci, double* rho, double* ux, double* 
   double* h[3] = {rho, ux, uy};
   for (int i = 0; i < 3 && e == hipSuccess; ++i)
     if (h[i]) e = hipMemcpy(h[i], d + i * np, np * sizeof(double), hipMemcpyDeviceToHost);
-  hipFree(d);
+  if (!kept) hipFree(d);
   if (e != hipSuccess) return fail(LBM_EDEVICE, hipGetErrorString(e));
   return LBM_OK;
 }
