@@ -133,6 +133,9 @@ def cpu_plan(progress=None):
 TRAFFIC_SOURCES = ("paper_1806_10251_amd/csrc/lbm_kernels.h",
                    "paper_1806_10251_amd/csrc/lbm_device.h",
                    "paper_1806_10251_amd/csrc/lbm_step.hip",
+                   "paper_1806_10251_amd/csrc/lbm_multi.h",
+                   "paper_1806_10251_amd/csrc/lbm_multi.hip",
+                   "paper_1806_10251_amd/csrc/lbm_api.hip",
                    "paper_1806_10251_amd/build.py")
 TRAFFIC_SUMMARY = "profiles/step_f32_cavity1024_hbm_traffic.md"
 
@@ -471,8 +474,9 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": measured_traffic(args.storage, n, by, rows),
-                     "note": f"{bpl} B/LUP algorithmic (each population read and written once) x "
-                             f"{n * n} nodes per launch / average step time "
+                     "note": f"{bpl} B/LUP algorithmic (each population read and written once per "
+                             f"step; the default launch shape takes two plain steps per pass over "
+                             f"memory) x {n * n} nodes / average step time "
                              f"{step_ms_dev * 1e3:.2f} us from HIP events on the library's "
                              f"stream over the timed window (its plain, store and check steps "
                              f"and check reductions); traffic: HBM bytes per plain-step launch "

@@ -1,8 +1,12 @@
 // Batched steady solver: many independent lattices (cases of different size,
-// Re, gamma and geometry) advanced together by one persistent kernel per
-// window of check_every steps.
+// Re, gamma and geometry) advanced together in windows of check_every steps.
 //
-// Work is a stream of tickets (step, case, tile) taken in order from one
+// Graph schedules: a window is one captured sequence of launches over the
+// tiles of all active cases, plain steps two per launch where that pays
+// (batch_multi_shape).  Launches, not steps, swap the two lattices, so the
+// batch keeps the index of its current one.
+//
+// Dataflow schedule: one persistent kernel per window.  Work is a stream of tickets (step, case, tile) taken in order from one
 // atomic counter; the order is step-major, so while the last tiles of one
 // step run, the first tiles of the next are already handed out.  A tile of
 // case c at step s may start once all tiles of case c at step s-1 are done

@@ -19,11 +19,14 @@
 //
 // Bound: 4096^2 FP32 spends 76 % of its time issuing vector instructions (225
 // per 64 nodes and step, the same count as the single step with its halo
-// work; 0.96 GB of HBM traffic per pair of steps instead of 1.8 GB).
+// work); a pair moves 1.36 GB to and from HBM instead of 2.42 GB.
 // Non-temporal stores, which the single step uses beyond the last-level
 // cache, are slower here (151 -> 184 us: the tiles' rows do not start on cache
-// lines and neighbours' partial lines merge in L2).  Three or more steps would
-// save traffic that no longer bounds it and add ring.
+// lines and neighbours' partial lines merge in L2).  Three or four steps
+// save traffic that no longer bounds a large lattice and add ring, and in a
+// small one a step inside the block costs 2.5-3 us at four wavefronts per SIMD
+// (32^2 FP64 2.75 us per step in pairs, 2.9-6.0 in threes and fours; 256^2 FP32
+// 2.68, 2.44-3.75).
 
 #include "lbm_kernels.h"
 
