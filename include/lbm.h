@@ -295,7 +295,8 @@ int lbm_batch_fields(lbm_batch* b, int32_t c, double* rho, double* ux, double* u
 /* Launch knobs of the batch (the autotuner's).  rows_per_item: block height
  * in wavefronts of one lattice row each, 4, 8 or 16 (0 = 4).  schedule:
  * 0 = one step kernel per time step over all active tiles, case after case,
- * a window of check_every steps captured into a HIP graph and replayed;
+ * a window of check_every steps captured into a HIP graph and replayed (plain
+ * steps run two per launch where that is faster, in tiles of their own);
  * 1 = the same with tiles interleaved across cases; 2 = one persistent
  * kernel per window in which each tile waits only for its own case's
  * previous step (per-case counters).  LBM_EINVAL for other values. */
