@@ -166,10 +166,22 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
         if (p >= a.npix) continue;
         float val = acc[s][b][v] + bias;
         if (a.relu) val = fmaxf(val, 0.f);
-        if (a.out_f32)
+        if (a.out_f32) {
           static_cast<float*>(a.y)[(long long)p * a.ldy + co] = val;
-        else
-          static_cast<bf16*>(a.y)[(long long)p * a.ldy + co] = (bf16)val;
+          continue;
+        }
+        bf16 o = (bf16)val;
+        if (a.mask && !((float)a.mask[(long long)p * a.ldmask + co] > 0.f)) o = (bf16)0.f;
+        bf16* out = static_cast<bf16*>(a.y) + co;
+        if (!a.up) {
+          out[(long long)p * a.ldy] = o;
+        } else {
+          const int x = p % a.wd, q = p / a.wd, y = q % a.h, img = q / a.h;
+#pragma unroll
+          for (int f = 0; f < 4; ++f)
+            out[(((long long)img * 2 * a.h + 2 * y + f / 2) * 2 * a.wd + 2 * x + f % 2) * a.ldy] =
+                o;
+        }
       }
     }
 }
@@ -661,6 +673,10 @@ int try_direct(const ConvArgs& a, hipStream_t st, bool* done) {
                 : try_direct_width<MP, NC, WP, WC, 32>(a, st, done);
 }
 
+__global__ void pool2_fwd_kernel(const bf16* x, int ldx, bf16* y, int ldy, int n, int h, int wd,
+                                 int cv);
+int grid_for(long long total);
+
 int launch_conv(ConvArgs a, hipStream_t st) {
   if (a.cin <= 0 || a.cout <= 0 || a.cin % 32 || a.cout % 32)
     return fail(UNET_EINVAL, "conv: cin and cout must be positive multiples of 32");
@@ -700,9 +716,8 @@ int launch_conv(ConvArgs a, hipStream_t st) {
     if (!rc && !done) rc = try_conv<1, 1, 4, 1>(a, st, &done);
     if (rc || done) return rc;
   }
-  // more input channels than LDS holds (none of the network's layers):
-  // operands straight from memory
-  if (a.mask || a.pool || a.up) return fail(UNET_EINVAL, "conv: no fused form of this size");
+  // an image of 2 GB, or more input channels than LDS holds (none of the
+  // network's layers): operands straight from memory
   if (a.cout % 64 == 0) {
     dim3 grid((a.npix + 63) / 64, a.cout / 64);
     hipLaunchKernelGGL(conv_fwd_kernel<2>, grid, dim3(256), 0, st, a);
@@ -711,6 +726,13 @@ int launch_conv(ConvArgs a, hipStream_t st) {
     hipLaunchKernelGGL(conv_fwd_kernel<1>, grid, dim3(256), 0, st, a);
   }
   UCHECK(hipGetLastError());
+  if (a.pool) {
+    const int n = a.npix / (a.h * a.wd);
+    hipLaunchKernelGGL(pool2_fwd_kernel, dim3(grid_for((long long)a.npix / 4 * (a.cout / 8))),
+                       dim3(256), 0, st, static_cast<const bf16*>(a.y), a.ldy, a.pool, a.ldpool, n,
+                       a.h, a.wd, a.cout / 8);
+    UCHECK(hipGetLastError());
+  }
   return UNET_OK;
 }
 

@@ -158,3 +158,82 @@ def test_mass_fix_and_maps_sizes(U, side):
         ref = R.fields_from_output(out, cp.astype(np.float64), solid)
         for g, r, tol in zip(got, ref, (2e-6, 1e-6, 1e-6)):
             np.testing.assert_allclose(host(g), r, rtol=0, atol=tol)
+
+
+def layered_gradients(U, params, x0, target, fluid):
+    """Weight gradients of all layers from the single-layer functions."""
+    import torch
+    lay, _ = R.param_layout()
+    ws = [params[w:w + 9 * ci * co].to(torch.bfloat16).reshape(co, 9, ci).contiguous()
+          for w, _, ci, co in lay]
+    bs = [params[b:b + co].contiguous() for _, b, _, co in lay]
+    xs, grads = {}, {}
+
+    def conv(k, x, relu=True):
+        xs[k] = x.contiguous()
+        return U.conv3x3_fwd(xs[k], ws[k], bs[k], lay[k][3], relu=relu, out_f32=not relu)
+
+    def back(k, dy, dx=True):
+        ci, co = lay[k][2:]
+        grads[k] = U.conv3x3_bwd_weight(dy, xs[k], ci, co)[0]
+        return U.conv3x3_bwd_data(dy, ws[k], ci) if dx else None
+
+    a0 = conv(0, x0)
+    e0 = conv(1, a0)
+    a1 = conv(2, U.pool2_fwd(e0))
+    e1 = conv(3, a1)
+    a2 = conv(4, U.pool2_fwd(e1))
+    e2 = conv(5, a2)
+    a3 = conv(6, U.pool2_fwd(e2))
+    b3 = conv(7, a3)
+    c2 = conv(8, torch.cat([U.up2_fwd(b3), e2], 3))
+    d2 = conv(9, c2)
+    c1 = conv(10, torch.cat([U.up2_fwd(d2), e1], 3))
+    d1 = conv(11, c1)
+    c0 = conv(12, torch.cat([U.up2_fwd(d1), e0], 3))
+    d0 = conv(13, c0)
+    _, dout = U.mse_loss(conv(14, d0, relu=False), target, fluid)
+    relu = lambda d, y: U.relu_bwd(d.contiguous(), y)   # noqa: E731
+    g = back(12, relu(back(13, relu(back(14, dout), d0)), c0))
+    s0, g = g[..., 64:], relu(U.up2_bwd(g[..., :64].contiguous()), d1)
+    g = back(10, relu(back(11, g), c1))
+    s1, g = g[..., 128:], relu(U.up2_bwd(g[..., :128].contiguous()), d2)
+    g = back(8, relu(back(9, g), c2))
+    s2, g = g[..., 256:], relu(U.up2_bwd(g[..., :256].contiguous()), b3)
+    g = back(6, relu(back(7, g), a3))
+    g = relu(U.pool2_bwd(g, s2.contiguous()), e2)
+    g = back(4, relu(back(5, g), a2))
+    g = relu(U.pool2_bwd(g, s1.contiguous()), e1)
+    g = back(2, relu(back(3, g), a1))
+    g = relu(U.pool2_bwd(g, s0.contiguous()), e0)
+    back(0, relu(back(1, g), a0), dx=False)
+    return grads
+
+
+@pytest.mark.parametrize("res,n", [(16, 2), (128, 3), (3360, 1)])
+def test_network_gradients_equal_its_layers(U, res, n):
+    """The backward pass (fused masks, grouped weight gradients, fragment
+    weights) against the single layers; 3360^2 has images of more than 2 GB in
+    the finest level, where every fused form takes the general kernel.  The
+    input gradients are the same bits, the weight gradients sum the same
+    products in FP32 over another split: 20 eps of the sum of absolute products
+    (chains of about 400 additions), taken as at most 800 largest entries."""
+    import torch
+    print("[gpu-case] network gradients", res, n, flush=True)
+    rng = np.random.default_rng(res)
+    net = U.UNet(max_batch=n, res=res, seed=6)
+    small = rng.standard_normal((n, 16, 16, 32))
+    rep = (res + 15) // 16
+    x0 = dev(R.bf16(np.tile(small, (1, rep, rep, 1))[:, :res, :res]), torch.bfloat16)
+    target = dev(np.tile(small[..., :3], (1, rep, rep, 1))[:, :res, :res], torch.float32)
+    fluid = torch.ones((n, res, res), dtype=torch.uint8, device="cuda")
+    params = dev(net.params(), torch.float32)
+    net.backward(x0, target, fluid)
+    got = net.grads()
+    want = layered_gradients(U, params, x0, target, fluid)
+    net.close()
+    lay, _ = R.param_layout()
+    for k, (w, _, ci, co) in enumerate(lay):
+        ref = want[k].float().cpu().numpy().reshape(-1)
+        err = np.abs(got[w:w + 9 * ci * co] - ref).max()
+        assert err <= 1e-3 * np.abs(ref).max(), (k, err, np.abs(ref).max())
