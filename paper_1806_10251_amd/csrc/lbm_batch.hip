@@ -714,6 +714,7 @@ int rebuild_items(lbm_batch* b) {
     hipFree(b->d_item_case);
     hipFree(b->d_item_tile);
     b->d_item_case = b->d_item_tile = nullptr;
+    b->item_cap = 0;
     HIPCHECK(hipMalloc(&b->d_item_case, sizeof(int) * b->n_items));
     HIPCHECK(hipMalloc(&b->d_item_tile, sizeof(int) * b->n_items));
     b->item_cap = b->n_items;
@@ -732,6 +733,7 @@ int rebuild_items(lbm_batch* b) {
     if (b->n_mitems > b->mitem_cap) {
       hipFree(b->d_mitems);
       b->d_mitems = nullptr;
+      b->mitem_cap = 0;
       HIPCHECK(hipMalloc(&b->d_mitems, sizeof(int2) * b->n_mitems));
       b->mitem_cap = b->n_mitems;
     }
