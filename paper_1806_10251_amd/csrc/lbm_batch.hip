@@ -6,17 +6,18 @@
 // (batch_multi_shape).  Launches, not steps, swap the two lattices, so the
 // batch keeps the index of its current one.
 //
-// Dataflow schedule: one persistent kernel per window.  Work is a stream of tickets (step, case, tile) taken in order from one
-// atomic counter; the order is step-major, so while the last tiles of one
-// step run, the first tiles of the next are already handed out.  A tile of
-// case c at step s may start once all tiles of case c at step s-1 are done
-// (a per-case completion counter): cases advance independently, with no
-// grid-wide barrier.  A block only ever waits for tickets that running blocks
-// already hold, so progress does not depend on co-residency; the wait is
-// bounded anyway (an error flag ends the launch).  The block that completes
-// a case's last tile of the window reduces, in a fixed order, that case's
-// residual partials and retires it when converged, stalled or diverged; the
-// host drops retired cases from the next window's ticket list.
+// Dataflow schedule: one persistent kernel per window.  Work is a stream of
+// tickets (step, case, tile) taken in order from one atomic counter; the order
+// is step-major, so while the last tiles of one step run, the first tiles of
+// the next are already handed out.  A tile of case c at step s may start once
+// all tiles of case c at step s-1 are done (a per-case completion counter):
+// cases advance independently, with no grid-wide barrier.  A block only ever
+// waits for tickets that running blocks already hold, so progress does not
+// depend on co-residency; the wait is bounded anyway (an error flag ends the
+// launch).  The block that completes a case's last tile of the window reduces,
+// in a fixed order, that case's residual partials and retires it when
+// converged, stalled or diverged; the host drops retired cases from the next
+// window's ticket list.
 //
 // All cases share one step counter and one storage type: FP32 or FP64
 // deviations.
@@ -514,9 +515,9 @@ int multi_inner(int n, int tiles, int len) {
 }
 
 // Shape of the two-step kernel for the active cases, or -1: as for a single
-// lattice, from the sum of their tiles, whatever the block height of the single
-// steps (256 FP32 cases with sides of 64 to 512, height 8: 1066 | 676 us).  Times per step, one step | two steps
-// per launch:
+// lattice, from the sum of their tiles, whatever the block height of the
+// single steps (256 FP32 cases with sides of 64 to 512, height 8: 1066 | 676
+// us).  Times per step, one step | two steps per launch:
 // - Up to one block per compute unit (or 512 of the 6-row blocks) the launch
 //   is what counts: 4 cavities 64^2 FP64 9.3 | 4.5 us, 20 of them 11.0 | 8.9,
 //   FP32 9.3 | 5.3.

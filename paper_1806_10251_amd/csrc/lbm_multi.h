@@ -244,11 +244,10 @@ constexpr size_t multi_lds() {
 }
 
 template <class S, int NW, int RPW, int T, bool OBST, bool OUTL, bool CL>
-__global__ __launch_bounds__(kLanes* NW, (multi_waves<S, NW, RPW>())) void multi_kernel(const typename S::T* __restrict__ fa,
-                                                           typename S::T* __restrict__ fb,
-                                                           const StepArgs args,
-                                                           const uint8_t* __restrict__ fluid,
-                                                           const Consts<typename S::C> k) {
+__global__ __launch_bounds__(kLanes* NW, (multi_waves<S, NW, RPW>()))
+void multi_kernel(const typename S::T* __restrict__ fa, typename S::T* __restrict__ fb,
+                  const StepArgs args, const uint8_t* __restrict__ fluid,
+                  const Consts<typename S::C> k) {
   using M = MultiTile<NW, RPW, T>;
   extern __shared__ __align__(16) char smem[];
   using F = typename S::T[NW * RPW - 2][kLanes];
