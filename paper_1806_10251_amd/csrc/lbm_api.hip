@@ -237,20 +237,21 @@ const void* consts_of(const lbm_ctx* c) {
 int enqueue_steps(lbm_ctx* c, int64_t left, hipStream_t st) {
   const int64_t idx = c->t + 1;
   const int flavor = flavor_of(c, idx);
-  StepArgs a = step_args(c);
+  const StepArgs a = step_args(c);
   const void* src = c->lat[c->cur];
   void* dst = c->lat[c->cur ^ 1];
   const void* k = consts_of(c);
   const int shape = c->multi;
   if (shape >= 0 && left > kMultiSteps && flavor == kPlain && flavor_of(c, idx + 1) == kPlain) {
-    a.tiles_x = multi_tiles_x(c);
-    a.ntiles = a.tiles_x * multi_tiles_y(c, shape);
+    StepArgs m = a;   // (a refused launch leaves the single step its own tiles)
+    m.tiles_x = multi_tiles_x(c);
+    m.ntiles = m.tiles_x * multi_tiles_y(c, shape);
     bool ok;
     switch (c->p.storage) {
-      case 0: ok = launch_multi<0>(shape, src, dst, a, c->d_fluid, k, st); break;
-      case 1: ok = launch_multi<1>(shape, src, dst, a, c->d_fluid, k, st); break;
-      case 2: ok = launch_multi<2>(shape, src, dst, a, c->d_fluid, k, st); break;
-      default: ok = launch_multi<3>(shape, src, dst, a, c->d_fluid, k, st); break;
+      case 0: ok = launch_multi<0>(shape, src, dst, m, c->d_fluid, k, st); break;
+      case 1: ok = launch_multi<1>(shape, src, dst, m, c->d_fluid, k, st); break;
+      case 2: ok = launch_multi<2>(shape, src, dst, m, c->d_fluid, k, st); break;
+      default: ok = launch_multi<3>(shape, src, dst, m, c->d_fluid, k, st); break;
     }
     if (ok) {
       c->cur ^= 1;

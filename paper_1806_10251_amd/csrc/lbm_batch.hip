@@ -854,8 +854,10 @@ bool launch_batch_multi(const lbm_batch* b, int par, hipStream_t st) {
   auto* fn = batch_multi_kernel<S, NW, RPW>;
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();   // (handled: single steps instead)
     return false;
+  }
   hipLaunchKernelGGL(fn, dim3(b->n_mitems), dim3(kLanes, NW), lds, st, b->d_cases, b->d_mitems,
                      par);
   return true;

@@ -33,8 +33,10 @@ bool go_kernel(const void* src, void* dst, const StepArgs& a, const uint8_t* flu
   auto* fn = multi_kernel<S, NW, RPW, kMultiSteps, OBST, OUTL, CL>;
   if (lds > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();   // (handled: the caller steps singly)
     return false;
+  }
   hipLaunchKernelGGL(fn, dim3(a.ntiles), dim3(kLanes, NW), lds, st, (const T*)src, (T*)dst, a,
                      fluid, k);
   return true;

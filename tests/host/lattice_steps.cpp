@@ -1,0 +1,51 @@
+// Host side of the lattice steps on the CPU: the queueing of steps with the
+// launches replaced by recorders (no device is touched).
+#include <hip/hip_runtime.h>
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(...) ((void)0)
+#include "../../paper_1806_10251_amd/csrc/lbm_api.hip"
+
+namespace lbmk {
+
+static StepArgs g_single;
+static int g_multi_calls;
+
+template <int ST, int FL>
+void launch_step(int, int, int, const void*, void*, const StepArgs& a, const void*, hipStream_t) {
+  g_single = a;
+}
+template <int ST>
+bool launch_multi(int, const void*, void*, const StepArgs&, const uint8_t*, const void*,
+                  hipStream_t) {
+  ++g_multi_calls;
+  return false;   // as where the device refuses the LDS
+}
+
+}  // namespace lbmk
+
+// A two-step launch that is refused: the single step that takes its place
+// covers the lattice with its own tiles.
+static int refused() {
+  static lbm_ctx c;
+  c.grid = lbm_grid{};
+  c.grid.nx = 200;
+  c.grid.ny = 100;
+  for (int i = 0; i < 4; ++i) c.grid.side[i] = LBM_SIDE_WALL;
+  c.p.check_every = 100;
+  c.p.storage = LBM_STORE_F32;
+  c.tiles_x = 4;
+  c.tiles_y = 25;
+  c.ntiles = 100;
+  c.out_rows = 4;
+  c.multi = 0;
+  const int taken = enqueue_steps(&c, 10, nullptr);
+  std::printf("%d %d %d %d %d %lld\n", taken, lbmk::g_multi_calls, lbmk::g_single.tiles_x,
+              lbmk::g_single.ntiles, c.cur, (long long)c.t);
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "refused") return refused();
+  return 2;
+}
