@@ -2,9 +2,11 @@
 
 Single lattice: every (block height, rows per thread) pair the library
 supports is timed on a scratch lattice of the same configuration with the
-library's own HIP-event timer; the fastest is cached per (nx, ny, storage,
-obstacles, outlet) in a JSON file ($LBM_TUNE_CACHE, default
-~/.cache/lbm_tune.json).
+library's own HIP-event timer; the fastest is cached in a JSON file
+($LBM_TUNE_CACHE, default ~/.cache/lbm_tune.json) under what decides which
+kernels run: size, storage, kinds of the sides, obstacles and their share,
+collision variant, and the revision of the kernels' sources, so that a choice
+made for other kernels is made again.
 
 Batch: block height (4, 8, 16 wavefronts) and schedule (graph of per-step
 kernels with tiles case after case or interleaved, or the persistent
@@ -12,6 +14,9 @@ dataflow kernel) are timed on a scratch batch of the same cases.
 """
 from __future__ import annotations
 
+import functools
+import glob
+import hashlib
 import json
 import os
 import time
@@ -46,16 +51,34 @@ def _save_cache(c):
         pass
 
 
-def lattice_key(nx, ny, sides, solid, storage):
-    has_solid = solid is not None and bool(np.asarray(solid).any())
-    return f"{nx}x{ny}:{storage}:obst{int(has_solid)}:outlet{int(sides[1] == L.OUTLET)}"
+@functools.lru_cache(maxsize=None)
+def kernel_revision():
+    """Hash of the sources the lattice kernels and their dispatch are built of."""
+    here = os.path.dirname(os.path.abspath(__file__))
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(here, "csrc", "lbm_*")) +
+                       [os.path.join(here, "build.py")]):
+        with open(path, "rb") as f:
+            h.update(os.path.basename(path).encode() + b"\0" + f.read())
+    return h.hexdigest()[:12]
+
+
+def lattice_key(nx, ny, sides, solid, storage, mrt=0, strain_fd=0):
+    """Everything the choice between the kernels (and between one and two
+    steps per launch) depends on."""
+    share = 0.0 if solid is None else float((np.asarray(solid) != 0).mean())
+    obst = f"obst{int(share > 0)}.{round(10 * share)}"
+    kinds = "".join(str(int(s)) for s in sides)
+    return (f"{nx}x{ny}:{storage}:{obst}:sides{kinds}:mrt{int(bool(mrt))}"
+            f":fd{int(bool(strain_fd))}:{kernel_revision()}")
 
 
 def tune_lattice(nx, ny, sides, solid=None, steps=400, warmup=100, use_cache=True, **params):
     """Fastest (by, rows) for this lattice configuration; returns
     (shape, {shape: us_per_step})."""
     storage = params.get("storage", "f32")
-    key = lattice_key(nx, ny, sides, solid, storage)
+    key = lattice_key(nx, ny, sides, solid, storage, params.get("mrt", 0),
+                      params.get("strain_fd", 0))
     cache = _load_cache() if use_cache else {}
     if key in cache:
         return tuple(cache[key]["shape"]), {tuple(json.loads(k)): v for k, v in
