@@ -137,7 +137,8 @@ long long multi_tiles(const lbm_ctx* c, int shape) {
 
 // Shape of the two-step kernel for this lattice, or -1 (step by step: the
 // variants, a launch shape other than the default, and where two steps at
-// once do not pay).  Times are per step, cavities, one step | two steps.
+// once do not pay).  Times are per step, cavities unless named otherwise, one
+// step | two steps.
 // - Up to one block per compute unit a launch costs its latency, whatever
 //   the size: the lowest blocks that still fit (2, 6, 10 output rows, one row
 //   per wavefront): 128^2 FP64 3.6 | 2.7 us, 256^2 FP32 3.4 | 2.6 us, 320^2
@@ -146,13 +147,43 @@ long long multi_tiles(const lbm_ctx* c, int shape) {
 // - Larger lattices: two rows per wavefront (10 output rows: 1024^2 FP32
 //   13.3 | 10.9, FP64 24.0 | 19.0 us, 2048^2 FP64 117 | 73.5 us); beyond the
 //   last-level cache, except in FP64 (registers), four rows (26 output rows:
-//   4096^2 FP32 264 | 151 us, channel 4096 x 1024 FP16 52.5 | 46.5 us).
-// - The ring costs instructions (1.2 to 1.4 times those of single steps).
-//   16-bit storages in cache are bound by theirs: beyond about 1.1 M nodes
-//   one step at a time is up to 3 % faster (1280^2 FP16 17.4 | 18.1 us, 2048^2
-//   38.1 | 38.8 us), except with a mask or an outlet, whose tests the
-//   two-step kernel leaves out where a tile has none.  Nor does it pay where
-//   the tiles fit the lattice badly (narrow strips).
+//   4096^2 FP32 264 | 158 us, channel 4096 x 1024 FP16 52.5 | 46.5 us).
+// - The ring costs instructions: the rows a pair collides over those of two
+//   single steps (work) are 1.1 to 1.4 where the tiles fit.  At 1.6 (59 to 64
+//   columns of 58 over 64, 175 to 192 of 3 x 58 over 3 x 64) every storage
+//   loses: 180 x 2000 FP16 6.6 | 8.4 us, FP32 6.8 | 7.3, FP64 11.1 | 13.0.
+//   FP64 has the least to spare: in small lattices up to 2 (64 x 1500 at 2.7:
+//   5.3 | 7.0 us), and tiles that are partly empty do not pay in strips of one
+//   or two tiles (80 x 4000 12.7 | 13.5 us with sides periodic in y) or where
+//   few compute units get a second block (129 x 1025 periodic 7.0 | 7.4 us);
+//   channels gain there all the same, their outlet being a serial chain
+//   (129 x 1025 13.7 | 10.0 us).
+// - 16-bit storages in cache are bound by instructions: beyond about 1.1 M
+//   nodes one step at a time is up to 3 % faster without an outlet (1280^2
+//   FP16 17.4 | 18.1 us, 2048^2 38.1 | 38.8 us), and up to 2.2 M nodes also
+//   with one in every 14th tile or fewer (1600 x 750 18.0 | 19.2 us; 2400 x
+//   1041 29.5 | 28.6), except with a mask, whose tests the two-step kernel
+//   leaves out where a tile has none (1600 x 750 20.5 | 20.2 us).
+struct MultiFit {
+  long long tiles;
+  double work, fill;   // fill: lattice nodes over output nodes of the tiles
+};
+MultiFit multi_fit(const lbm_ctx* c, int shape) {
+  const int nx = c->grid.nx, ny = c->grid.ny, nr = multi_rows(shape);
+  MultiFit f{multi_tiles(c, shape), 0, 0};
+  f.work = f.tiles * (2.0 * nr - 8.0) / (2.0 * ((nx + kLanes - 1) / kLanes) * ny);
+  f.fill = (double)nx * ny /
+           ((double)f.tiles * (kLanes - 2 * kMultiRing) * (nr - 2 * kMultiRing));
+  return f;
+}
+
+// 16-bit lattices in cache beyond 1.1 M nodes
+bool multi_big16(const lbm_ctx* c) {
+  const Geom g = make_geom(c);
+  return c->esize == 2 && 2 * 9 * (size_t)g.plane * c->esize <= kLastLevelCacheBytes &&
+         (long long)c->grid.nx * c->grid.ny > 1100000;
+}
+
 int multi_shape(const lbm_ctx* c) {
   if (c->by != 4 || c->rows != 1 || c->p.strain_fd || c->p.mrt) return -1;
   const int nx = c->grid.nx, ny = c->grid.ny;
@@ -163,33 +194,82 @@ int multi_shape(const lbm_ctx* c) {
   if (c->esize == 2 && (c->grid.side[0] == LBM_SIDE_PERIODIC ||
                         c->grid.side[2] == LBM_SIDE_PERIODIC))
     return -1;
-  for (int s = 0; s < 3; ++s)
-    if (multi_tiles(c, s) <= 256) return s;
-  if (multi_tiles(c, 1) <= 512) return 1;
+  const bool outlet = c->grid.side[1] == LBM_SIDE_OUTLET;
+  const bool tight = c->esize == 8 && !outlet;
+  int small = -1;
+  for (int s = 0; s < 3 && small < 0; ++s)
+    if (multi_tiles(c, s) <= 256) small = s;
+  if (small < 0 && multi_tiles(c, 1) <= 512) small = 1;
+  if (small >= 0) return tight && small > 0 && multi_fit(c, small).work > 2.0 ? -1 : small;
   const Geom g = make_geom(c);
   const bool cached = 2 * 9 * (size_t)g.plane * c->esize <= kLastLevelCacheBytes;
-  const bool big16 = c->esize == 2 && cached && (long long)nx * ny > 1100000;
-  if (big16 && !c->d_solid && c->grid.side[1] != LBM_SIDE_OUTLET) return -1;
+  const bool big16 = multi_big16(c);
+  if (big16 && !outlet) return -1;
   const int shape = (cached && !big16) || c->esize == 8 ? 3 : 4;
-  const int nr = multi_rows(shape);
-  const double rows = multi_tiles(c, shape) * (2.0 * nr - 8.0);   // collided, both steps
-  if (rows > 1.6 * 2.0 * ((nx + kLanes - 1) / kLanes) * ny) return -1;
+  const MultiFit f = multi_fit(c, shape);
+  if (f.work > 1.55) return -1;
+  if (big16 && (f.work > 1.25 || (!c->d_solid && f.work > 1.15 && multi_tiles_x(c) >= 14 &&
+                                  (long long)nx * ny < 2200000)))
+    return -1;
+  if (tight && f.fill < 0.85 && (multi_tiles_x(c) <= 2 || f.tiles <= 384)) return -1;
   return shape;
 }
 
+// The share of the regions' rows that may be near a solid node (a row with one
+// or next to one takes the tests of every neighbour, in the single step as
+// well, but the ring's rows too).  Dots on a share of the lattice, per step,
+// one step | two steps, at these shares:
+// - channels always gain (1024^2 FP64 with all rows 38.6 | 35.5 us), 16-bit ones
+//   in cache beyond 1.1 M nodes up to a quarter (2048^2 FP16 at 0.16 57.1 | 52.1,
+//   at 0.40 57.9 | 59.0);
+// - FP64 beyond one block per compute unit: 0.15 (512^2 at 0.14 9.5 | 9.3,
+//   0.18 9.6 | 9.9; 1024^2 periodic at 0.15 25.3 | 25.1, 0.17 25.1 | 25.5),
+//   closed lattices of more tiles 0.5 (1024^2 at 0.41 27.1 | 25.7, at 0.89 28.4 |
+//   29.4), and 0.4 where a lattice one tile wide takes two of the two-step tiles
+//   (64^2 at 0.29 4.3 | 3.3, 0.46 4.3 | 4.5);
+// - FP32: any (1024^2, all rows 17.5 | 15.7), except 0.2 with periodic sides in
+//   cache beyond 1.1 M nodes (1500^2 at 0.15 25.1 | 24.5, 0.41 25.9 | 27.1) and
+//   0.05 where few compute units get a second, partly empty block (129 x 1025
+//   at 0.02 5.1 | 4.9, 0.16 5.2 | 5.7);
+// - 16 bits: 0.05 beyond two rounds of small blocks (1024^2 FP16 at 0.03 14.0 |
+//   13.7, 0.17 14.2 | 14.9).
+double multi_near_share(const lbm_ctx* c, int shape) {
+  const MultiFit f = multi_fit(c, shape);
+  const int32_t* sd = c->grid.side;
+  if (sd[1] == LBM_SIDE_OUTLET) return multi_big16(c) ? 0.25 : 1.0;
+  bool closed = true;
+  for (int q = 0; q < 4; ++q)
+    closed = closed && (sd[q] == LBM_SIDE_WALL || sd[q] == LBM_SIDE_LID);
+  if (c->esize == 8) {
+    if (f.tiles > 256) return closed && f.tiles > 512 ? 0.5 : 0.15;
+    return closed && f.work > 3.0 ? 0.4 : 1.0;
+  }
+  if (shape < 3) return 1.0;
+  if (c->esize == 2 || (f.fill < 0.85 && f.tiles <= 512)) return 0.05;
+  return shape == 3 && !closed && (long long)c->grid.nx * c->grid.ny > 1100000 ? 0.2 : 1.0;
+}
+
 // fluid[tile] = 1 where the region of the tile (64 x nr nodes from (x0, y0),
-// inside the lattice) holds no solid node; one wavefront per tile.
+// inside the lattice) holds no solid node, and near[tile]: its rows with a solid
+// node in them or in the row above or below; one wavefront per tile, nr <= 32.
 __global__ __launch_bounds__(kLanes) void multi_fluid_kernel(const uint8_t* __restrict__ solid,
                                                              int nx, int ny, int tiles_x, int txo,
                                                              int tyo, int h, int nr,
-                                                             uint8_t* __restrict__ fluid) {
+                                                             uint8_t* __restrict__ fluid,
+                                                             uint8_t* __restrict__ near) {
   const int tile = blockIdx.x, x = tile % tiles_x * txo - h + int(threadIdx.x);
   const int y0 = tile / tiles_x * tyo - h;
-  int any = 0;
-  if (x >= 0 && x < nx)
-    for (int y = y0 < 0 ? 0 : y0; y < y0 + nr && y < ny; ++y) any |= solid[y * nx + x];
-  const bool some = __builtin_amdgcn_ballot_w64(any != 0) != 0;
-  if (threadIdx.x == 0) fluid[tile] = some ? 0 : 1;
+  unsigned rows = 0;
+  for (int r = 0; r < nr; ++r) {
+    const int y = y0 + r;
+    const bool s = x >= 0 && x < nx && y >= 0 && y < ny && solid[y * nx + x];
+    rows |= __builtin_amdgcn_ballot_w64(s) != 0 ? 1u << r : 0u;
+  }
+  if (threadIdx.x != 0) return;
+  fluid[tile] = rows ? 0 : 1;
+  rows |= rows << 1 | rows >> 1;
+  if (nr < 32) rows &= (1u << nr) - 1;
+  near[tile] = uint8_t(__builtin_popcount(rows));
 }
 
 // Choose the two-step shape of the current configuration and mark its tiles
@@ -198,12 +278,20 @@ __global__ __launch_bounds__(kLanes) void multi_fluid_kernel(const uint8_t* __re
 int configure_multi(lbm_ctx* c) {
   c->multi = multi_shape(c);
   if (c->multi < 0 || !c->d_solid) return LBM_OK;
-  const int tx = multi_tiles_x(c), n = tx * multi_tiles_y(c, c->multi);
+  const int tx = multi_tiles_x(c), n = tx * multi_tiles_y(c, c->multi), nr = multi_rows(c->multi);
+  uint8_t* d_near = c->d_fluid + n;
   hipLaunchKernelGGL(multi_fluid_kernel, dim3(n), dim3(kLanes), 0, c->stream, c->d_solid,
-                     c->grid.nx, c->grid.ny, tx, kLanes - 2 * kMultiRing,
-                     multi_rows(c->multi) - 2 * kMultiRing, kMultiRing, multi_rows(c->multi),
-                     c->d_fluid);
+                     c->grid.nx, c->grid.ny, tx, kLanes - 2 * kMultiRing, nr - 2 * kMultiRing,
+                     kMultiRing, nr, c->d_fluid, d_near);
   HIPCHECK(hipGetLastError());
+  const double allowed = multi_near_share(c, c->multi);
+  if (allowed >= 1.0) return LBM_OK;
+  std::vector<uint8_t> near(n);
+  HIPCHECK(hipMemcpyAsync(near.data(), d_near, n, hipMemcpyDeviceToHost, c->stream));
+  HIPCHECK(hipStreamSynchronize(c->stream));
+  long long rows = 0;
+  for (uint8_t v : near) rows += v;
+  if (rows > allowed * n * nr) c->multi = -1;
   return LBM_OK;
 }
 
@@ -464,9 +552,9 @@ int lbm_create(const lbm_grid* grid, const uint8_t* solid_mask, const lbm_params
     if (any) {
       c->h_solid.assign(solid_mask, solid_mask + n);
       for (auto& v : c->h_solid) v = v ? 1 : 0;
-      // followed by one byte per tile of the two-step kernel (two output rows
+      // followed by two bytes per tile of the two-step kernel (two output rows
       // or more each)
-      ok = dev(hipMalloc(&c->d_solid, n + (size_t)multi_tiles(c, 0)), "hipMalloc mask") &&
+      ok = dev(hipMalloc(&c->d_solid, n + 2 * (size_t)multi_tiles(c, 0)), "hipMalloc mask") &&
            dev(hipMemcpy(c->d_solid, c->h_solid.data(), n, hipMemcpyHostToDevice), "copy mask");
       c->d_fluid = c->d_solid + n;
     }

@@ -44,8 +44,25 @@ static int refused() {
   return 0;
 }
 
+// shape of the two-step kernel and allowed share of rows near solid nodes:
+// nx ny W E S N storage mask
+static int shape(char** v) {
+  static lbm_ctx c;
+  static uint8_t solid;
+  c.grid.nx = std::atoi(v[0]);
+  c.grid.ny = std::atoi(v[1]);
+  for (int i = 0; i < 4; ++i) c.grid.side[i] = std::atoi(v[2 + i]);
+  c.p.storage = std::atoi(v[6]);
+  c.esize = storage_bytes(c.p.storage);
+  c.d_solid = std::atoi(v[7]) ? &solid : nullptr;
+  const int s = multi_shape(&c);
+  std::printf("%d %g\n", s, s < 0 ? 0.0 : multi_near_share(&c, s));
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "refused") return refused();
+  if (what == "shape" && argc == 10) return shape(argv + 2);
   return 2;
 }

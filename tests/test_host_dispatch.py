@@ -40,3 +40,51 @@ def program(tmp_path_factory):
 def test_refused_two_step_launch_falls_back_to_whole_single_steps(program):
     """200 x 100 nodes in single-step tiles of 64 x 4: 4 columns, 100 tiles."""
     assert program("lattice_steps", "refused") == [["1", "1", "4", "100", "1", "1"]]
+
+
+CAVITY, CHANNEL, MILL, DUCT, COUETTE = ((1, 1, 1, 2), (3, 4, 1, 1), (0, 0, 0, 0), (0, 0, 1, 1),
+                                        (2, 1, 0, 0))
+F64, F32, BF16, F16 = range(4)
+ONE_BY_ONE = -1
+
+
+@pytest.mark.parametrize("nx,ny,sides,storage,mask,shape,share", [
+    # small: the lowest blocks that fit, whatever the mask
+    (32, 32, CAVITY, F64, 0, 0, 1.0), (256, 256, CAVITY, F32, 1, 1, 1.0),
+    (251, 251, MILL, F64, 0, 1, 1.0), (300, 300, CAVITY, F16, 1, 2, 1.0),
+    (384, 384, CAVITY, F32, 0, 1, 1.0), (400, 400, CAVITY, F16, 1, 1, 1.0),
+    # FP64 where two of the two-step tiles stand for one
+    (128, 128, CAVITY, F64, 0, 0, 1.0), (64, 64, CAVITY, F64, 1, 0, 0.4),
+    (64, 64, MILL, F64, 1, 0, 1.0), (64, 1000, CAVITY, F64, 0, ONE_BY_ONE, 0),
+    (64, 1500, MILL, F64, 0, ONE_BY_ONE, 0), (64, 1500, CHANNEL, F64, 0, 1, 1.0),
+    (64, 1000, CAVITY, F32, 0, 2, 1.0), (70, 1000, CAVITY, F64, 0, 2, 1.0),
+    # larger: the ring's work
+    (1024, 1024, CAVITY, F32, 0, 3, 1.0), (1024, 1024, CAVITY, F64, 1, 3, 0.5),
+    (1024, 1024, MILL, F64, 1, 3, 0.15), (512, 512, CAVITY, F64, 1, 3, 0.15),
+    (4096, 4096, CAVITY, F32, 0, 4, 1.0), (2048, 2048, CAVITY, F64, 0, 3, 0.5),
+    (180, 2000, CAVITY, F32, 0, ONE_BY_ONE, 0), (190, 1500, CHANNEL, F16, 0, ONE_BY_ONE, 0),
+    (180, 1000, MILL, F64, 0, ONE_BY_ONE, 0), (200, 2000, CAVITY, F64, 0, 3, 0.5),
+    (250, 1025, CAVITY, F32, 0, 3, 1.0),
+    # FP64 in partly empty tiles
+    (129, 1025, MILL, F64, 0, ONE_BY_ONE, 0), (129, 1025, CHANNEL, F64, 1, 3, 1.0),
+    (129, 2000, MILL, F64, 0, 3, 0.15), (16, 4000, COUETTE, F64, 0, ONE_BY_ONE, 0),
+    (80, 4000, COUETTE, F64, 0, ONE_BY_ONE, 0), (116, 4000, COUETTE, F64, 0, 3, 0.15),
+    (129, 1025, CAVITY, F32, 1, 3, 0.05), (16, 4000, CAVITY, F32, 1, 3, 0.05), (450, 450, CAVITY, F64, 0, 3, 0.15),
+    # FP32 periodic in cache
+    (1500, 1500, MILL, F32, 1, 3, 0.2), (1500, 1500, CAVITY, F32, 1, 3, 1.0),
+    (2048, 2048, DUCT, F32, 1, 4, 1.0),
+    # 16 bits
+    (128, 128, MILL, F16, 0, ONE_BY_ONE, 0), (1024, 1024, CAVITY, BF16, 1, 3, 0.05),
+    (1500, 1500, CAVITY, F16, 0, ONE_BY_ONE, 0), (1500, 1500, CAVITY, F16, 1, ONE_BY_ONE, 0),
+    (4096, 4096, CAVITY, F16, 0, 4, 0.05), (1600, 750, CHANNEL, F16, 0, ONE_BY_ONE, 0),
+    (1600, 750, CHANNEL, F16, 1, 4, 0.25), (400, 3000, CHANNEL, F16, 0, 4, 0.25),
+    (300, 4000, CHANNEL, F16, 1, ONE_BY_ONE, 0), (2400, 1041, CHANNEL, F16, 0, 4, 0.25),
+    (4096, 1024, CHANNEL, F16, 1, 4, 0.25),
+    # never
+    (15, 400, CAVITY, F32, 0, ONE_BY_ONE, 0), (4000, 15, CAVITY, F64, 0, ONE_BY_ONE, 0),
+])
+def test_two_step_shape(program, nx, ny, sides, storage, mask, shape, share):
+    """Where two steps per launch were measured slower the lattice steps one by
+    one; the share of rows near solid nodes up to which they pay."""
+    (got,) = program("lattice_steps", "shape", nx, ny, *sides, storage, mask)
+    assert (int(got[0]), float(got[1])) == (shape, share)
