@@ -1,0 +1,128 @@
+// Host side of a batch on the CPU: device memory from malloc, launches and
+// copies replaced by recorders.
+#include <chrono>
+#include <condition_variable>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <mutex>
+#include <set>
+#include <string>
+#include <thread>
+#include <tuple>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+#include "no_device.h"
+
+namespace rec {
+
+std::mutex mu;
+std::condition_variable cv;
+std::set<char*> live;         // allocations
+int uploads = 0, waiting = 0, meet = 0;
+bool stale = false;           // a copy from memory that was given back
+thread_local char* exported;  // destination of this thread's last export
+std::vector<char*> exports;
+
+hipError_t alloc(void** p, size_t n) {
+  std::lock_guard<std::mutex> l(mu);
+  *p = std::malloc(n + 64);
+  live.insert((char*)*p);
+  return hipSuccess;
+}
+hipError_t give_back(void* p) {
+  std::lock_guard<std::mutex> l(mu);
+  live.erase((char*)p);       // (kept by malloc: addresses stay distinct)
+  return hipSuccess;
+}
+hipError_t copy(void* dst, const void* src, size_t n, hipMemcpyKind kind) {
+  std::lock_guard<std::mutex> l(mu);
+  if (kind == hipMemcpyHostToDevice) {
+    ++uploads;
+    std::memcpy(dst, src, n);
+  } else if (exported && src >= exported && !live.count(exported)) {
+    stale = true;
+  }
+  return hipSuccess;
+}
+// Waits until `meet` threads are here, two seconds at most.
+hipError_t sync() {
+  std::unique_lock<std::mutex> l(mu);
+  ++waiting;
+  cv.notify_all();
+  cv.wait_for(l, std::chrono::seconds(2), [] { return waiting >= meet; });
+  return hipSuccess;
+}
+template <class... A>
+void launch(A... a) {
+  if constexpr (sizeof...(A) == 14) {   // export_kernel: the last three are the outputs
+    std::lock_guard<std::mutex> l(mu);
+    exported = (char*)std::get<11>(std::tuple<A...>(a...));
+    exports.push_back(exported);
+  }
+}
+
+}  // namespace rec
+
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(fn, grid, block, lds, st, ...) rec::launch(__VA_ARGS__)
+#define hipMalloc(p, n) rec::alloc((void**)(p), n)
+#define hipFree(p) rec::give_back(p)
+#define hipMemcpy(d, s, n, k) rec::copy(d, s, n, k)
+#define hipStreamSynchronize(s) rec::sync()
+#include "../../paper_1806_10251_amd/csrc/lbm_batch.hip"
+
+namespace lbmh {
+int fail(int code, const std::string& msg) {
+  std::fprintf(stderr, "%s\n", msg.c_str());
+  return code;
+}
+}  // namespace lbmh
+extern "C" const char* lbm_last_error(void) { return ""; }
+
+// Cases "nx ny W E S N solid" (solid: every solid-th node, 0 none).
+static void add_case(lbm_batch& b, char** v) {
+  HostCase c;
+  c.grid = lbm_grid{};
+  c.grid.nx = std::atoi(v[0]);
+  c.grid.ny = std::atoi(v[1]);
+  for (int i = 0; i < 4; ++i) c.grid.side[i] = std::atoi(v[2 + i]);
+  c.g = make_geom_for(c.grid.nx, c.grid.ny, c.grid.side, b.storage == LBM_STORE_F64 ? 8 : 4);
+  c.h_mask.assign((size_t)c.grid.nx * c.grid.ny, 0);
+  if (const int every = std::atoi(v[6]))
+    for (size_t i = 0; i < c.h_mask.size(); i += every) c.h_mask[i] = 1;
+  b.cs.push_back(c);
+  ++b.n;
+  b.enabled.push_back(1);
+  b.h_active.push_back(1);
+}
+
+// Two threads read the fields of two cases at the same time.
+static int fields() {
+  static lbm_batch b;
+  b.storage = LBM_STORE_F32;
+  char* v[] = {(char*)"40", (char*)"30", (char*)"1", (char*)"1", (char*)"1", (char*)"2", (char*)"0"};
+  add_case(b, v);
+  v[0] = (char*)"80";
+  add_case(b, v);
+  rec::meet = 2;
+  std::vector<double> out[2];
+  std::thread t[2];
+  for (int i = 0; i < 2; ++i)
+    t[i] = std::thread([&, i] {
+      out[i].resize(80 * 30);
+      lbm_batch_fields(&b, i, out[i].data(), nullptr, nullptr);
+    });
+  for (auto& x : t) x.join();
+  std::printf("%d %d %d\n", (int)rec::exports.size(), rec::exports[0] != rec::exports[1],
+              (int)rec::stale);
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "fields") return fields();
+  return 2;
+}

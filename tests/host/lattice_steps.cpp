@@ -1,6 +1,9 @@
 // Host side of the lattice steps on the CPU: the queueing of steps with the
 // launches replaced by recorders (no device is touched).
 #include <hip/hip_runtime.h>
+
+#include "no_device.h"
+
 #undef hipLaunchKernelGGL
 #define hipLaunchKernelGGL(...) ((void)0)
 #include "../../paper_1806_10251_amd/csrc/lbm_api.hip"

@@ -172,3 +172,21 @@ def test_batch_reports_diverging_case(lbm):
     assert b.diverged
     assert steps[2] < 0
     assert steps[0] > 0 and steps[1] > 0 and steps[0] < 30000 and steps[1] < 30000
+
+
+def test_fields_of_cases_read_by_threads(lbm):
+    """Several threads read the cases of one batch at the same time: the values
+    of one thread reading alone."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    cases = small_cases()
+    _say("batch fields by threads")
+    b = make_batch(lbm, cases)
+    b.run(0.0, 150)
+    want = [b.fields(i, c["ny"], c["nx"]) for i, c in enumerate(cases)]
+    with ThreadPoolExecutor(4) as ex:
+        got = list(ex.map(lambda k: b.fields(k % len(cases), cases[k % len(cases)]["ny"],
+                                             cases[k % len(cases)]["nx"]), range(40)))
+    for k, fields in enumerate(got):
+        for p, q in zip(fields, want[k % len(cases)]):
+            np.testing.assert_array_equal(p, q)
