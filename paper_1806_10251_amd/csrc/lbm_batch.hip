@@ -411,6 +411,8 @@ struct lbm_batch {
   int multi = -1;       // shape of the two-step kernel, -1: step by step
   int2* d_mitems = nullptr;   // its items (case, tile and interior bit)
   int n_mitems = 0, mitem_cap = 0;
+  int mitems_shape = -1;             // shape and active cases the device's items are
+  std::vector<int> mitems_active;    // for (built again when either changes)
   double* d_stage = nullptr;   // staging of lbm_batch_fields (see there)
   size_t stage_bytes = 0;
   std::mutex stage_mutex;
@@ -557,39 +559,47 @@ int batch_multi_shape(lbm_batch* b) {
   return 4 * inner >= tiles[shape] ? shape : -1;
 }
 
-// Cost of an item of the two-step kernel relative to the others (12 FP64 cases
-// with sides of 64 to 128, channels among them: 17.3 us per step with equal
-// weights, 13.8 with these, 14.9 with 2 : 3 : 4).
-int multi_weight(const lbm_batch* b, const int2& it) {
-  if ((unsigned(it.y) >> kInteriorBit) & 1) return 1;
-  const HostCase& c = b->cs[it.x];
-  const int tx = multi_tiles_x(c);
-  return c.grid.side[1] == LBM_SIDE_OUTLET && (it.y & kTileMask) % tx == tx - 1 ? 3 : 2;
-}
-
-// The items (case by case) in launch order.  Block i runs on XCD i mod 8: every
-// XCD gets a contiguous range of about the same cost, so that neighbouring
+// Items of the two-step kernel in launch order.  Block i runs on XCD i mod 8:
+// every XCD gets a contiguous range of about the same cost, so that neighbouring
 // tiles share its L2, the dearest items first, so that the last blocks are
 // short ones.  Ranges that end earlier are padded with empty items (case -1).
-std::vector<int2> multi_launch_order(const lbm_batch* b, const std::vector<int2>& items) {
+// Cost relative to the others: interior 1, boundary 2, with the outlet column 3
+// (12 FP64 cases with sides of 64 to 128, channels among them: 17.3 us per step
+// with equal weights, 13.8 with these, 14.9 with 2 : 3 : 4).  Linear in the
+// items, as it is host time of a run (64 cases, about 13 000 items).
+std::vector<int2> multi_items(lbm_batch* b) {
+  std::vector<int2> items;
+  std::vector<uint8_t> cost;
   long long total = 0;
-  for (const int2& it : items) total += multi_weight(b, it);
-  std::vector<int2> part[8];
-  long long sum = 0;
-  for (const int2& it : items) {
-    part[std::min<long long>(7, sum * 8 / total)].push_back(it);
-    sum += multi_weight(b, it);
+  for (int i = 0; i < b->n; ++i) {
+    if (!b->h_active[i]) continue;
+    const std::vector<uint8_t>& f = multi_interior(b->cs[i], b->multi);
+    const int tx = multi_tiles_x(b->cs[i]);
+    const bool outlet = b->cs[i].grid.side[1] == LBM_SIDE_OUTLET;
+    for (int t = 0, x = 0; t < (int)f.size(); ++t, x = x + 1 == tx ? 0 : x + 1) {
+      items.push_back(int2{i, t | (int(f[t]) << kInteriorBit)});
+      cost.push_back(f[t] ? 1 : outlet && x == tx - 1 ? 3 : 2);
+      total += cost.back();
+    }
   }
-  size_t longest = 0;
-  for (auto& v : part) {
-    std::stable_sort(v.begin(), v.end(), [&](const int2& p, const int2& q) {
-      return multi_weight(b, p) > multi_weight(b, q);
-    });
-    longest = std::max(longest, v.size());
+  // count per range and cost, then place in the order of the list
+  std::vector<uint8_t> range(items.size());
+  size_t count[8][4] = {}, at[8][4], longest = 0;
+  long long sum = 0;
+  for (size_t i = 0; i < items.size(); ++i) {
+    range[i] = uint8_t(std::min<long long>(7, sum * 8 / total));
+    ++count[range[i]][cost[i]];
+    sum += cost[i];
+  }
+  for (int k = 0; k < 8; ++k) {
+    at[k][3] = 0;
+    at[k][2] = count[k][3];
+    at[k][1] = at[k][2] + count[k][2];
+    longest = std::max(longest, at[k][1] + count[k][1]);
   }
   std::vector<int2> out(8 * longest, int2{-1, 0});
-  for (size_t k = 0; k < 8; ++k)
-    for (size_t i = 0; i < part[k].size(); ++i) out[8 * i + k] = part[k][i];
+  for (size_t i = 0; i < items.size(); ++i)
+    out[8 * at[range[i]][cost[i]]++ + range[i]] = items[i];
   return out;
 }
 
@@ -664,7 +674,8 @@ void drop_graphs(lbm_batch* b) {
     }
 }
 
-int rebuild_items(lbm_batch* b) {
+// left: steps still to take.
+int rebuild_items(lbm_batch* b, int64_t left) {
   drop_graphs(b);
   // ticket order within a step: schedule 0 = case by case (a case's tiles
   // contiguous), 1 = tiles interleaved across cases
@@ -722,16 +733,12 @@ int rebuild_items(lbm_batch* b) {
     HIPCHECK(hipMalloc(&b->d_item_tile, sizeof(int) * b->n_items));
     b->item_cap = b->n_items;
   }
-  b->multi = batch_multi_shape(b);
-  if (b->multi >= 0) {
-    std::vector<int2> mi;
-    for (int i = 0; i < b->n; ++i) {
-      if (!b->h_active[i]) continue;
-      const std::vector<uint8_t>& f = multi_interior(b->cs[i], b->multi);
-      for (size_t t = 0; t < f.size(); ++t)
-        mi.push_back(int2{i, int(t) | (int(f[t]) << kInteriorBit)});
-    }
-    mi = multi_launch_order(b, mi);
+  // (a run or window without two plain steps in a row before its last one has no
+  // pairs: its items would be built for nothing)
+  b->multi = left > kMultiSteps && b->K >= kMultiSteps + 2 ? batch_multi_shape(b) : -1;
+  if (b->multi >= 0 && (b->multi != b->mitems_shape || b->h_active != b->mitems_active)) {
+    b->mitems_shape = -1;
+    const std::vector<int2> mi = multi_items(b);
     b->n_mitems = (int)mi.size();
     if (b->n_mitems > b->mitem_cap) {
       hipFree(b->d_mitems);
@@ -741,6 +748,8 @@ int rebuild_items(lbm_batch* b) {
       b->mitem_cap = b->n_mitems;
     }
     HIPCHECK(hipMemcpy(b->d_mitems, mi.data(), sizeof(int2) * b->n_mitems, hipMemcpyHostToDevice));
+    b->mitems_shape = b->multi;
+    b->mitems_active = b->h_active;
   }
   if (b->n_items) {
     HIPCHECK(hipMemcpy(b->d_item_case, ic.data(), sizeof(int) * b->n_items, hipMemcpyHostToDevice));
@@ -1126,7 +1135,7 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
                           b->stream));
   HIPCHECK(hipMemsetAsync(b->d_err, 0, sizeof(int), b->stream));
   const int64_t t_start = b->t;
-  int rc = rebuild_items(b);
+  int rc = rebuild_items(b, max_steps);
   if (rc) return rc;
   const RetireArgs ret = retire_args(b, tol, t_start + 2LL * b->K);
   {
@@ -1210,7 +1219,7 @@ int lbm_batch_run(lbm_batch* b, double tol, int64_t max_steps, int64_t* steps_pe
         for (int i = 0; i < n; ++i)
           if (b->h_active[i] && !act[i]) b->cs[i].state_par = b->par;
         b->h_active = act;
-        rc = rebuild_items(b);
+        rc = rebuild_items(b, left);
         if (rc) return rc;
       }
       active_n = now;

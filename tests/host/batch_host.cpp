@@ -1,5 +1,6 @@
 // Host side of a batch on the CPU: device memory from malloc, launches and
 // copies replaced by recorders.
+#include <algorithm>
 #include <chrono>
 #include <condition_variable>
 #include <cstdio>
@@ -121,8 +122,59 @@ static int fields() {
   return 0;
 }
 
+// Item lists over runs of the given lengths (a negative length drops case 0):
+// shape, items and uploads so far after each.  Then the launch order of the
+// last list: every item once, ranges of equal cost, dearest first.
+static int items(int argc, char** argv) {
+  static lbm_batch b;
+  b.storage = LBM_STORE_F64;
+  b.K = std::atoi(argv[0]);
+  char* cavity[] = {(char*)"190", (char*)"200", (char*)"1", (char*)"1", (char*)"1", (char*)"2",
+                    (char*)"977"};
+  char* channel[] = {(char*)"400", (char*)"260", (char*)"3", (char*)"4", (char*)"1", (char*)"1",
+                     (char*)"0"};
+  for (int i = 0; i < 4; ++i) {
+    add_case(b, cavity);
+    add_case(b, channel);
+  }
+  if (configure(&b)) return 1;
+  for (int i = 1; i < argc; ++i) {
+    int left = std::atoi(argv[i]);
+    if (left < 0) {
+      b.h_active[0] = 0;
+      left = -left;
+    }
+    rec::uploads = 0;
+    if (rebuild_items(&b, left)) return 1;
+    std::printf("%d %d %d\n", b.multi, b.n_mitems, rec::uploads);
+  }
+  std::set<std::pair<int, int>> seen;
+  long long cost[8] = {}, dear = 0;
+  for (int k = 0; k < 8; ++k) {
+    int last = 3;
+    for (int i = k; i < b.n_mitems; i += 8) {
+      const int2 it = b.d_mitems[i];
+      if (it.x < 0) continue;
+      seen.insert({it.x, it.y & kTileMask});
+      const HostCase& c = b.cs[it.x];
+      const int tx = multi_tiles_x(c), x = (it.y & kTileMask) % tx;
+      const int w = it.y >> kInteriorBit & 1 ? 1 : it.x % 2 && x == tx - 1 ? 3 : 2;
+      if (w > last) ++dear;
+      last = w;
+      cost[k] += w;
+    }
+  }
+  long long want = 0;
+  for (int i = 0; i < b.n; ++i)
+    if (b.h_active[i]) want += (long long)multi_tiles_x(b.cs[i]) * multi_tiles_y(b.cs[i], b.multi);
+  std::printf("%d %lld %d\n", seen.size() == (size_t)want, dear,
+              *std::max_element(cost, cost + 8) - *std::min_element(cost, cost + 8) <= 6);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "fields") return fields();
+  if (what == "items" && argc > 3) return items(argc - 2, argv + 2);
   return 2;
 }

@@ -96,3 +96,19 @@ def test_fields_read_by_two_threads_have_staging_of_their_own(program):
     """Two threads inside lbm_batch_fields of one batch at the same time: two
     exports, to different memory, and no copy from memory given back."""
     assert program("batch_host", "fields") == [["2", "1", "0"]]
+
+
+def test_two_step_items_are_built_for_runs_that_use_them(program):
+    """Runs of one and two steps, and windows without two plain steps in a row,
+    build no list; a list stays until the cases or the shape change."""
+    got = [list(map(int, r)) for r in program("batch_host", "items", 100, 1, 2, 3, 100, 2, 50,
+                                              -100, 1, 100)]
+    runs, (every_item, out_of_order, even) = got[:-1], got[-1]
+    shapes, uploads = [r[0] for r in runs], [r[2] for r in runs]
+    s = shapes[2]
+    assert s >= 0 and shapes == [-1, -1, s, s, -1, s, s, -1, s]
+    assert uploads == [2, 2, 3, 2, 2, 2, 3, 2, 2]
+    assert runs[3][1] == runs[5][1] > runs[6][1]
+    assert (every_item, out_of_order, even) == (1, 0, 1)
+    assert [int(r[0]) for r in program("batch_host", "items", 3, 3, 30)[:2]] == [-1, -1]
+    assert [int(r[0]) for r in program("batch_host", "items", 4, 3)[:1]] == [s]
