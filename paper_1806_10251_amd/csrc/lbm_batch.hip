@@ -387,7 +387,7 @@ struct HostCase {
 
 }  // namespace
 
-constexpr size_t kKeptStage = 64ull << 20;
+constexpr size_t kKeptStageMin = 1ull << 20, kKeptStage = 64ull << 20;
 
 struct lbm_batch {
   std::vector<HostCase> cs;
@@ -1361,13 +1361,13 @@ int lbm_batch_fields(lbm_batch* b, int32_t ci, double* rho, double* ux, double* 
   if (!b || ci < 0 || ci >= b->n) return fail(LBM_EINVAL, "bad batch or case index");
   HostCase& c = b->cs[ci];
   const size_t np = (size_t)c.grid.nx * c.grid.ny;
-  // Staging of up to kKeptStage bytes stays with the batch (512 x 512 nodes: 610
-  // us per call with an allocation of its own, 535 without; below 256 x 256 no
-  // difference).  Larger ones last for the call, and so do those of a call that
-  // finds the kept staging in use by another thread.
+  // Staging of kKeptStageMin to kKeptStage bytes stays with the batch (512 x 512
+  // nodes: 610 us per call with an allocation of its own, 535 without; 256 x 256
+  // 121 either way, 64 x 64 46.2 and 48.6).  Others last for the call, and so do
+  // those of a call that finds the kept staging in use by another thread.
   const size_t bytes = 3 * np * sizeof(double);
   std::unique_lock<std::mutex> lock(b->stage_mutex, std::defer_lock);
-  const bool kept = bytes <= kKeptStage && lock.try_lock();
+  const bool kept = bytes >= kKeptStageMin && bytes <= kKeptStage && lock.try_lock();
   if (kept && bytes > b->stage_bytes) {
     hipFree(b->d_stage);
     b->d_stage = nullptr;

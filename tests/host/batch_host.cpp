@@ -22,7 +22,7 @@ namespace rec {
 std::mutex mu;
 std::condition_variable cv;
 std::set<char*> live;         // allocations
-int uploads = 0, waiting = 0, meet = 0;
+int allocs = 0, uploads = 0, waiting = 0, meet = 0;
 bool stale = false;           // a copy from memory that was given back
 thread_local char* exported;  // destination of this thread's last export
 std::vector<char*> exports;
@@ -31,6 +31,7 @@ hipError_t alloc(void** p, size_t n) {
   std::lock_guard<std::mutex> l(mu);
   *p = std::malloc(n + 64);
   live.insert((char*)*p);
+  ++allocs;
   return hipSuccess;
 }
 hipError_t give_back(void* p) {
@@ -104,16 +105,16 @@ static void add_case(lbm_batch& b, char** v) {
 static int fields() {
   static lbm_batch b;
   b.storage = LBM_STORE_F32;
-  char* v[] = {(char*)"40", (char*)"30", (char*)"1", (char*)"1", (char*)"1", (char*)"2", (char*)"0"};
+  char* v[] = {(char*)"400", (char*)"300", (char*)"1", (char*)"1", (char*)"1", (char*)"2", (char*)"0"};
   add_case(b, v);
-  v[0] = (char*)"80";
+  v[0] = (char*)"800";
   add_case(b, v);
   rec::meet = 2;
   std::vector<double> out[2];
   std::thread t[2];
   for (int i = 0; i < 2; ++i)
     t[i] = std::thread([&, i] {
-      out[i].resize(80 * 30);
+      out[i].resize(800 * 300);
       lbm_batch_fields(&b, i, out[i].data(), nullptr, nullptr);
     });
   for (auto& x : t) x.join();
@@ -172,9 +173,22 @@ static int items(int argc, char** argv) {
   return 0;
 }
 
+// Allocations after reading a case of nx x 300 nodes three times.
+static int staging(char* nx) {
+  static lbm_batch b;
+  b.storage = LBM_STORE_F32;
+  char* v[] = {nx, (char*)"300", (char*)"1", (char*)"1", (char*)"1", (char*)"2", (char*)"0"};
+  add_case(b, v);
+  std::vector<double> out((size_t)b.cs[0].grid.nx * 300);
+  for (int i = 0; i < 3; ++i) lbm_batch_fields(&b, 0, out.data(), nullptr, nullptr);
+  std::printf("%d %d\n", rec::allocs, (int)rec::live.size());
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "fields") return fields();
+  if (what == "staging" && argc == 3) return staging(argv[2]);
   if (what == "items" && argc > 3) return items(argc - 2, argv + 2);
   return 2;
 }

@@ -112,3 +112,9 @@ def test_two_step_items_are_built_for_runs_that_use_them(program):
     assert (every_item, out_of_order, even) == (1, 0, 1)
     assert [int(r[0]) for r in program("batch_host", "items", 3, 3, 30)[:2]] == [-1, -1]
     assert [int(r[0]) for r in program("batch_host", "items", 4, 3)[:1]] == [s]
+
+
+@pytest.mark.parametrize("nx,allocs,live", [(100, 3, 0), (200, 1, 1), (4000, 1, 1), (10000, 3, 0)])
+def test_staging_is_kept_where_it_pays(program, nx, allocs, live):
+    """Three reads of nx x 300 nodes: from 1 to 64 MB one allocation that stays."""
+    assert program("batch_host", "staging", nx) == [[str(allocs), str(live)]]
