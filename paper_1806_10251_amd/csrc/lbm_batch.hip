@@ -525,20 +525,28 @@ int multi_inner(int n, int tiles, int len) {
 // - Up to one block per compute unit (or 512 of the 6-row blocks) the launch
 //   is what counts: 4 cavities 64^2 FP64 9.3 | 4.5 us, 20 of them 11.0 | 8.9,
 //   FP32 9.3 | 5.3.
-// - More tiles: as long as a quarter of them keep away from the sides (20 cavities 128^2
-//   FP64 21.3 | 14.9 us, FP32 11.8 | 8.9; 20 channels 400 x 100 FP64 38.1 |
+// - More tiles: as long as a quarter of them keep away from the sides (20 cavities
+//   128^2 FP64 21.3 | 14.9 us, FP32 11.8 | 8.9; 20 channels 400 x 100 FP64 38.1 |
 //   25.6; 20 cavities 512^2 FP64 157 | 128, FP32 96.3 | 60.7).  Many small
 //   lattices have none, and the boundary work is done on the ring as well (200
 //   cavities 64^2 FP64 25.7 | 40.3 us, FP32 16.6 | 23.2).
+// - Beyond 2048 tiles (eight per compute unit) the work counts, as for a single
+//   lattice: the rows a pair collides over those of two single steps, up to 1.7
+//   (1.6: 39 cavities 190^2 FP64 53.8 | 46.2 us; 1.8: 76 cavities 128^2 FP64 43.3 |
+//   45.9, 512 of them 264 | 301, 76 FP32 21.3 | 22.5).
+// Solid nodes do not decide it (60 FP64 cavities 400^2 with solids in every tile
+// 650 | 315 us; of all batches measured only 20 of 200^2 lost, 30.0 | 33.0).
 int batch_multi_shape(lbm_batch* b) {
   if (b->schedule != 0) return -1;
   long long tiles[kNumMultiShapes] = {};
+  double rows = 0;   // of 64 nodes, two single steps
   bool any = false;
   for (int i = 0; i < b->n; ++i) {
     if (!b->h_active[i]) continue;
     const HostCase& c = b->cs[i];
     if (c.grid.nx < 16 || c.grid.ny < 16) return -1;
     any = true;
+    rows += 2.0 * ((c.grid.nx + kLanes - 1) / kLanes) * c.grid.ny;
     for (int s = 0; s < kNumMultiShapes; ++s)
       tiles[s] += (long long)multi_tiles_x(c) * multi_tiles_y(c, s);
   }
@@ -548,11 +556,12 @@ int batch_multi_shape(lbm_batch* b) {
   if (tiles[1] <= 512) return 1;
   const bool cached = active_lattice_bytes(b) <= kLastLevelCacheBytes;
   const int shape = cached || b->storage == LBM_STORE_F64 ? 3 : 4;
+  const int nr = kMultiShapes[shape].nw * kMultiShapes[shape].rpw;
+  if (tiles[shape] > 2048 && tiles[shape] * (2.0 * nr - 8.0) > 1.7 * rows) return -1;
   long long inner = 0;
   for (int i = 0; i < b->n; ++i) {
     if (!b->h_active[i]) continue;
     const HostCase& c = b->cs[i];
-    const int nr = kMultiShapes[shape].nw * kMultiShapes[shape].rpw;
     inner += (long long)multi_inner(c.grid.nx, multi_tiles_x(c), kLanes) *
              multi_inner(c.grid.ny, multi_tiles_y(c, shape), nr);
   }

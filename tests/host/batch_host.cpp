@@ -185,9 +185,21 @@ static int staging(char* nx) {
   return 0;
 }
 
+// Shape of the two-step kernel: storage, then per kind of case its number and
+// the case.
+static int shape(int argc, char** argv) {
+  static lbm_batch b;
+  b.storage = std::atoi(argv[0]);
+  for (int i = 1; i + 8 <= argc; i += 8)
+    for (int k = 0; k < std::atoi(argv[i]); ++k) add_case(b, argv + i + 1);
+  std::printf("%d\n", batch_multi_shape(&b));
+  return 0;
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "fields") return fields();
+  if (what == "shape" && argc > 3) return shape(argc - 2, argv + 2);
   if (what == "staging" && argc == 3) return staging(argv[2]);
   if (what == "items" && argc > 3) return items(argc - 2, argv + 2);
   return 2;

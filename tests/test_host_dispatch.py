@@ -118,3 +118,26 @@ def test_two_step_items_are_built_for_runs_that_use_them(program):
 def test_staging_is_kept_where_it_pays(program, nx, allocs, live):
     """Three reads of nx x 300 nodes: from 1 to 64 MB one allocation that stays."""
     assert program("batch_host", "staging", nx) == [[str(allocs), str(live)]]
+
+
+@pytest.mark.parametrize("storage,cases,shape", [
+    # one block per compute unit, two rounds of them
+    (F64, [(4, 64, 64, CAVITY, 0)], 0), (F64, [(16, 64, 64, CAVITY, 0)], 2),
+    (F64, [(20, 64, 64, CAVITY, 0)], 1), (F32, [(14, 100, 100, MILL, 3)], 1),
+    # tiles away from the sides: none, a quarter, many
+    (F64, [(200, 64, 64, CAVITY, 0)], ONE_BY_ONE), (F32, [(30, 116, 116, CAVITY, 0)], ONE_BY_ONE),
+    (F64, [(20, 128, 128, CAVITY, 0)], 3), (F32, [(20, 512, 512, CAVITY, 0)], 4),
+    (F64, [(20, 400, 100, CHANNEL, 0)], 3),
+    # the ring's work beyond 2048 tiles
+    (F64, [(30, 128, 128, CAVITY, 0)], 3), (F64, [(76, 128, 128, CAVITY, 0)], ONE_BY_ONE),
+    (F32, [(76, 128, 128, MILL, 0)], ONE_BY_ONE), (F64, [(102, 128, 256, DUCT, 0)], ONE_BY_ONE),
+    (F64, [(41, 180, 180, CAVITY, 0)], 3), (F32, [(102, 128, 256, DUCT, 0)], 4),
+    (F64, [(85, 256, 64, CHANNEL, 0)], 3),
+    # solids in every tile
+    (F64, [(60, 400, 400, CAVITY, 41)], 3), (F32, [(20, 200, 200, CAVITY, 41)], 3),
+    # a lattice narrower than 16 nodes
+    (F32, [(4, 64, 64, CAVITY, 0), (1, 15, 64, CAVITY, 0)], ONE_BY_ONE),
+])
+def test_two_step_shape_of_batches(program, storage, cases, shape):
+    args = [v for n, nx, ny, sides, every in cases for v in (n, nx, ny, *sides, every)]
+    assert program("batch_host", "shape", storage, *args) == [[str(shape)]]
