@@ -9,8 +9,8 @@
 // pixels, which are strided in NHWC: its operands are read with the
 // transposing LDS load, the pixel tiles are split over blocks, and the FP32
 // partial sums are added in a fixed order.  Images of 2 GB and channel counts
-// beyond the LDS take conv_fwd_kernel (16x16x32, operands from memory); every
-// path reduces in the same order and gives the same bits.
+// beyond the LDS take conv_fwd_kernel or conv_fwd32_kernel (operands from
+// memory); every path reduces in the same order and gives the same bits.
 //
 // MFMA 16x16x32 bf16 lane layout (verified on the device): lane l holds
 // A[l % 16][8 (l / 16) + v] and B[8 (l / 16) + v][l % 16] for v < 8, and
@@ -101,6 +101,27 @@ __device__ __forceinline__ bf16x8 relu_mask(bf16x8 d, const bf16x8& y) {
   return d;
 }
 
+// One output value (bias added) of pixel p: ReLU, then FP32, or bf16 masked or
+// upsampled.
+__device__ __forceinline__ void store_value(const ConvArgs& a, int p, int co, float val) {
+  if (a.relu) val = fmaxf(val, 0.f);
+  if (a.out_f32) {
+    static_cast<float*>(a.y)[(long long)p * a.ldy + co] = val;
+    return;
+  }
+  bf16 o = (bf16)val;
+  if (a.mask && !((float)a.mask[(long long)p * a.ldmask + co] > 0.f)) o = (bf16)0.f;
+  bf16* out = static_cast<bf16*>(a.y) + co;
+  if (!a.up) {
+    out[(long long)p * a.ldy] = o;
+    return;
+  }
+  const int x = p % a.wd, q = p / a.wd, y = q % a.h, img = q / a.h;
+#pragma unroll
+  for (int f = 0; f < 4; ++f)
+    out[(((long long)img * 2 * a.h + 2 * y + f / 2) * 2 * a.wd + 2 * x + f % 2) * a.ldy] = o;
+}
+
 // WC: waves along the output channels (1 or 2); 4 / WC waves along pixels.
 template <int WC>
 __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
@@ -163,25 +184,84 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int p = px0 + 16 * s + 4 * g + v;
-        if (p >= a.npix) continue;
-        float val = acc[s][b][v] + bias;
-        if (a.relu) val = fmaxf(val, 0.f);
-        if (a.out_f32) {
-          static_cast<float*>(a.y)[(long long)p * a.ldy + co] = val;
-          continue;
-        }
-        bf16 o = (bf16)val;
-        if (a.mask && !((float)a.mask[(long long)p * a.ldmask + co] > 0.f)) o = (bf16)0.f;
-        bf16* out = static_cast<bf16*>(a.y) + co;
-        if (!a.up) {
-          out[(long long)p * a.ldy] = o;
-        } else {
-          const int x = p % a.wd, q = p / a.wd, y = q % a.h, img = q / a.h;
+        if (p < a.npix) store_value(a, p, co, acc[s][b][v] + bias);
+      }
+    }
+}
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// The same on v_mfma_f32_32x32x16_bf16 (layout at the tiled convolution below):
+// a wave owns 64 pixels x 32 CT output channels and does twice the work per
+// loaded byte, so it needs that many pixels to fill the device (704 -> 64
+// channels at 16 x 64 x 64: 353 us with the tiles above, 209 with these).
+template <int CT>
+__global__ __launch_bounds__(256) void conv_fwd32_kernel(ConvArgs a) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int px0 = blockIdx.x * 256 + 64 * wv;
+  const int co0 = blockIdx.y * (32 * CT);
+  const int r = lane & 31, g = lane >> 5;
+  int pidx[2], py[2], pxx[2];
+  bool pv[2];
 #pragma unroll
-          for (int f = 0; f < 4; ++f)
-            out[(((long long)img * 2 * a.h + 2 * y + f / 2) * 2 * a.wd + 2 * x + f % 2) * a.ldy] =
-                o;
-        }
+  for (int s = 0; s < 2; ++s) {
+    const int p = px0 + 32 * s + r;
+    pv[s] = p < a.npix;
+    const int q = pv[s] ? p : 0;
+    pidx[s] = q;
+    pxx[s] = q % a.wd;
+    py[s] = (q / a.wd) % a.h;
+  }
+  f32x16 acc[2][CT];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int b = 0; b < CT; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[s][b][v] = 0.f;
+  for (int t = 0; t < 9; ++t) {
+    const int dy = t / 3 - 1, dx = t % 3 - 1;
+    const bf16* xa[2];
+    bool ok[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int yy = py[s] + dy, xx = pxx[s] + dx;
+      ok[s] = pv[s] && yy >= 0 && yy < a.h && xx >= 0 && xx < a.wd;
+      xa[s] = a.x + (long long)(ok[s] ? pidx[s] + dy * a.wd + dx : 0) * a.ldx + 8 * g;
+    }
+    const bf16* wb[CT];
+#pragma unroll
+    for (int b = 0; b < CT; ++b)
+      wb[b] = a.w + ((long long)(co0 + 32 * b + r) * 9 + t) * a.cin + 8 * g;
+    for (int c0 = 0; c0 < a.cin; c0 += 16) {
+      bf16x8 A[2], B[CT];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        A[s] = *reinterpret_cast<const bf16x8*>(xa[s] + c0);
+        if (!ok[s]) A[s] = bf16x8{};
+      }
+#pragma unroll
+      for (int b = 0; b < CT; ++b) B[b] = *reinterpret_cast<const bf16x8*>(wb[b] + c0);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int b = 0; b < CT; ++b) acc[s][b] = mfma32(A[s], B[b], acc[s][b]);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int b = 0; b < CT; ++b) {
+      const int co = co0 + 32 * b + r;
+      const float bias = a.bias ? a.bias[co] : 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int p = px0 + 32 * s + 8 * (v / 4) + 4 * g + (v % 4);
+        if (p < a.npix) store_value(a, p, co, acc[s][b][v] + bias);
       }
     }
 }
@@ -208,13 +288,8 @@ __global__ __launch_bounds__(256) void conv_fwd_kernel(ConvArgs a) {
 // What is left is latency in series (launch, tile load, per stage LDS reads
 // and a barrier, store), no single unit: leaving out any one of MFMA, LDS
 // reads, tile load, weight loads or stores saves 5-20 %.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ f32x16 mfma32(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
 constexpr int kLdsBytes = 160 * 1024;
+constexpr int kConv32MinPix = 65536;   // pixels from which conv_fwd32_kernel is faster
 
 // A stage is KS channels of one tap (KS = 96, 64 or 32, the largest that
 // divides cin) or, for cin = 32 (ROW), the three taps of a kernel row, so
@@ -644,8 +719,11 @@ int try_conv(const ConvArgs& a, hipStream_t st, bool* done) {
   const bool narrow = (a.wd + 15) / 16 * 16 < (a.wd + 31) / 32 * 32 ||
                       (ConvTile<MP, NC, WP, WC, 32, KS>::lds(a.cin) > half &&
                        ConvTile<MP, NC, WP, WC, 16, KS>::lds(a.cin) <= half);
-  return narrow ? try_conv_width<MP, NC, WP, WC, 16>(a, st, done)
-                : try_conv_width<MP, NC, WP, WC, 32>(a, st, done);
+  int rc = UNET_OK;
+  if (!narrow) rc = try_conv_width<MP, NC, WP, WC, 32>(a, st, done);
+  // (or where only they fit: 640 -> 64 at 16 x 64 x 64, 321 -> 133 us)
+  if (!rc && !*done) rc = try_conv_width<MP, NC, WP, WC, 16>(a, st, done);
+  return rc;
 }
 
 template <int MP, int NC, int WP, int WC, int TX>
@@ -718,7 +796,16 @@ int launch_conv(ConvArgs a, hipStream_t st) {
   }
   // an image of 2 GB, or more input channels than LDS holds (none of the
   // network's layers): operands straight from memory
-  if (a.cout % 64 == 0) {
+  // (32 output channels of many input channels: 544 -> 32 at 16 x 64 x 64 99 us with
+  // the small tiles, 127 with the large)
+  if (a.npix >= kConv32MinPix && (a.cout % 64 == 0 || a.cin < 448)) {
+    const int ct = a.cout % 64 == 0 ? 2 : 1;
+    dim3 grid((a.npix + 255) / 256, a.cout / (32 * ct));
+    if (ct == 2)
+      hipLaunchKernelGGL(conv_fwd32_kernel<2>, grid, dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL(conv_fwd32_kernel<1>, grid, dim3(256), 0, st, a);
+  } else if (a.cout % 64 == 0) {
     dim3 grid((a.npix + 63) / 64, a.cout / 64);
     hipLaunchKernelGGL(conv_fwd_kernel<2>, grid, dim3(256), 0, st, a);
   } else {

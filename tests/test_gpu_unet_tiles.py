@@ -237,3 +237,31 @@ def test_network_gradients_equal_its_layers(U, res, n):
         ref = want[k].float().cpu().numpy().reshape(-1)
         err = np.abs(got[w:w + 9 * ci * co] - ref).max()
         assert err <= 1e-3 * np.abs(ref).max(), (k, err, np.abs(ref).max())
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (3, 9, 37, 416, 32),      # a tile of 16 columns, where 32 do not fit
+    (2, 17, 33, 640, 64),
+    (1, 257, 259, 704, 64),   # no tile fits: 64-pixel wave tiles, last block partial
+    (1, 263, 250, 1024, 32),  # the same with 32 output channels
+])
+def test_wide_convolutions_equal_narrow_ones(U, n, h, w, cin, cout):
+    """Many input channels.  The outer ones are zero, so the result is that of the
+    inner 64 alone, which another kernel takes: the same bits, as zeros add
+    nothing to the sums."""
+    import torch
+    print("[gpu-case] wide", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(24)
+    x = torch.zeros((n, h, w, cin), device="cuda", dtype=torch.bfloat16)
+    wt = torch.zeros((cout, 9, cin), device="cuda", dtype=torch.bfloat16)
+    xs, ws = dev(bf(rng, n, h, w, 64), torch.bfloat16), dev(bf(rng, cout, 9, 64), torch.bfloat16)
+    x[..., :64], wt[..., :64] = xs, ws
+    b = dev(rng.standard_normal(cout), torch.float32)
+    for kw in (dict(out_f32=True), dict(relu=True)):
+        assert torch.equal(U.conv3x3_fwd(x, wt, b, cout, **kw), U.conv3x3_fwd(xs, ws, b, cout, **kw))
+    # and against the reference at a corner with every channel
+    xr, wr = bf(rng, 1, 5, 6, cin), bf(rng, cout, 9, cin, scale=0.1)
+    x[:1, :5, :6] = dev(xr, torch.bfloat16)
+    got = host(U.conv3x3_fwd(x, dev(wr, torch.bfloat16), None, cout, out_f32=True))[0, :4, :5]
+    bound = R.conv3x3(np.abs(xr), np.abs(wr))[0, :4, :5]
+    assert (np.abs(got - R.conv3x3(xr, wr)[0, :4, :5]) <= 1e-5 * bound + 1e-6).all()

@@ -141,3 +141,17 @@ def test_staging_is_kept_where_it_pays(program, nx, allocs, live):
 def test_two_step_shape_of_batches(program, storage, cases, shape):
     args = [v for n, nx, ny, sides, every in cases for v in (n, nx, ny, *sides, every)]
     assert program("batch_host", "shape", storage, *args) == [[str(shape)]]
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,kernel", [
+    # LDS holds a tile of 32 columns, only one of 16, none
+    (16, 64, 64, 352, 32, "tile"), (16, 64, 64, 384, 96, "tile"), (4, 9, 9, 416, 32, "tile"),
+    (16, 64, 64, 640, 64, "tile"), (2, 64, 64, 576, 128, "tile"),
+    (16, 64, 64, 704, 64, "conv_fwd32_kernel"), (1, 256, 256, 1024, 32, "conv_fwd_kernel"),
+    (16, 64, 63, 704, 64, "conv_fwd_kernel"), (1, 3, 5, 1216, 64, "conv_fwd_kernel"),
+])
+def test_wide_convolutions(program, n, h, w, cin, cout, kernel):
+    """Many input channels: a tile wherever one fits, else the 64-pixel wave
+    tiles from 65536 pixels on (64 output channels)."""
+    (launch,) = program("unet_launches", "fwd", n, h, w, cin, cout)
+    assert launch[0] == kernel
