@@ -8,9 +8,10 @@
 // makes every operand one 16-byte read.  The weight gradient reduces over
 // pixels, which are strided in NHWC: its operands are read with the
 // transposing LDS load, the pixel tiles are split over blocks, and the FP32
-// partial sums are added in a fixed order.  Images of 2 GB and channel counts
-// beyond the LDS take conv_fwd_kernel or conv_fwd32_kernel (operands from
-// memory); every path reduces in the same order and gives the same bits.
+// partial sums are added in a fixed order.  Images of 2 GB, channel counts
+// beyond the LDS and many small images take conv_fwd_kernel or
+// conv_fwd32_kernel (operands from memory); every path reduces in the same
+// order and gives the same bits.
 //
 // MFMA 16x16x32 bf16 lane layout (verified on the device): lane l holds
 // A[l % 16][8 (l / 16) + v] and B[8 (l / 16) + v][l % 16] for v < 8, and
@@ -683,13 +684,35 @@ __global__ __launch_bounds__(64 * WP * WC) void conv_direct_kernel(ConvArgs a, i
   store_tile<MP, NC, WP, WC, TX, KS>(a, acc, img, x0, y0, co0, sbias, smem);
 }
 
-// Launches a tiling if its LDS fits (*done); otherwise leaves *done false.
+// Whether tiles of P pixels cost more than the kernels without tiles: every image
+// has tiles of its own, so many small images are mostly padding.  Up to three
+// blocks per compute unit that does not matter.  Beyond, the tiles win up to a
+// ratio of covered to image pixels of 4 to 5; of 3 against conv_fwd32_kernel, or
+// with input channels that leave room for one block per compute unit; less with
+// the largest channel counts, and with few input for many output channels, where
+// the stores bound both.  The next smaller tile is tried first.  Without
+// tiles | with, 64 -> 64 channels: 4096 images of 4 x 4 27.8 | 83.4 us, 1024 of them
+// 12.9 | 11.5; 4062 of 8 x 8 96.5 | 85.4; 128 -> 128: 4096 of 1 x 1 16.3 | 121.
+bool tiles_padded(const ConvArgs& a, long long tiles, int P, int channel_blocks) {
+  const long long n = a.npix / (a.h * a.wd);
+  if (tiles * n * channel_blocks <= 768) return false;
+  const bool big = a.npix >= kConv32MinPix;
+  double most = a.cout % 64 == 0 ? 5.2 : 4.0;
+  if (a.cin == 32 && a.cout >= 128) most = 1.99;
+  else if (big && a.cin >= 256 && a.cout >= 256) most = 2.2;
+  else if (big || a.cin >= 256) most = a.cout >= 128 ? 3.0 : 3.2;
+  return (double)tiles * P > most * a.h * a.wd;
+}
+
+// Launches a tiling if its LDS fits and its tiles are filled (*done); otherwise
+// leaves *done false.
 template <int MP, int NC, int WP, int WC, int TX, int KS, bool ROW>
 int try_conv_tile(const ConvArgs& a, hipStream_t st, bool* done) {
   using L = ConvTile<MP, NC, WP, WC, TX, KS>;
   const int tx = (a.wd + TX - 1) / TX, ty = (a.h + L::TY - 1) / L::TY;
   const size_t lds = L::lds(a.cin);
-  if (lds > (size_t)kLdsBytes) return UNET_OK;
+  if (lds > (size_t)kLdsBytes || tiles_padded(a, (long long)tx * ty, L::P, a.cout / L::CB))
+    return UNET_OK;
   auto* fn = conv_tile_kernel<MP, NC, WP, WC, TX, KS, ROW>;
   if (lds > 64 * 1024)
     UCHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -732,7 +755,8 @@ int try_direct_width(const ConvArgs& a, hipStream_t st, bool* done) {
   if (a.cin % 64 || a.cout % L::CB) return UNET_OK;
   const int tx = (a.wd + TX - 1) / TX, ty = (a.h + L::TY - 1) / L::TY;
   const size_t lds = L::lds_direct(a.cin);
-  if (lds > (size_t)kLdsBytes) return UNET_OK;
+  if (lds > (size_t)kLdsBytes || tiles_padded(a, (long long)tx * ty, L::P, a.cout / L::CB))
+    return UNET_OK;
   auto* fn = conv_direct_kernel<MP, NC, WP, WC, TX, 64>;
   if (lds > 64 * 1024)
     UCHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -794,8 +818,8 @@ int launch_conv(ConvArgs a, hipStream_t st) {
     if (!rc && !done) rc = try_conv<1, 1, 4, 1>(a, st, &done);
     if (rc || done) return rc;
   }
-  // an image of 2 GB, or more input channels than LDS holds (none of the
-  // network's layers): operands straight from memory
+  // an image of 2 GB, more input channels than LDS holds (none of the network's
+  // layers), or many small images: operands straight from memory
   // (32 output channels of many input channels: 544 -> 32 at 16 x 64 x 64 99 us with
   // the small tiles, 127 with the large)
   if (a.npix >= kConv32MinPix && (a.cout % 64 == 0 || a.cin < 448)) {

@@ -265,3 +265,39 @@ def test_wide_convolutions_equal_narrow_ones(U, n, h, w, cin, cout):
     got = host(U.conv3x3_fwd(x, dev(wr, torch.bfloat16), None, cout, out_f32=True))[0, :4, :5]
     bound = R.conv3x3(np.abs(xr), np.abs(wr))[0, :4, :5]
     assert (np.abs(got - R.conv3x3(xr, wr)[0, :4, :5]) <= 1e-5 * bound + 1e-6).all()
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [
+    (2000, 1, 1, 32, 64), (1400, 3, 2, 96, 32), (4100, 4, 4, 64, 128), (16400, 1, 4, 32, 32),
+    (3300, 9, 9, 64, 128),
+])
+def test_many_small_images_equal_single_ones(U, n, h, w, cin, cout):
+    """Kernels without tiles (small and large form), and a smaller tile: the bits
+    of one image alone."""
+    import torch
+    print("[gpu-case] small images", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(25)
+    x, wt = dev(bf(rng, n, h, w, cin), torch.bfloat16), dev(bf(rng, cout, 9, cin), torch.bfloat16)
+    for kw in (dict(out_f32=True), dict(relu=True)):
+        y = U.conv3x3_fwd(x, wt, None, cout, **kw)
+        for k in (0, n // 2, n - 1):
+            one = U.conv3x3_fwd(x[k:k + 1].contiguous(), wt, None, cout, **kw)
+            assert torch.equal(one[0], y[k])
+
+
+@pytest.mark.parametrize("res,n", [(8, 1100), (16, 1030)])
+def test_network_of_many_small_samples(U, res, n):
+    """Levels of 1 x 1 to 16 x 16: the fused forms (pooling, upsampling, masks) in
+    the kernels without tiles give the bits of the single layers, and a sample the
+    bits it has alone."""
+    import torch
+    print("[gpu-case] network, small samples", res, n, flush=True)
+    rng = np.random.default_rng(res)
+    net = U.UNet(max_batch=n, res=res, seed=7)
+    x0 = dev(bf(rng, n, res, res, 32), torch.bfloat16)
+    want = layered_forward(U, dev(net.params(), torch.float32), x0)
+    got = net.forward(x0)
+    assert torch.equal(got, want)
+    for k in (0, n - 1):
+        assert torch.equal(net.forward(x0[k:k + 1].contiguous())[0], want[k])
+    net.close()

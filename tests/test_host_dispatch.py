@@ -155,3 +155,22 @@ def test_wide_convolutions(program, n, h, w, cin, cout, kernel):
     tiles from 65536 pixels on (64 output channels)."""
     (launch,) = program("unet_launches", "fwd", n, h, w, cin, cout)
     assert launch[0] == kernel
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,kernel", [
+    # few blocks: tiles, however empty
+    (500, 1, 1, 32, 32, "tile"), (125, 4, 4, 64, 64, "tile"), (300, 2, 3, 256, 64, "tile"),
+    # many small images: without tiles, the large form from 65536 pixels on
+    (2000, 1, 1, 32, 32, "conv_fwd_kernel"), (4096, 1, 1, 128, 128, "conv_fwd_kernel"),
+    (4096, 2, 2, 256, 256, "conv_fwd_kernel"), (1333, 3, 3, 96, 32, "conv_fwd_kernel"),
+    (4096, 4, 4, 64, 64, "conv_fwd32_kernel"), (5000, 4, 4, 96, 32, "conv_fwd32_kernel"),
+    (16250, 1, 16, 128, 128, "conv_fwd32_kernel"), (937, 8, 8, 32, 128, "conv_fwd_kernel"),
+    # a smaller tile
+    (3209, 9, 9, 128, 128, "tile"), (1015, 16, 16, 64, 64, "tile"), (1024, 4, 4, 64, 64, "tile"),
+    (4062, 8, 8, 64, 64, "tile"), (899, 17, 17, 64, 64, "tile"),
+    # the sizes of the network
+    (16, 128, 128, 32, 32, "tile"), (16, 16, 16, 256, 256, "tile"), (2048, 16, 16, 256, 256, "tile"),
+])
+def test_many_small_images(program, n, h, w, cin, cout, kernel):
+    (launch,) = program("unet_launches", "fwd", n, h, w, cin, cout)
+    assert launch[0] == kernel
