@@ -24,6 +24,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "unet.h"
@@ -964,8 +965,9 @@ struct WgradGroup {
   WgradLayer l[kMaxLayers];
 };
 
-// BIG: images of 2 GB or more, whose loads take 64-bit addresses.
-template <bool BIG>
+// BIG: images of 2 GB or more, whose loads take 64-bit addresses.  RAGGED: some
+// layer's tiles reach beyond its images.
+template <bool BIG, bool RAGGED>
 __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
   constexpr int TX = 16, TY = 16;
   constexpr int CO = 32, CI = 32, NT = 512, WK = NT / 64;
@@ -1011,8 +1013,7 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
     px_[i] = v < kXVec ? (q / HX) << 16 | (q % HX) : 0x7FFF0000;   // (never inside)
     ox[i] = unsigned((q / HX * a.wd + q % HX) * a.ldx + 8 * c) * 2u;
   }
-  // next tile to load
-  int tx = u0 % a.tiles_x, ty = (u0 / a.tiles_x) % a.tiles_y, img = u0 / (a.tiles_x * a.tiles_y);
+  int tx, ty, img;   // next tile to load
   bf16x8 rd[kDyPer], rx[kXPer];
   auto load = [&]() {
     const int x0 = tx * TX, y0 = ty * TY;
@@ -1079,12 +1080,6 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
   };
 
   f32x16 acc[9], accb;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    accb[v] = 0.f;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t][v] = 0.f;
-  }
   bf16x8 ones;
 #pragma unroll
   for (int v = 0; v < 8; ++v) ones[v] = (bf16)1.f;
@@ -1093,32 +1088,76 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
   const int lch = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
   const char* pd = smem + (RW * wk * TX + lrow) * SD + 2 * lch;
   const char* px = smem + P * SD + (RW * wk * HX + lrow) * SX + 2 * lch;
-  if (u0 < u1) load();
-  store(0);
-  if (u0 + 1 < u1) load();
-  __syncthreads();
-  for (int u = u0; u < u1; ++u) {
-    const int buf = (u - u0) & 1;
-    const char* d = pd + buf * kStage;
-    const char* b = px + buf * kStage;
-    bf16x8 B[3][3];
+  // The sums over this block's tiles.  masked: pixels outside the image take no
+  // part (else they do with dy = 0).
+  auto sweep = [&](auto masked) {
 #pragma unroll
-    for (int j = 0; j < RW; ++j) {
+    for (int v = 0; v < 16; ++v) {
+      accb[v] = 0.f;
 #pragma unroll
-      for (int k = j ? 2 : 0; k < 3; ++k)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const char* bt = b + ((j + k) * HX + c) * SX;
-          B[(j + k) % 3][c] = lds_tr8(bt, bt + 4 * SX);
-        }
-      const bf16x8 A = lds_tr8(d + j * TX * SD, d + (j * TX + 4) * SD);
-#pragma unroll
-      for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[(j + t / 3) % 3][t % 3], acc[t]);
-      if (bias) accb = mfma32(A, ones, accb);
+      for (int t = 0; t < 9; ++t) acc[t][v] = 0.f;
     }
-    if (u + 1 < u1) store(buf ^ 1);
-    if (u + 2 < u1) load();
+    tx = u0 % a.tiles_x;
+    ty = (u0 / a.tiles_x) % a.tiles_y;
+    img = u0 / (a.tiles_x * a.tiles_y);
+    int mx = tx, my = ty;   // tile being multiplied
+    if (u0 < u1) load();
+    store(0);
+    if (u0 + 1 < u1) load();
     __syncthreads();
+    for (int u = u0; u < u1; ++u) {
+      const int buf = (u - u0) & 1;
+      const char* d = pd + buf * kStage;
+      const char* b = px + buf * kStage;
+      bf16x8 B[3][3];
+#pragma unroll
+      for (int j = 0; j < RW; ++j) {
+#pragma unroll
+        for (int k = j ? 2 : 0; k < 3; ++k)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const char* bt = b + ((j + k) * HX + c) * SX;
+            B[(j + k) % 3][c] = lds_tr8(bt, bt + 4 * SX);
+            if constexpr (masked) {
+#pragma unroll
+              for (int v = 0; v < 8; ++v)
+                if (mx * TX + 8 * (lane >> 5) + v >= a.wd) B[(j + k) % 3][c][v] = (bf16)0.f;
+            }
+          }
+        if (masked && my * TY + RW * wk + j >= a.h) continue;   // uniform
+        const bf16x8 A = lds_tr8(d + j * TX * SD, d + (j * TX + 4) * SD);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[(j + t / 3) % 3][t % 3], acc[t]);
+        if (bias) accb = mfma32(A, ones, accb);
+      }
+      if (masked && ++mx == a.tiles_x) {
+        mx = 0;
+        my = my + 1 == a.tiles_y ? 0 : my + 1;
+      }
+      if (u + 1 < u1) store(buf ^ 1);
+      if (u + 2 < u1) load();
+      __syncthreads();
+    }
+  };
+  sweep(std::false_type{});
+  // Inputs that are not finite: a pixel outside the image (dy = 0) has neighbours
+  // inside, and 0 times infinity is none of the sum.  Seen in the sums, which are
+  // then taken again without those pixels (masks in the loop itself cost 4 to 14 %
+  // of a launch).
+  if constexpr (RAGGED) {
+    int* again = reinterpret_cast<int*>(smem);   // (every wave has left the loop)
+    float z = 0.f;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z += acc[t][v] * 0.f;
+    if (tid == 0) *again = 0;
+    __syncthreads();
+    if (z != 0.f) *again = 1;
+    __syncthreads();
+    const int redo = *again;
+    __syncthreads();
+    if (redo) sweep(std::true_type{});
   }
   const int r = lane & 31, g = lane >> 5;
   float* part = a.part + (long long)split * 9 * a.cin * a.cout;
@@ -1800,16 +1839,19 @@ static long long add_wgrad(WgradGroup& g, const WgradPlan& p, const bf16* dy, in
 static int launch_wgrad(const WgradGroup& g, hipStream_t st) {
   const WgradLayer& e = g.l[g.layers - 1];
   const dim3 grid(e.first + e.splits * (e.cin / 32) * (e.cout / 32)), block(512);
-  bool big = false;
+  bool big = false, ragged = false;
   for (int k = 0; k < g.layers; ++k) {
     const WgradLayer& l = g.l[k];
+    ragged = ragged || l.h % 16 || l.wd % 16;
     big = big || image_bytes(l.h, l.wd, l.lddy, 32) > kMaxRsrc ||
           image_bytes(l.h, l.wd, l.ldx, 32) > kMaxRsrc;
   }
   if (big)
-    hipLaunchKernelGGL(wgrad_tile_kernel<true>, grid, block, 0, st, g);
+    hipLaunchKernelGGL((wgrad_tile_kernel<true, true>), grid, block, 0, st, g);
+  else if (ragged)
+    hipLaunchKernelGGL((wgrad_tile_kernel<false, true>), grid, block, 0, st, g);
   else
-    hipLaunchKernelGGL(wgrad_tile_kernel<false>, grid, block, 0, st, g);
+    hipLaunchKernelGGL((wgrad_tile_kernel<false, false>), grid, block, 0, st, g);
   UCHECK(hipGetLastError());
   SumArgs sums{};
   sums.layers = g.layers;

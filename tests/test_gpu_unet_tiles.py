@@ -301,3 +301,38 @@ def test_network_of_many_small_samples(U, res, n):
     for k in (0, n - 1):
         assert torch.equal(net.forward(x0[k:k + 1].contiguous())[0], want[k])
     net.close()
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout", [(2, 13, 35, 32, 64), (1, 16, 16, 32, 32),
+                                            (3, 21, 11, 64, 32), (1, 33, 48, 32, 32)])
+def test_weight_gradient_of_inputs_that_are_not_finite(U, n, h, w, cin, cout):
+    """An infinity in the last row or column reaches the taps that see it and no
+    others: the padding of the pixel tiles adds nothing."""
+    import torch
+    import torch.nn.functional as F
+    print("[gpu-case] weight gradient, infinities", n, h, w, cin, cout, flush=True)
+    rng = np.random.default_rng(26)
+    x, dy = bf(rng, n, h, w, cin), np.abs(bf(rng, n, h, w, cout)) + 0.5
+    x[0, h - 1, w // 2, 1] = np.inf
+    x[n - 1, h // 2, w - 1, 2] = -np.inf
+    x[0, h - 1, w - 1, 3] = np.inf
+    dw, db = U.conv3x3_bwd_weight(dev(dy, torch.bfloat16), dev(x, torch.bfloat16), cin, cout)
+    # the sums themselves, tap by tap, over the pixels a tap sees
+    dyr = host(dev(dy, torch.bfloat16))
+    want = np.zeros((cout, 9, cin))
+    xp = np.zeros((n, h + 2, w + 2, cin))
+    xp[:, 1:-1, 1:-1] = x
+    for t in range(9):
+        view = xp[:, t // 3:t // 3 + h, t % 3:t % 3 + w]
+        inside = np.zeros((n, h + 2, w + 2, 1), bool)
+        inside[:, 1:-1, 1:-1] = True
+        inside = inside[:, t // 3:t // 3 + h, t % 3:t % 3 + w, 0]
+        want[:, t] = dyr[inside].T @ view[inside]
+    got = host(dw)
+    finite = np.isfinite(want)
+    assert 0 < (~finite).sum() < finite.size
+    np.testing.assert_array_equal(np.isfinite(got), finite)
+    np.testing.assert_array_equal(got[~finite], want[~finite])
+    bound = np.abs(dyr).reshape(-1, cout).sum(0).max() * np.abs(x[np.isfinite(x)]).max()
+    assert np.abs(got[finite] - want[finite]).max() <= 1e-5 * bound
+    assert np.isfinite(host(db)).all()
