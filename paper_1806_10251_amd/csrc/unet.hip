@@ -958,17 +958,24 @@ struct WgradLayer {
   int lddy, ldx, h, wd, cin, cout;
   int tiles_x, tiles_y, units, splits;
   int first;                  // first block
-  unsigned dybytes, xbytes;   // image_bytes of a channel tile of dy and of x
-};
+  unsigned dybytes, xbytes;   // from the first to the last pixel of ax ay images,
+                              // 32 channels of dy and of x
+  int n, ax, ay;              // images, and those across and down a tile (see
+};                            // wgrad_tiles); last: most forms do not load them
 struct WgradGroup {
   int layers;
   WgradLayer l[kMaxLayers];
 };
 
-// BIG: images of 2 GB or more, whose loads take 64-bit addresses.  RAGGED: some
-// layer's tiles reach beyond its images.
-template <bool BIG, bool RAGGED>
+// Forms of the kernel, by what some layer of the group needs: tiles inside the
+// images (sides of multiples of 16), tiles that reach beyond them, several images to
+// a tile as well, and 64-bit addresses as well (tiles of 2 GB or more).  Each costs
+// registers and a longer start (2 us) that the ones before it do without.
+enum WgradForm { kWgradFull, kWgradRagged, kWgradPacked, kWgradBig };
+template <WgradForm FORM>
 __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
+  constexpr bool BIG = FORM == kWgradBig, PACKED = FORM >= kWgradPacked;
+  constexpr bool RAGGED = FORM >= kWgradRagged;
   constexpr int TX = 16, TY = 16;
   constexpr int CO = 32, CI = 32, NT = 512, WK = NT / 64;
   constexpr int SD = 2 * CO, SX = 2 * CI, HX = TX + 2, HP = HX * (TY + 2), P = TX * TY;
@@ -997,47 +1004,101 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
   const int u1 = int((long long)(split + 1) * a.units / a.splits);
   const bool bias = a.bpart != nullptr && ci0 == 0;
 
-  // this thread's pieces of a tile: pixel within the tile and byte offset
-  // from the tile's first pixel, the same for every tile
+  // Pixel (r, c) of a tile (-1 and 16: its ring) is pixel (r, c) of image k of the
+  // tile; false: between images.
+  const int per = PACKED ? a.ax * a.ay : 1;
+  auto place = [&](int& r, int& c, int& k) {
+    k = 0;
+    if constexpr (PACKED) {
+      const int ky = a.ay > 1 && r > 0 ? r / (a.h + 1) : 0;
+      const int kx = a.ax > 1 && c > 0 ? c / (a.wd + 1) : 0;
+      r -= ky * (a.h + 1);
+      c -= kx * (a.wd + 1);
+      k = ky * a.ax + kx;
+      return ky < a.ay && kx < a.ax && (a.ay == 1 || (r >= 0 && r < a.h)) &&
+             (a.ax == 1 || (c >= 0 && c < a.wd));
+    }
+    return true;
+  };
+  // this thread's pieces of a tile: pixel within the image (row << 16 | column, of
+  // x from the ring's first on) and byte offset from the tile's first pixel, the
+  // same for every tile; packed: image << 10 | row << 5 | column, negative for none
   int pd_[kDyPer], px_[kXPer];
   unsigned od[kDyPer], ox[kXPer];
 #pragma unroll
   for (int i = 0; i < kDyPer; ++i) {
     const int v = tid + NT * i, q = v / (CO / 8), c = v % (CO / 8);
-    pd_[i] = (q / TX) << 16 | (q % TX);
-    od[i] = unsigned(((q / TX) * a.wd + q % TX) * a.lddy + 8 * c) * 2u;
+    if constexpr (PACKED) {
+      int y = q / TX, x = q % TX, k;
+      const bool in = place(y, x, k);
+      pd_[i] = in ? k << 10 | y << 5 | x : -1;
+      od[i] = unsigned(((k * a.h + y) * a.wd + x) * a.lddy + 8 * c) * 2u;
+    } else {
+      pd_[i] = (q / TX) << 16 | (q % TX);
+      od[i] = unsigned(((q / TX) * a.wd + q % TX) * a.lddy + 8 * c) * 2u;
+    }
   }
 #pragma unroll
   for (int i = 0; i < kXPer; ++i) {
     const int v = tid + NT * i, q = v / (CI / 8), c = v % (CI / 8);
-    px_[i] = v < kXVec ? (q / HX) << 16 | (q % HX) : 0x7FFF0000;   // (never inside)
-    ox[i] = unsigned((q / HX * a.wd + q % HX) * a.ldx + 8 * c) * 2u;
+    if constexpr (PACKED) {
+      int y = q / HX - 1, x = q % HX - 1, k;
+      const bool in = place(y, x, k) && v < kXVec;
+      px_[i] = in ? k << 10 | (y + 1) << 5 | (x + 1) : -1;
+      ox[i] = unsigned(((k * a.h + y + 1) * a.wd + x + 1) * a.ldx + 8 * c) * 2u;
+    } else {
+      px_[i] = v < kXVec ? (q / HX) << 16 | (q % HX) : 0x7FFF0000;   // (never stored)
+      ox[i] = unsigned((q / HX * a.wd + q % HX) * a.ldx + 8 * c) * 2u;
+    }
   }
   int tx, ty, img;   // next tile to load
   bf16x8 rd[kDyPer], rx[kXPer];
   auto load = [&]() {
     const int x0 = tx * TX, y0 = ty * TY;
-    const long long org = (long long)img * a.h * a.wd;
+    const long long org = (long long)img * (PACKED ? per : 1) * a.h * a.wd;
     const bf16* dy = a.dy + org * a.lddy + co0;
     const bf16* xs = a.x + org * a.ldx + ci0;
-    if constexpr (BIG) {
+    if constexpr (PACKED) {
+      const int left = min(per, a.n - img * per);   // images of this tile
+      if constexpr (BIG) {
 #pragma unroll
-      for (int i = 0; i < kDyPer; ++i) {
-        const int v = tid + NT * i;
-        const int y = y0 + (pd_[i] >> 16), x = x0 + (pd_[i] & 0xFFFF);
-        rd[i] = bf16x8{};
-        if (y < a.h && x < a.wd)
-          rd[i] = *reinterpret_cast<const bf16x8*>(dy + ((long long)y * a.wd + x) * a.lddy +
-                                                   8 * (v % (CO / 8)));
-      }
+        for (int i = 0; i < kDyPer; ++i) {
+          const int c = (tid + NT * i) % (CO / 8), k = pd_[i] >> 10;
+          const int y = y0 + (pd_[i] >> 5 & 31), x = x0 + (pd_[i] & 31);
+          rd[i] = bf16x8{};
+          if (pd_[i] >= 0 && k < left && y < a.h && x < a.wd)
+            rd[i] = *reinterpret_cast<const bf16x8*>(
+                dy + (((long long)k * a.h + y) * a.wd + x) * a.lddy + 8 * c);
+        }
 #pragma unroll
-      for (int i = 0; i < kXPer; ++i) {
-        const int v = tid + NT * i;
-        const int y = y0 - 1 + (px_[i] >> 16), x = x0 - 1 + (px_[i] & 0xFFFF);
-        rx[i] = bf16x8{};
-        if (v < kXVec && y >= 0 && y < a.h && x >= 0 && x < a.wd)
-          rx[i] = *reinterpret_cast<const bf16x8*>(xs + ((long long)y * a.wd + x) * a.ldx +
-                                                   8 * (v % (CI / 8)));
+        for (int i = 0; i < kXPer; ++i) {
+          const int c = (tid + NT * i) % (CI / 8), k = px_[i] >> 10;
+          const int y = y0 - 1 + (px_[i] >> 5 & 31), x = x0 - 1 + (px_[i] & 31);
+          rx[i] = bf16x8{};
+          if (px_[i] >= 0 && k < left && y >= 0 && y < a.h && x >= 0 && x < a.wd)
+            rx[i] = *reinterpret_cast<const bf16x8*>(
+                xs + (((long long)k * a.h + y) * a.wd + x) * a.ldx + 8 * c);
+        }
+      } else {
+        // (images beyond the last lie beyond the resource)
+        const unsigned gone = unsigned((per - left) * a.h * a.wd) * 2u;
+        const Rsrc dr = image_rsrc(dy, a.dybytes - gone * unsigned(a.lddy));
+        const Rsrc xr = image_rsrc(xs, a.xbytes - gone * unsigned(a.ldx));
+        const unsigned tb = unsigned((y0 * a.wd + x0) * a.lddy) * 2u;
+        const unsigned xb = unsigned(((y0 - 1) * a.wd + x0 - 1) * a.ldx) * 2u;   // (may wrap)
+#pragma unroll
+        for (int i = 0; i < kDyPer; ++i) {
+          const bool in =
+              pd_[i] >= 0 && y0 + (pd_[i] >> 5 & 31) < a.h && x0 + (pd_[i] & 31) < a.wd;
+          rd[i] = load8(dr, in ? od[i] + tb : kOutside);
+        }
+#pragma unroll
+        for (int i = 0; i < kXPer; ++i) {
+          const bool in = px_[i] >= 0 &&
+                          unsigned(y0 - 1 + (px_[i] >> 5 & 31)) < unsigned(a.h) &&
+                          unsigned(x0 - 1 + (px_[i] & 31)) < unsigned(a.wd);
+          rx[i] = load8(xr, in ? ox[i] + xb : kOutside);
+        }
       }
     } else {
       const Rsrc dr = image_rsrc(dy, a.dybytes), xr = image_rsrc(xs, a.xbytes);
@@ -1109,6 +1170,14 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
       const int buf = (u - u0) & 1;
       const char* d = pd + buf * kStage;
       const char* b = px + buf * kStage;
+      unsigned cols = 0, rows = 0;   // bit: column, row of the tile inside an image
+      if constexpr (masked) {
+        for (int i = 0; i < TX; ++i) {
+          int r0 = 0, c0 = 0, r = i, c = i, k;
+          if (place(r0, c, k) && mx * TX + c < a.wd) cols |= 1u << i;
+          if (place(r, c0, k) && my * TY + r < a.h) rows |= 1u << i;
+        }
+      }
       bf16x8 B[3][3];
 #pragma unroll
       for (int j = 0; j < RW; ++j) {
@@ -1121,10 +1190,10 @@ __global__ __launch_bounds__(512, 2) void wgrad_tile_kernel(WgradGroup G) {
             if constexpr (masked) {
 #pragma unroll
               for (int v = 0; v < 8; ++v)
-                if (mx * TX + 8 * (lane >> 5) + v >= a.wd) B[(j + k) % 3][c][v] = (bf16)0.f;
+                if (!((cols >> (8 * (lane >> 5) + v)) & 1)) B[(j + k) % 3][c][v] = (bf16)0.f;
             }
           }
-        if (masked && my * TY + RW * wk + j >= a.h) continue;   // uniform
+        if (masked && !((rows >> (RW * wk + j)) & 1)) continue;   // uniform
         const bf16x8 A = lds_tr8(d + j * TX * SD, d + (j * TX + 4) * SD);
 #pragma unroll
         for (int t = 0; t < 9; ++t) acc[t] = mfma32(A, B[(j + t / 3) % 3][t % 3], acc[t]);
@@ -1262,12 +1331,23 @@ __global__ __launch_bounds__(256) void sum_splits_kernel(SumArgs a) {
 // In a group (per_block > 0) that many tiles per block, more shares than
 // eight in multiples of eight (one per XCD).
 struct WgradPlan {
-  int tiles_x, tiles_y, units, splits;
+  int ax, ay, tiles_x, tiles_y, units, splits;
 };
 
+// Pixel tiles.  Images of up to seven pixels a side lie several to a tile, with a
+// row or column of zeros between them (128 -> 128 channels: 12 000 images of 1 x 1,
+// 64 to a tile, 851 us with a tile each, 31 so; 3750 of 4 x 4, nine to a tile, 276
+// and 47).
+WgradPlan wgrad_tiles(int n, int h, int wd) {
+  WgradPlan p{17 / (wd + 1), 17 / (h + 1), (wd + 15) / 16, (h + 15) / 16, 0, 0};
+  if (p.ax < 1) p.ax = 1;
+  if (p.ay < 1) p.ay = 1;
+  p.units = (n + p.ax * p.ay - 1) / (p.ax * p.ay) * p.tiles_x * p.tiles_y;
+  return p;
+}
+
 WgradPlan wgrad_plan(int n, int h, int wd, int cin, int cout, int per_block = 0) {
-  WgradPlan p{(wd + 15) / 16, (h + 15) / 16, 0, 0};
-  p.units = n * p.tiles_x * p.tiles_y;
+  WgradPlan p = wgrad_tiles(n, h, wd);
   if (per_block > 0) {
     const int s = (p.units + per_block - 1) / per_block;
     p.splits = s < 8 ? s : std::min(s / 8 * 8, 1024);
@@ -1820,13 +1900,15 @@ static int launch_fields(const float* out, int ldo, int n, int res, const float*
 
 // Adds a layer to a group; returns the floats of `work` it uses.
 static long long add_wgrad(WgradGroup& g, const WgradPlan& p, const bf16* dy, int lddy,
-                           const bf16* x, int ldx, float* dw, float* db, int h, int wd, int cin,
-                           int cout, float* work) {
+                           const bf16* x, int ldx, float* dw, float* db, int n, int h, int wd,
+                           int cin, int cout, float* work) {
   WgradLayer& l = g.l[g.layers];
   const long long wcount = 9LL * cin * cout;
+  const int per = p.ax * p.ay;
   l = WgradLayer{dy, x, work, db ? work + p.splits * wcount : nullptr, dw, db, lddy, ldx, h, wd,
                  cin, cout, p.tiles_x, p.tiles_y, p.units, p.splits, 0,
-                 (unsigned)image_bytes(h, wd, lddy, 32), (unsigned)image_bytes(h, wd, ldx, 32)};
+                 (unsigned)image_bytes(per * h, wd, lddy, 32),
+                 (unsigned)image_bytes(per * h, wd, ldx, 32), n, p.ax, p.ay};
   if (g.layers) {
     const WgradLayer& q = g.l[g.layers - 1];
     l.first = q.first + (q.splits * (q.cin / 32) * (q.cout / 32) + 7) / 8 * 8;
@@ -1839,19 +1921,31 @@ static long long add_wgrad(WgradGroup& g, const WgradPlan& p, const bf16* dy, in
 static int launch_wgrad(const WgradGroup& g, hipStream_t st) {
   const WgradLayer& e = g.l[g.layers - 1];
   const dim3 grid(e.first + e.splits * (e.cin / 32) * (e.cout / 32)), block(512);
-  bool big = false, ragged = false;
+  WgradForm form = kWgradFull;
   for (int k = 0; k < g.layers; ++k) {
     const WgradLayer& l = g.l[k];
-    ragged = ragged || l.h % 16 || l.wd % 16;
-    big = big || image_bytes(l.h, l.wd, l.lddy, 32) > kMaxRsrc ||
-          image_bytes(l.h, l.wd, l.ldx, 32) > kMaxRsrc;
+    const int rows = l.ax * l.ay * l.h;
+    const bool big = image_bytes(rows, l.wd, l.lddy, 32) > kMaxRsrc ||
+                     image_bytes(rows, l.wd, l.ldx, 32) > kMaxRsrc;
+    form = std::max(form, big                     ? kWgradBig
+                          : l.ax * l.ay > 1       ? kWgradPacked
+                          : l.h % 16 || l.wd % 16 ? kWgradRagged
+                                                  : kWgradFull);
   }
-  if (big)
-    hipLaunchKernelGGL((wgrad_tile_kernel<true, true>), grid, block, 0, st, g);
-  else if (ragged)
-    hipLaunchKernelGGL((wgrad_tile_kernel<false, true>), grid, block, 0, st, g);
-  else
-    hipLaunchKernelGGL((wgrad_tile_kernel<false, false>), grid, block, 0, st, g);
+  switch (form) {
+    case kWgradFull:
+      hipLaunchKernelGGL(wgrad_tile_kernel<kWgradFull>, grid, block, 0, st, g);
+      break;
+    case kWgradRagged:
+      hipLaunchKernelGGL(wgrad_tile_kernel<kWgradRagged>, grid, block, 0, st, g);
+      break;
+    case kWgradPacked:
+      hipLaunchKernelGGL(wgrad_tile_kernel<kWgradPacked>, grid, block, 0, st, g);
+      break;
+    default:
+      hipLaunchKernelGGL(wgrad_tile_kernel<kWgradBig>, grid, block, 0, st, g);
+      break;
+  }
   UCHECK(hipGetLastError());
   SumArgs sums{};
   sums.layers = g.layers;
@@ -1928,7 +2022,7 @@ int unet_conv3x3_bwd_weight(const void* dy, int32_t lddy, const void* x, int32_t
     return fail(UNET_EINVAL, "bwd_weight: bad ld");
   WgradGroup g{};
   add_wgrad(g, wgrad_plan(n, h, wd, cin, cout), static_cast<const bf16*>(dy), lddy,
-            static_cast<const bf16*>(x), ldx, dw, dbias, h, wd, cin, cout, work);
+            static_cast<const bf16*>(x), ldx, dw, dbias, n, h, wd, cin, cout, work);
   return launch_wgrad(g, as_stream(stream));
 }
 
@@ -2178,8 +2272,8 @@ int forward_impl(unet* net, const bf16* x0, int n, float* out) {
 int wgrad_per_block(int res, int n) {
   long long tiles = 0;
   for (const Conv& c : kConvs) {
-    const int t = ((res >> c.level) + 15) / 16;
-    tiles += (long long)n * t * t * (c.cin / 32) * (c.cout / 32);
+    const int s = res >> c.level;
+    tiles += (long long)wgrad_tiles(n, s, s).units * (c.cin / 32) * (c.cout / 32);
   }
   return (int)std::min<long long>(std::max<long long>(tiles / 1024, 1), 12);
 }
@@ -2194,7 +2288,7 @@ int conv_backward(unet* net, int k, int n, const bf16* dy, int lddy, bool need_d
   const int s = side(net, c.level);
   used += add_wgrad(g, wgrad_plan(n, s, s, c.cin, c.cout, per_block), dy, lddy,
                     net->act[c.in] + c.in_off, kBuf[c.in].ch, net->grad + c.w_off,
-                    net->grad + c.b_off, s, s, c.cin, c.cout, net->wwork + used);
+                    net->grad + c.b_off, n, s, s, c.cin, c.cout, net->wwork + used);
   if (!need_dx) return UNET_OK;
   ConvArgs a{};
   a.x = dy;

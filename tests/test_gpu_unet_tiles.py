@@ -336,3 +336,48 @@ def test_weight_gradient_of_inputs_that_are_not_finite(U, n, h, w, cin, cout):
     bound = np.abs(dyr).reshape(-1, cout).sum(0).max() * np.abs(x[np.isfinite(x)]).max()
     assert np.abs(got[finite] - want[finite]).max() <= 1e-5 * bound
     assert np.isfinite(host(db)).all()
+
+
+@pytest.mark.parametrize("n,h,w", [
+    (1, 1, 1), (63, 1, 1), (65, 1, 1), (300, 1, 1), (26, 2, 2), (40, 3, 5), (10, 4, 4), (9, 4, 4),
+    (5, 7, 7), (4, 7, 7), (7, 6, 1), (9, 1, 7), (3, 5, 40), (5, 40, 6), (17, 1, 33), (3, 200, 1),
+    (3, 7, 8), (3, 8, 7),
+])
+def test_weight_gradient_of_small_images(U, n, h, w):
+    """Several images to a pixel tile, full and partly filled, packed along one side
+    or both; image sizes around the largest that is packed."""
+    import torch
+    print("[gpu-case] weight gradient, small images", n, h, w, flush=True)
+    rng = np.random.default_rng(27)
+    cin, cout = 64, 32
+    dyf, xf = bf(rng, n, h, w, cout + 8), bf(rng, n, h, w, cin + 32)
+    dy, x = dyf[..., :cout], xf[..., :cin]
+    dw_ref, db_ref = R.conv3x3_bwd_weight(dy, x)
+    bound, _ = R.conv3x3_bwd_weight(np.abs(dy), np.abs(x))
+    dw, db = U.conv3x3_bwd_weight(dev(dyf, torch.bfloat16), dev(xf, torch.bfloat16), cin, cout)
+    assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()
+    assert (np.abs(host(db) - db_ref) <= 1e-5 * np.abs(dy).reshape(-1, cout).sum(0) + 1e-6).all()
+    # an infinity stays in its image
+    x[n // 2, h - 1, w - 1, 0] = np.inf
+    xf[..., :cin] = x
+    dwi, _ = U.conv3x3_bwd_weight(dev(dyf, torch.bfloat16), dev(xf, torch.bfloat16), cin, cout)
+    got = host(dwi)
+    np.testing.assert_array_equal(got[:, :, 1:], host(dw)[:, :, 1:])
+    sees = [t for t in range(9) if 0 <= h - 1 - (t // 3 - 1) < h and 0 <= w - 1 - (t % 3 - 1) < w]
+    assert not np.isfinite(got[:, sees, 0]).any()
+    assert np.isfinite(got[:, [t for t in range(9) if t not in sees], 0]).all()
+
+
+def test_small_images_with_a_wide_stride(U):
+    """Images of a few pixels whose pixel stride makes a tile of them 2 GB."""
+    import torch
+    print("[gpu-case] small images, 2 GB tile", flush=True)
+    rng = np.random.default_rng(28)
+    n, ld = 9, 2 ** 27 + 8
+    x, dy = bf(rng, n, 1, 1, 32), bf(rng, n, 1, 1, 32)
+    xd = torch.empty(n * ld, device="cuda", dtype=torch.bfloat16).view(n, 1, 1, ld)
+    xd[..., :32] = dev(x, torch.bfloat16)
+    dw, _ = U.conv3x3_bwd_weight(dev(dy, torch.bfloat16), xd, 32, 32)
+    dw_ref, _ = R.conv3x3_bwd_weight(dy, x)
+    bound, _ = R.conv3x3_bwd_weight(np.abs(dy), np.abs(x))
+    assert (np.abs(host(dw) - dw_ref) <= 1e-5 * bound + 1e-6).all()

@@ -174,3 +174,13 @@ def test_wide_convolutions(program, n, h, w, cin, cout, kernel):
 def test_many_small_images(program, n, h, w, cin, cout, kernel):
     (launch,) = program("unet_launches", "fwd", n, h, w, cin, cout)
     assert launch[0] == kernel
+
+
+@pytest.mark.parametrize("n,h,w,blocks", [
+    (64, 1, 1, 1), (65, 1, 1, 2), (25, 2, 2, 1), (9, 4, 4, 1), (10, 4, 4, 2), (4, 7, 7, 1),
+    (2, 8, 8, 2), (8, 1, 16, 1), (2, 7, 40, 2), (3, 40, 7, 4), (1, 16, 16, 1),
+])
+def test_small_images_share_the_tiles_of_a_weight_gradient(program, n, h, w, blocks):
+    """Blocks for 32 x 32 channels: the power of two up to the pixel tiles."""
+    tile, _ = program("unet_launches", "bwdw", n, h, w, 32, 32)
+    assert tile[:3] == ["wgrad_tile_kernel", str(blocks), "1"]
