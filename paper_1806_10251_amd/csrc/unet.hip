@@ -2007,7 +2007,7 @@ int unet_conv3x3_bwd_data(const void* dy, int32_t lddy, const void* w, void* dx,
 }
 
 int64_t unet_wgrad_work_floats(int32_t n, int32_t h, int32_t wd, int32_t cin, int32_t cout) {
-  if (n <= 0 || h <= 0 || wd <= 0 || cin <= 0 || cout <= 0) return 0;
+  if (n <= 0 || h <= 0 || wd <= 0 || cin < 32 || cout < 32) return 0;   // (nothing to do)
   return (int64_t)wgrad_plan(n, h, wd, cin, cout).splits * (9LL * cin * cout + cout);
 }
 

@@ -42,5 +42,9 @@ int main(int argc, char** argv) {
   if (what == "bwdw")
     return unet_conv3x3_bwd_weight(mem, co, mem, ci, (float*)mem, (float*)mem, n, h, w, ci, co,
                                    (float*)mem, nullptr);
+  if (what == "work") {
+    std::printf("%lld\n", (long long)unet_wgrad_work_floats(n, h, w, ci, co));
+    return 0;
+  }
   return 2;
 }

@@ -184,3 +184,12 @@ def test_small_images_share_the_tiles_of_a_weight_gradient(program, n, h, w, blo
     """Blocks for 32 x 32 channels: the power of two up to the pixel tiles."""
     tile, _ = program("unet_launches", "bwdw", n, h, w, 32, 32)
     assert tile[:3] == ["wgrad_tile_kernel", str(blocks), "1"]
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,floats", [
+    (1, 16, 16, 32, 32, 9 * 1024 + 32), (1, 16, 16, 16, 32, 0), (1, 16, 16, 32, 8, 0),
+    (2, 3, 5, 0, 32, 0), (0, 16, 16, 32, 32, 0),
+])
+def test_scratch_of_a_weight_gradient(program, n, h, w, cin, cout, floats):
+    """Channel counts that the gradient refuses need none (and end no process)."""
+    assert program("unet_launches", "work", n, h, w, cin, cout) == [[str(floats)]]
