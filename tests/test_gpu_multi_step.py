@@ -209,3 +209,87 @@ def test_batch_windows(check_every):
             lats[i].step(1)
         for p, q in zip(b.fields(i, ny, nx), lats[i].fields()):
             np.testing.assert_array_equal(np.asarray(p), np.asarray(q))
+
+
+@pytest.mark.parametrize("nx,ny", [(200, 190), (700, 333)])
+def test_changes_of_storage_and_launch_shape(nx, ny):
+    """Storage and launch shape change in the middle of a run of a lattice with a
+    mask: the two-step shape and its marks are chosen again."""
+    from paper_1806_10251_amd import lbm
+    print("[gpu-case] two-step changes", nx, ny, flush=True)
+    m = obstacles(nx, ny)
+    a, b = pair(nx, ny, CHANNEL, "f64", mask=m)
+    shapes = lbm.launch_shapes()
+
+    def both(n):
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        for p, q in zip(a.fields(), b.fields()):
+            np.testing.assert_array_equal(p, q)
+
+    both(5)
+    for storage in ("f32", "f16", "f32", "f64"):
+        a.set_storage(storage)
+        b.set_storage(storage)
+        both(6)
+    for shape in ((8, 2), (4, 1)):
+        assert shape in shapes
+        a.set_launch(*shape)
+        b.set_launch(*shape)
+        both(7)
+
+
+def test_steps_on_a_stream_of_the_caller():
+    """Lattices and a batch on streams of their own, their steps queued in turn."""
+    import torch
+    from paper_1806_10251_amd import lbm
+    print("[gpu-case] two-step streams", flush=True)
+    a, b = pair(123, 90, CAVITY, "f32", mask=obstacles(123, 90))
+    c, d = pair(250, 61, CHANNEL, "f64")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    a.set_stream(streams[0])
+    c.set_stream(streams[1])
+    bat, lats = batch_of([(64, 64, CAVITY), (90, 33, CHANNEL)], "f32", 10, [None, None])
+    bat.set_stream(streams[2])
+    for n in (3, 8, 25):
+        a.step(n)
+        c.step(n)
+        bat.run(0.0, n)
+    for one in (b, d, *lats):
+        for _ in range(36):
+            one.step(1)
+    got = [a.fields(), c.fields(), bat.fields(0, 64, 64), bat.fields(1, 33, 90)]
+    for p, q in zip(got, (b, d, *lats)):
+        for x, y in zip(p, q.fields()):
+            np.testing.assert_array_equal(x, y)
+
+
+def test_fp64_batch_beyond_the_last_level_cache():
+    """FP64 keeps two rows per wavefront whatever the size: three lattices of
+    1600 x 1000 hold 0.7 GB."""
+    shapes = [(1600, 1000, CHANNEL), (1600, 1000, CAVITY), (1600, 1000, (PERIODIC,) * 4)]
+    print("[gpu-case] two-step batch, FP64 beyond the cache", flush=True)
+    masks = [obstacles(1600, 1000), None, None]
+    b, lats = batch_of(shapes, "f64", 10, masks)
+    for n in (7, 16):
+        b.run(0.0, n)
+        for i, (nx, ny, _) in enumerate(shapes):
+            for _ in range(n):
+                lats[i].step(1)
+            fluid = np.ones((ny, nx), bool) if masks[i] is None else masks[i] == 0
+            for p, q in zip(b.fields(i, ny, nx), lats[i].fields()):
+                np.testing.assert_array_equal(np.asarray(p)[fluid], np.asarray(q)[fluid])
+
+
+@pytest.mark.parametrize("nx,ny,sides,storage", [
+    (180, 700, CAVITY, "f32"), (190, 800, CHANNEL, "f16"), (129, 1025, (PERIODIC,) * 4, "f64"),
+    (64, 1000, CAVITY, "f64"), (512, 512, CAVITY, "f64"),
+])
+def test_lattices_around_the_rule(nx, ny, sides, storage):
+    """Lattices that step one by one by the rule on their tiles, and one whose mask
+    (a third of the nodes solid) decides it."""
+    m = None
+    if nx == ny:
+        m = (np.random.default_rng(9).random((ny, nx)) > 0.66).astype(np.uint8)
+    same_after(nx, ny, sides, storage, steps=5, mask=m)
