@@ -220,8 +220,8 @@ int lbm_set_force_field(lbm_ctx* ctx, const double* fx, const double* fy);
  * holding `rows` lattice rows (the autotuner's knobs).  Supported pairs are
  * listed by lbm_launch_shapes.  With the default shape (4, 1) the library runs
  * consecutive plain steps of the default kernel two per launch where that is
- * faster (the same results bit for bit); every other shape runs step by step.
- * Rebuilds cached graphs. */
+ * faster (the same results bit for bit while all densities are finite); every
+ * other shape runs step by step.  Rebuilds cached graphs. */
 int lbm_set_launch(lbm_ctx* ctx, int32_t by, int32_t rows);
 int lbm_get_launch(lbm_ctx* ctx, int32_t* by, int32_t* rows);
 /* Writes up to cap (by, rows) pairs into shapes[2*i], shapes[2*i+1]; returns

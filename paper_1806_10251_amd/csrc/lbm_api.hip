@@ -147,7 +147,7 @@ long long multi_tiles(const lbm_ctx* c, int shape) {
 // - Larger lattices: two rows per wavefront (10 output rows: 1024^2 FP32
 //   13.3 | 10.9, FP64 24.0 | 19.0 us, 2048^2 FP64 117 | 73.5 us); beyond the
 //   last-level cache, except in FP64 (registers), four rows (26 output rows:
-//   4096^2 FP32 264 | 158 us, channel 4096 x 1024 FP16 52.5 | 46.5 us).
+//   4096^2 FP32 264 | 158 us, channel 4096 x 1024 FP16 52.5 | 47.1 us).
 // - The ring costs instructions: the rows a pair collides over those of two
 //   single steps (work) are 1.1 to 1.4 where the tiles fit.  At 1.6 (59 to 64
 //   columns of 58 over 64, 175 to 192 of 3 x 58 over 3 x 64) every storage

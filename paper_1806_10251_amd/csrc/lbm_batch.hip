@@ -573,9 +573,12 @@ int batch_multi_shape(lbm_batch* b) {
 // tiles share its L2, the dearest items first, so that the last blocks are
 // short ones.  Ranges that end earlier are padded with empty items (case -1).
 // Cost relative to the others: interior 1, boundary 2, with the outlet column 3
-// (12 FP64 cases with sides of 64 to 128, channels among them: 17.3 us per step
-// with equal weights, 13.8 with these, 14.9 with 2 : 3 : 4).  Linear in the
-// items, as it is host time of a run (64 cases, about 13 000 items).
+// (us per step in the order of the tiles | ordered with ranges of equal weights |
+// with these, mixes of cavities and channels: 12 FP64 cases with sides of 64 to
+// 128 18.1 | 16.1 | 14.8, 16 FP64 of 64 to 256 41.0 | 35.6 | 35.6, 32 FP32 of
+// 64 to 256 29.2 | 26.9 | 27.2, 20 FP32 of 64 to 512 78.3 | 74.6 | 75.7: the
+// order pays everywhere, the weights in few, dear tiles).  Linear in the items,
+// as it is host time of a run.
 std::vector<int2> multi_items(lbm_batch* b) {
   std::vector<int2> items;
   std::vector<uint8_t> cost;

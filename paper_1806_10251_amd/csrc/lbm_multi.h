@@ -15,14 +15,19 @@
 // the edge node (for the density only), across a periodic side the region
 // simply continues.  Arithmetic, storage rounding (values go through the
 // storage type between the steps) and the seeds of the stochastic rounding
-// are those of the single step, so any mix of both gives the same bits.
+// are those of the single step, so any mix of both gives the same bits as long
+// as the densities are finite (the single step takes a density of +Inf for a
+// solid node, here the mask decides; only a state that has diverged has one).
 //
-// Bound: 4096^2 FP32 spends 76 % of its time issuing vector instructions (225
-// per 64 nodes and step, the same count as the single step with its halo
-// work); a pair moves 1.36 GB to and from HBM instead of 2.42 GB.
-// Non-temporal stores, which the single step uses beyond the last-level
-// cache, are slower here (151 -> 184 us: the tiles' rows do not start on cache
-// lines and neighbours' partial lines merge in L2).  Three or four steps
+// Bound: vector instructions.  4096^2 FP32 issues them in 77 % of its cycles,
+// 225 per 64 nodes of each row that a step collides, the ring's rows included;
+// that is 269 per 64 nodes of the lattice and step (the single step with its
+// halo work 283).  A pair moves 1.36 GB to and from HBM, two single steps 2.43
+// GB.  1024^2 FP32: 75 % of the time, 314 instructions against 286, 79 MB
+// against 154 MB.  Non-temporal stores, which the single step uses beyond the
+// last-level cache, are slower here (4096^2 from rest 151 -> 184 us per step:
+// the tiles' rows do not start on cache lines and neighbours' partial lines
+// merge in L2).  Three or four steps
 // save traffic that no longer bounds a large lattice and add ring, and in a
 // small one a step inside the block costs 2.5-3 us at four wavefronts per SIMD
 // (32^2 FP64 2.75 us per step in pairs, 2.9-6.0 in threes and fours; 256^2 FP32

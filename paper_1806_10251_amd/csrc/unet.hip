@@ -1759,7 +1759,10 @@ __global__ __launch_bounds__(256) void fields_kernel(const float* out, int ldo, 
 // Bound by latency (three dependent passes over the case): 1024 threads with
 // 16 independent loads each in flight per field, kept in registers from pass to
 // pass where they hold the case (256 threads with one load: 96 us for 12 cases
-// of 128 x 128; eight loads and every pass from memory: 19.2 us; now 17).
+// of 128 x 128; eight loads and every pass from memory: 19.2 us; now 17).  A
+// case one node larger than they hold is read three times: all output maps of 12
+// cases take 25.5 us at 128 x 128 and 34.2 at 129 x 129, of 64 cases 56.8 and
+// 64.9.
 constexpr int kMassThreads = 1024, kMassLoads = 16;
 __global__ __launch_bounds__(kMassThreads) void mass_fix_kernel(float* rho, float* ux, float* uy,
                                                                 const uint8_t* solid, int nx,
